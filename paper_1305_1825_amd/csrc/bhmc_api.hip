@@ -123,9 +123,13 @@ static double* scratch_address(int dev) {
 
 // ------------------------------------------------------------ handle
 struct bhmc_tree {
-    int R = 0, p = 0, nterms = 0, mstride = 0;
+    int R = 0, p = 0, nterms = 0, mstride = 0, hstride = 0;
     hipStream_t stream = nullptr;
     std::vector<bhmc_params> params;
+    // Commits repair what the replica's far field reads: the expansion rows H, or with a
+    // single-precision far field the Cartesian moments M and their copy.  Per replica: moves were
+    // committed since the other of the two was last computed.
+    std::vector<uint8_t> m_stale, h_stale;
     Rep* host = nullptr;             // pinned mirror of the descriptor table
     char* pin = nullptr;             // pinned staging for every other host<->device copy
     size_t pin_bytes = 0;
@@ -156,6 +160,7 @@ struct bhmc_tree {
     int moves_per_round = 0;         // 0: as many as the order allows; 1: the move-by-move kernel
     bool rounds_ok = true;           // the rounds kernel needs N_0 = 0 and no line images on every replica
     bool has_lines = false;          // some replica has line images
+    bool has_far32 = false;          // some replica has a single-precision far field
     int mc_grid = 1;
     int mc_wide = 1;                 // one replica: the 512-thread Metropolis kernel
     hipGraph_t graph = nullptr;
@@ -386,7 +391,7 @@ static bhmc_status alloc_phase2(bhmc_tree* t, int r) {
     if (t->arena2[r]) { hipFree(t->arena2[r]); t->arena2[r] = nullptr; }
     const size_t nc = h.ncell, nl = h.nleaf, np = h.pool;
     size_t b = align_up(32 * nc) + align_up(16 * nc) + 4 * align_up(4 * nc) + align_up(8 * nc) +
-               align_up(8 * nc * (size_t)t->mstride) + 3 * align_up(4 * nl) + align_up(32 * np) +
+               align_up(8 * nc * (size_t)t->mstride) + align_up(8 * nc * (size_t)t->hstride) + 3 * align_up(4 * nl) + align_up(32 * np) +
                align_up(4 * np) + (h.far32 ? align_up(4 * nc * (size_t)t->mstride) : 0);
     HIP_TRY(hipMalloc(&t->arena2[r], b));
     Carver c{(char*)t->arena2[r]};
@@ -396,6 +401,7 @@ static bhmc_status alloc_phase2(bhmc_tree* t, int r) {
     h.clevel = c.take<int>(nc); h.cbegin = c.take<int>(nc); h.cend = c.take<int>(nc);
     h.ckey = c.take<uint64_t>(nc);
     h.M = c.take<double>(nc * (size_t)t->mstride);
+    h.H = c.take<double>(nc * (size_t)t->hstride);
     h.lcell = c.take<int>(nl); h.lbase = c.take<int>(nl); h.lcap = c.take<int>(nl);
     h.pool4 = c.take<double4>(np); h.pidx = c.take<int>(np);
     h.M32 = h.far32 ? c.take<float>(nc * (size_t)t->mstride) : nullptr;
@@ -462,6 +468,41 @@ static const char* status_name(int s) {
     }
 }
 
+// Moments of the replicas in `list` (device copy dlist) from the current members of their leaves.
+static void fresh_moments(bhmc_tree* t, const int* list, int n, const int* dlist) {
+    bhmc::launch_moments(t->stream, n, t->reps, dlist, t->nterms, t->mstride, t->host, list);
+    for (int i = 0; i < n; ++i) t->m_stale[list[i]] = 0;
+}
+
+// Expansion rows of the replicas in `list` from their moments.
+static void expand(bhmc_tree* t, const int* list, int n, const int* dlist) {
+    int maxc = 1;
+    for (int i = 0; i < n; ++i) { maxc = std::max(maxc, t->host[list[i]].ncell); t->h_stale[list[i]] = 0; }
+    t->ops->expand(t->stream, n, t->reps, dlist, maxc);
+}
+
+// Both from the current members of the leaves.
+static void fresh_expansions(bhmc_tree* t, const int* list, int n, const int* dlist) {
+    fresh_moments(t, list, n, dlist);
+    expand(t, list, n, dlist);
+}
+
+// Moves of replica r may have been committed.
+static void moves_ran(bhmc_tree* t, int r) {
+    if (t->host[r].far32) t->h_stale[r] = 1;
+    else t->m_stale[r] = 1;
+}
+
+// M of replica r as of its current members, for the calls that read it.
+static bhmc_status current_moments(bhmc_tree* t, int r) {
+    if (!t->m_stale[r]) return BHMC_OK;
+    bhmc_status st = h2d(t, t->list_one, &r, sizeof(int));
+    if (st) return st;
+    fresh_moments(t, &r, 1, t->list_one);
+    HIP_TRY(hipGetLastError());
+    return BHMC_OK;
+}
+
 // Build (or rebuild) the replicas in `list`.  x == nullptr rebuilds from the
 // replicas' own current ions.
 static bhmc_status build_list(bhmc_tree* t, const std::vector<int>& list, const double* x,
@@ -516,7 +557,7 @@ static bhmc_status build_list(bhmc_tree* t, const std::vector<int>& list, const 
     if ((st = download(t))) return st;  // cells per level size the moment launches
     for (int r : list)
         if (t->host[r].status) return fail(BHMC_EHIP, "replica %d: %s", r, status_name(t->host[r].status));
-    bhmc::launch_moments(t->stream, nr, t->reps, dlist, t->nterms, t->mstride, t->host, list.data());
+    fresh_expansions(t, list.data(), nr, dlist);
     HIP_TRY(hipGetLastError());
     if ((st = download(t))) return st;
     for (int r : list)
@@ -556,6 +597,9 @@ static bhmc_status create(const bhmc_params* params, int32_t R, const int64_t* n
     t->p = params[0].p;
     t->nterms = bhmc::nterms_of(t->p);
     t->mstride = bhmc::mstride_of(t->p);
+    t->hstride = bhmc::hstride_of(t->p);
+    t->m_stale.assign(R, 0);
+    t->h_stale.assign(R, 0);
     t->stream = (hipStream_t)stream;
     t->params.assign(params, params + R);
     if (hipHostMalloc((void**)&t->host, sizeof(Rep) * R, hipHostMallocDefault) != hipSuccess) {
@@ -567,6 +611,7 @@ static bhmc_status create(const bhmc_params* params, int32_t R, const int64_t* n
     t->ops = bhmc::eval_ops(t->p);
     for (int r = 0; r < R; ++r) {
         if (params[r].line_images > 0) t->has_lines = true;
+        if (params[r].far_fp32) t->has_far32 = true;
         if (params[r].n0 != 0 || params[r].line_images > 0) t->rounds_ok = false;
     }
     std::vector<long long> off(R);
@@ -656,7 +701,8 @@ extern "C" bhmc_status bhmc_refresh_moments(bhmc_tree* t, int32_t replica) {
     bhmc_status st = check_rep(t, replica);
     if (st) return st;
     if ((st = h2d(t, t->list_one, &replica, sizeof(int)))) return st;
-    bhmc::launch_moments(t->stream, 1, t->reps, t->list_one, t->nterms, t->mstride, t->host, &replica);
+    const int r = replica;
+    fresh_expansions(t, &r, 1, t->list_one);
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipStreamSynchronize(t->stream));
     return BHMC_OK;
@@ -715,7 +761,8 @@ extern "C" bhmc_status bhmc_energy(bhmc_tree* t, int32_t replica, double* E_host
     const int n = t->host[replica].n;
     if ((st = ensure_eterm(t, n))) return st;
     for (;;) {
-        t->ops->energy(t->stream, t->reps, replica, n, phi_dev, t->eterm, energy_grid_bound(t), t->host[replica].nline);
+        t->ops->energy(t->stream, t->reps, replica, n, phi_dev, t->eterm, energy_grid_bound(t), t->host[replica].nline,
+                       t->host[replica].far32);
         HIP_TRY(hipGetLastError());
         bool again = false;
         if ((st = finish_energy(t, replica, n, E_host, "energy", &again)) || !again) return st;
@@ -734,7 +781,8 @@ extern "C" bhmc_status bhmc_energy_noalloc(bhmc_tree* t, int32_t replica, double
         return fail(BHMC_EINVAL, "replica %d has %d ions; the allocation-free energy takes at most %d", replica, n,
                     kScratchDoubles);
     if (!t->scratch) return fail(BHMC_EHIP, "scratch array not resolved");
-    t->ops->energy(t->stream, t->reps, replica, n, phi_dev, t->scratch, energy_grid_bound(t), t->host[replica].nline);
+    t->ops->energy(t->stream, t->reps, replica, n, phi_dev, t->scratch, energy_grid_bound(t), t->host[replica].nline,
+                       t->host[replica].far32);
     bhmc::launch_sum(t->stream, t->scratch, n, t->host[replica].l_B, E_dev);
     HIP_TRY(hipGetLastError());
     return BHMC_OK;
@@ -748,6 +796,7 @@ extern "C" bhmc_status bhmc_energy_grad(bhmc_tree* t, int32_t replica, double* d
     if (st) return st;
     if (!dEdr_dev || !dEdq_dev) return fail(BHMC_EINVAL, "null gradient output");
     if (!t->ops->grad) return fail(BHMC_EINVAL, "gradient not available for p = %d", t->p);
+    if ((st = current_moments(t, replica))) return st;
     const Rep& h = t->host[replica];
     const int n = h.n;
     if ((st = ensure_eterm(t, n))) return st;
@@ -794,7 +843,8 @@ static bhmc_status run_move(bhmc_tree* t, int64_t i, const double* r_new, int mo
     for (;;) {
         io = io_in;
         if ((st = h2d(t, t->io, &io, sizeof(io)))) return st;
-        t->ops->move(t->stream, t->reps, 0, t->io, t->has_lines ? 1 : 0);
+        if (mode == 1) moves_ran(t, 0);
+        t->ops->move(t->stream, t->reps, 0, t->io, t->has_lines ? 1 : 0, t->host[0].far32);
         HIP_TRY(hipGetLastError());
         if ((st = d2h(t, &io, t->io, sizeof(io)))) return st;
         if (io.status != -7) break;
@@ -847,6 +897,7 @@ static int rounds_of(const bhmc_tree* t) {
 static void launch_mc(bhmc_tree* t, hipStream_t s, bhmc::McArgs a, int grid, int wide) {
     const int bm = rounds_of(t);
     a.lines = t->has_lines ? 1 : 0;
+    a.far32 = t->has_far32 ? 1 : 0;
     if (bm <= 1) {
         t->ops->mc(s, t->reps, a, grid, wide);
     } else {
@@ -858,6 +909,7 @@ static void launch_mc(bhmc_tree* t, hipStream_t s, bhmc::McArgs a, int grid, int
 static bhmc_status run_replica_until_done(bhmc_tree* t, int r, const bhmc::McArgs& base, long long* rebuilds) {
     long long last_stop = -1;
     for (;;) {
+        moves_ran(t, r);
         bhmc::McArgs a = base;
         a.list = t->list_one;
         a.nlist = 1;
@@ -974,6 +1026,7 @@ static bhmc_status finish_sweep(bhmc_tree* t, const bhmc::McArgs& base, std::vec
         a.list = t->list_rest;
         a.nlist = (int)rest.size();
         bhmc::launch_reset_queue(t->stream, t->queue);
+        for (int r : rest) moves_ran(t, r);
         launch_mc(t, t->stream, a, std::min((int)rest.size(), t->mc_grid), t->mc_wide);
         HIP_TRY(hipGetLastError());
     }
@@ -1017,6 +1070,7 @@ extern "C" bhmc_status bhmc_batch_sweep(bhmc_tree* t, uint64_t seed, int32_t n_s
         }
     }
     for (int s = 0; s < n_sweeps; ++s) {
+        for (int r = 0; r < t->R; ++r) moves_ran(t, r);
         if (use_graph) {
             HIP_TRY(hipGraphLaunch(t->gexec, gs));
             if (gs != t->stream) HIP_TRY(hipStreamSynchronize(gs));
@@ -1219,6 +1273,7 @@ extern "C" bhmc_status bhmc_get_cells(bhmc_tree* t, int32_t r, int32_t* level, u
     }
     if (geo && (st = d2h(t, geo, h.cgeo, 32 * nc))) return st;
     if (moments) {
+        if ((st = current_moments(t, r))) return st;
         std::vector<double> rows(nc * (size_t)t->mstride);
         if ((st = d2h(t, rows.data(), h.M, sizeof(double) * rows.size()))) return st;
         for (size_t c = 0; c < nc; ++c)

@@ -63,6 +63,7 @@ struct Rep {
     uint64_t* ckey;                // smallest key of the cell
     int* cbegin; int* cend;        // build range in the sorted order
     double* M;                     // moments, cell-major: M[cell * nterms + k]
+    double* H;                     // expansion rows read by the far field: harmonic coefficients and centre
     float* M32;                    // single-precision copy read by the far field, or null
     int* lcell; int* lbase; int* lcap;
     double4* pool4;                // (x, y, z, q) in leaf slot order

@@ -7,16 +7,16 @@
 // sits in LDS, every lane classifies one (cell, target) entry, and a block
 // scan hands out slots in the far list, the near list and the next frontier,
 // so the order of every list, and therefore every sum, is deterministic.
-// Far cells are evaluated lane-per-cell with the recurrence of eq. 3.4 fused
-// into the dot product with the moments of eq. 3.3; near leaves are flattened
+// Far cells are evaluated lane-per-cell in the harmonic form of the expansion
+// of eq. 3.3 (below); near leaves are flattened
 // into (leaf, slot) pairs read from the leaf-ordered pool, so the lanes of a
 // wave read consecutive slots.
 //
 // Exclusion.  The mover i and its image are taken out of the source set: a
 // frontier entry carries two bits telling whether its cell holds them (the
 // bits follow the digits of their keys down the tree).  At most one far cell
-// per (target, excluded source) can hold one of them, so the corrected
-// moments M - q (r - c)^n of those cells are formed in LDS.
+// per (target, excluded source) can hold one of them; those cells go to a list
+// of their own and are evaluated less the expansion of the excluded source.
 #include "bhmc_dev.hpp"
 #include "bhmc_internal.hpp"
 
@@ -149,25 +149,308 @@ __device__ __forceinline__ int2 gload(const int2* p) {
 }
 __device__ __forceinline__ int gload(const int* p) { return *(GInt)p; }
 
-// sum_n T_n M^n, each T_n folded into the sum as soon as it exists
-template <int K, class MP>
-__device__ __forceinline__ void far_rec(double (&T)[NTERM], double Rx, double Ry, double Rz,
-                                        double ir2, MP __restrict__ Mc, double& acc) {
-    if constexpr (K < NTERM) {
-        if constexpr (K > 0) t_step<K>(T, Rx, Ry, Rz, ir2);
-        acc = fma(T[K], Mc[K], acc);
-        far_rec<K + 1>(T, Rx, Ry, Rz, ir2, Mc, acc);
+// ------------------------------------------------------------ harmonic form of the expansion
+// Up to order p the sum of eq. 3.3 over the C(p + 3, 3) Cartesian terms is, degree by
+// degree, sum_j q_j P_l(cos psi_j) |d_j|^l / |X|^(l + 1) (d_j = y_j - c, X = x - c), and
+// by the addition theorem of the Legendre polynomials that is a sum over the (p + 1)^2
+// solid harmonics:
+//   phi(x) = sum_{l <= p} sum_{m <= l} [Hc_lm Re A_lm(X) + Hs_lm Im A_lm(X)] / |X|^(2l + 1),
+//   A_lm(v) = (v_x + i v_y)^m a_lm(v_z, |v|^2),  a_mm = 1, a_{m+1,m} = v_z,
+//   a_lm = v_z a_{l-1,m} - beta_lm |v|^2 a_{l-2,m},  beta_lm = ((l-1)^2 - m^2) / ((2l-1)(2l-3)),
+//   H_lm = N_lm sum_j q_j A_lm(d_j),  N_lm = (2 - [m = 0]) ((2l-1)!!)^2 / ((l + m)! (l - m)!)
+// (a_lm is P_l^m without its (1 - z^2)^(m/2), scaled to leading coefficient one).  The
+// value is the one of the Cartesian sum up to rounding; it reads (p + 1)^2 coefficients
+// instead of C(p + 3, 3) (36 for 56 at p = 5, 81 for 165 at p = 8) and costs 5 FP64
+// instructions per (l, m) instead of 8 per Cartesian term, with no T_n held in registers:
+// 90 FP64 instructions a cell at p = 5 where the Cartesian form took about 450.  The far
+// cells were bound by the issue of those (32 of the 104 us of a round of eight moves on the
+// 10^4-ion colloid, 212 of 390 us in the sweep of 256 replicas at theta = 0.3, p = 5; now 21
+// and 73).
+// Row of a cell: the (c, s) pairs of m = 1..p (l = m..p each), the p + 1 coefficients of
+// m = 0, the centre.
+constexpr int NH = (P + 1) * (P + 1);
+constexpr int NPAIR = (P + 1) * (P + 2) / 2;
+constexpr int HCEN = NH;                   // centre at [NH], [NH + 1], [NH + 2]
+constexpr int HSTR = (NH + 3 + 1) & ~1;    // row stride, 16-byte rows
+
+// place of the (l, m) coefficient (of its c part for m >= 1; the s part follows it)
+constexpr int hplace(int l, int m) {
+    if (m == 0) return NH - (P + 1) + l;
+    int o = 0;
+    for (int k = 1; k < m; ++k) o += 2 * (P + 1 - k);
+    return o + 2 * (l - m);
+}
+constexpr double hbeta(int l, int m) {
+    return l < m + 2 ? 0.0 : (double)((l - 1) * (l - 1) - m * m) / (double)((2 * l - 1) * (2 * l - 3));
+}
+constexpr double hnorm(int l, int m) {
+    double v = m == 0 ? 1.0 : 2.0;
+    for (int k = 1; k <= l; ++k) v *= (double)(2 * k - 1) * (double)(2 * k - 1);
+    for (int k = 2; k <= l + m; ++k) v /= (double)k;
+    for (int k = 2; k <= l - m; ++k) v /= (double)k;
+    return v;
+}
+
+// sum_{lm} H_lm A_lm(X) / |X|^(2l+1) at X = (x, y, z): with w = 1 / |X|^2, u = z w and
+// zeta = (x + i y) w, each a_lm / |X|^(2(l-m)) obeys the recurrence above in (u, w), and the
+// powers of zeta come in by Horner's rule from m = p down.  The row is loaded in one or two
+// runs of columns ahead of their use (as many loads in flight as registers allow), and the
+// scheduling boundaries keep the compiler from computing every column's factors first.
+constexpr int kHRun = 64;  // doubles of a row held in registers at once
+constexpr int hsplit() {   // columns m >= hsplit() are the first run
+    if (NH <= kHRun) return 0;
+    int m = P;
+    while (m > 0 && hplace(m, m) + 2 * (P + 1 - m) > NH / 2 + P) --m;
+    return m + 1;
+}
+constexpr int kHSplit = hsplit();
+
+// column m of the recurrence: qc, qs = sum_l H_lm a_lm / |X|^(2(l-m)); h is the row from place base on
+template <int M, int N>
+__device__ __forceinline__ void far_column(const double (&h)[N], int base, double u, double w, double& qc, double& qs) {
+    constexpr int pl = hplace(M, M), st = M ? 2 : 1;
+    qc = h[pl - base];
+    qs = M ? h[pl + 1 - base] : 0.0;
+    double a0 = 1.0, a1 = u;
+#pragma unroll
+    for (int l = M + 1; l <= P; ++l) {
+        if (l > M + 1) {
+            const double bw = hbeta(l, M) * w;
+            const double a2 = l == M + 2 ? fma(u, a1, -bw) : fma(u, a1, -bw * a0);
+            a0 = a1; a1 = a2;
+        }
+        qc = fma(h[pl + st * (l - M) - base], a1, qc);
+        if (M) qs = fma(h[pl + st * (l - M) + 1 - base], a1, qs);
     }
 }
 
+template <int M, int LAST, int N>
+__device__ __forceinline__ void far_columns(const double (&h)[N], int base, double u, double w, double zx, double zy,
+                                            double& a, double& b) {
+    if constexpr (M >= LAST) {
+        double qc, qs;
+        far_column<M>(h, base, u, w, qc, qs);
+        if constexpr (M == P) {
+            a = qc; b = qs;
+        } else {
+            const double ta = fma(b, zy, fma(a, zx, qc));
+            if constexpr (M > 0) b = fma(b, zx, fma(-a, zy, qs));
+            a = ta;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        far_columns<M - 1, LAST>(h, base, u, w, zx, zy, a, b);
+    }
+}
+
+// Value at (tx, ty, tz) of an expansion row, its own centre included.
+template <class HP>
+__device__ __forceinline__ double far_row(HP __restrict__ H, double tx, double ty, double tz) {
+    // the columns of the first run take places 0 .. n1 - 1 (m = 1 .. p lie in this order in the
+    // row, so a first run of the columns m >= kHSplit is the tail of the pairs)
+    constexpr int lo = kHSplit ? hplace(kHSplit, kHSplit) : 0;         // first place of the first run
+    constexpr int n1 = (kHSplit ? NH - (P + 1) : NH) - lo;
+    const double x = tx - H[HCEN], y = ty - H[HCEN + 1], z = tz - H[HCEN + 2];
+    double a = 0.0, b = 0.0, u, w, zx, zy, ir;
+    {
+        double h[n1];
+#pragma unroll
+        for (int k = 0; k < n1; ++k) h[k] = H[lo + k];
+        const double r2 = x * x + y * y + z * z;
+        ir = rsqrt_nr(r2);
+        w = ir * ir; u = z * w; zx = x * w; zy = y * w;
+        __builtin_amdgcn_sched_barrier(0);
+        far_columns<P, kHSplit>(h, lo, u, w, zx, zy, a, b);
+    }
+    if constexpr (kHSplit > 0) {
+        // the columns below the split: their pairs at places 0 .. lo - 1, then those of m = 0
+        double h[NH];
+#pragma unroll
+        for (int k = 0; k < lo; ++k) h[k] = H[k];
+#pragma unroll
+        for (int k = NH - (P + 1); k < NH; ++k) h[k] = H[k];
+        __builtin_amdgcn_sched_barrier(0);
+        far_columns<kHSplit - 1, 0>(h, 0, u, w, zx, zy, a, b);
+    }
+    return ir * a;
+}
+
+// Tables of the regular harmonics for terms picked at run time, copied to LDS: beta_lm
+// at [l * (P + 1) + m], and per pair (l, m) its norm and l | m << 8 | place << 16.
+struct HTab {
+    double beta[(P + 1) * (P + 1)];
+    double norm[NPAIR];
+    uint32_t lm[NPAIR];
+};
+constexpr HTab make_htab() {
+    HTab t{};
+    int k = 0;
+    for (int l = 0; l <= P; ++l)
+        for (int m = 0; m <= P; ++m) {
+            t.beta[l * (P + 1) + m] = m <= l ? hbeta(l, m) : 0.0;
+            if (m > l) continue;
+            t.norm[k] = hnorm(l, m);
+            t.lm[k] = (uint32_t)l | ((uint32_t)m << 8) | ((uint32_t)hplace(l, m) << 16);
+            ++k;
+        }
+    return t;
+}
+__constant__ HTab c_htab = make_htab();
+
+__device__ __forceinline__ void fill_htab(HTab& t) {
+    for (int k = threadIdx.x; k < (P + 1) * (P + 1); k += blockDim.x) t.beta[k] = c_htab.beta[k];
+    for (int k = threadIdx.x; k < NPAIR; k += blockDim.x) { t.norm[k] = c_htab.norm[k]; t.lm[k] = c_htab.lm[k]; }
+}
+
+// A_lm(d) for l, m picked at run time.
+__device__ __forceinline__ void reg_pair(const HTab& T, int l, int m, double dx, double dy, double dz, double& c,
+                                         double& s) {
+    double cr = 1.0, ci = 0.0;
+    for (int e = 0; e < m; ++e) {
+        const double t = fma(cr, dx, -(ci * dy));
+        ci = fma(cr, dy, ci * dx);
+        cr = t;
+    }
+    const double r2 = dx * dx + dy * dy + dz * dz;
+    double a0 = 0.0, a1 = 1.0;
+    for (int k = m + 1; k <= l; ++k) {
+        const double a2 = fma(dz, a1, -(T.beta[k * (P + 1) + m] * r2) * a0);
+        a0 = a1; a1 = a2;
+    }
+    c = cr * a1;
+    s = ci * a1;
+}
+
+// q N_lm A_lm(d) for every place of a row (c and s parts).
+__device__ __forceinline__ void reg_row(double dx, double dy, double dz, double q, double* row) {
+    const double r2 = dx * dx + dy * dy + dz * dz;
+    double cr = q, ci = 0.0;
+#pragma unroll
+    for (int m = 0; m <= P; ++m) {
+        if (m > 0) {
+            const double t = fma(cr, dx, -(ci * dy));
+            ci = fma(cr, dy, ci * dx);
+            cr = t;
+        }
+        double a0 = 0.0, a1 = 1.0;
+#pragma unroll
+        for (int l = m; l <= P; ++l) {
+            if (l == m + 1) { a0 = 1.0; a1 = dz; }
+            if (l > m + 1) {
+                const double a2 = fma(dz, a1, -(hbeta(l, m) * r2) * a0);
+                a0 = a1; a1 = a2;
+            }
+            const double v = hnorm(l, m) * a1;
+            row[hplace(l, m)] = v * cr;
+            if (m > 0) row[hplace(l, m) + 1] = v * ci;
+        }
+    }
+}
+
+// The coefficients of pair k of cell c, and a source of charge q at offset d added to them.
+struct HPair { double c, s; };
+__device__ __forceinline__ HPair hpair_load(const Rep& R, const HTab& T, int c, int k) {
+    const uint32_t code = T.lm[k];
+    const GRow h = grow(R.H + (size_t)c * HSTR + (code >> 16));
+    return HPair{h[0], (code & 0xFF00u) ? h[1] : 0.0};
+}
+__device__ __forceinline__ void hpair_store(const Rep& R, const HTab& T, int c, int k, double hc, double hs) {
+    const uint32_t code = T.lm[k];
+    double* h = R.H + (size_t)c * HSTR + (code >> 16);
+    h[0] = hc;
+    if (code & 0xFF00u) h[1] = hs;
+}
+__device__ __forceinline__ void hpair_add(const HTab& T, int k, double dx, double dy, double dz, double q, double& hc,
+                                          double& hs) {
+    const uint32_t code = T.lm[k];
+    double c, s;
+    reg_pair(T, (int)(code & 255u), (int)((code >> 8) & 255u), dx, dy, dz, c, s);
+    const double w = q * T.norm[k];
+    hc = fma(w, c, hc);
+    hs = fma(w, s, hs);
+}
+
+// A row's coefficients from the Cartesian moments: H_lm = N_lm sum_n A_lm,n M^n with the
+// monomial coefficients of A_lm, a sparse table (term, coefficient) per row place.
+constexpr int hrow_terms() {  // how many (place, term) coefficients are not zero
+    int n = 0;
+    for (int l = 0; l <= P; ++l)
+        for (int m = 0; m <= l; ++m)
+            for (int t = m; t <= l; t += 2)            // powers of x and y together
+                for (int b = 0; b <= t; ++b) n += (m == 0 ? (b % 2 == 0) : 1);
+    return n;
+}
+constexpr int HROWT = hrow_terms();
+struct HRows {
+    int start[NH + 1];
+    int term[HROWT];
+    double coef[HROWT];
+};
+// Coefficients of A_lm by its recurrence over dense polynomials of one degree: place of
+// x^a y^b z^c is cmindex(a, b, c).
+constexpr HRows make_hrows() {
+    HRows t{};
+    int n = 0;
+    // rows in the order of their places: m = 1..p (c, s alternating in l), then m = 0
+    for (int mm = 1; mm <= P + 1; ++mm) {
+        const int m = mm <= P ? mm : 0;
+        // polynomials of the last two degrees, index by (a, b): c = l - a - b
+        double A[3][2][(P + 1) * (P + 1)] = {};
+        // (x + i y)^m
+        double binom = 1.0;
+        for (int b = 0; b <= m; ++b) {
+            const double sgn = (b % 4 == 0 || b % 4 == 1) ? 1.0 : -1.0;
+            A[m % 3][b % 2][(m - b) * (P + 1) + b] = sgn * binom;
+            binom = binom * (double)(m - b) / (double)(b + 1);
+        }
+        for (int l = m; l <= P; ++l) {
+            if (l > m) {
+                for (int part = 0; part < 2; ++part)
+                    for (int k = 0; k < (P + 1) * (P + 1); ++k) A[l % 3][part][k] = A[(l + 2) % 3][part][k];  // z A_{l-1}
+                if (l >= m + 2)
+                    for (int part = 0; part < 2; ++part)
+                        for (int a = 0; a <= l - 2; ++a)
+                            for (int b = 0; a + b <= l - 2; ++b) {
+                                const double v = A[(l + 1) % 3][part][a * (P + 1) + b] * hbeta(l, m);
+                                if (v == 0.0) continue;
+                                A[l % 3][part][(a + 2) * (P + 1) + b] -= v;
+                                A[l % 3][part][a * (P + 1) + b + 2] -= v;
+                                A[l % 3][part][a * (P + 1) + b] -= v;
+                            }
+            }
+            for (int part = 0; part < (m == 0 ? 1 : 2); ++part) {
+                t.start[hplace(l, m) + part] = n;
+                for (int a = 0; a <= l; ++a)
+                    for (int b = 0; a + b <= l; ++b) {
+                        const double v = A[l % 3][part][a * (P + 1) + b];
+                        if (v == 0.0) continue;
+                        t.term[n] = cmindex(a, b, l - a - b);
+                        t.coef[n] = hnorm(l, m) * v;
+                        ++n;
+                    }
+            }
+        }
+    }
+    t.start[NH] = n;
+    return t;
+}
+__device__ const HRows c_hrows = make_hrows();
+
+// sum_n T_n M^n in the Cartesian form, each T_n folded into the sum as soon as it exists
+template <int K, class MP>
+__device__ __forceinline__ void cart_rec(double (&T)[NTERM], double Rx, double Ry, double Rz, double ir2,
+                                         MP __restrict__ Mc, double& acc) {
+    if constexpr (K < NTERM) {
+        if constexpr (K > 0) t_step<K>(T, Rx, Ry, Rz, ir2);
+        acc = fma(T[K], Mc[K], acc);
+        cart_rec<K + 1>(T, Rx, Ry, Rz, ir2, Mc, acc);
+    }
+}
 template <class MP>
-__device__ __forceinline__ double far_eval(double Rx, double Ry, double Rz, MP Mc) {
-    const double r2 = Rx * Rx + Ry * Ry + Rz * Rz;
+__device__ __forceinline__ double cart_eval(double Rx, double Ry, double Rz, MP Mc) {
     double T[NTERM];
-    T[0] = rsqrt_nr(r2);
-    const double ir2 = T[0] * T[0];
+    T[0] = rsqrt_nr(Rx * Rx + Ry * Ry + Rz * Rz);
     double acc = 0.0;
-    far_rec<0>(T, Rx, Ry, Rz, ir2, Mc, acc);
+    cart_rec<0>(T, Rx, Ry, Rz, T[0] * T[0], Mc, acc);
     return acc;
 }
 
@@ -212,10 +495,16 @@ __device__ __forceinline__ double far_eval_f(double Rx, double Ry, double Rz, co
     return (double)acc;
 }
 
-// Far value of cell c at relative position R: FP32 from M32 when the replica keeps it.
-__device__ __forceinline__ double far_value(const Rep& R, int c, double Rx, double Ry, double Rz) {
-    if (R.M32) return far_eval_f(Rx, Ry, Rz, R.M32 + (size_t)c * MSTR);
-    return far_eval(Rx, Ry, Rz, grow(R.M + (size_t)c * MSTR));
+// Far value of cell c at (tx, ty, tz): FP32 from M32 when the replica keeps it.  The kernels
+// are instantiated twice: F32 = false for handles without such a replica, whose registers the
+// FP32 recurrence (every T_n of eq. 3.4 at once) would otherwise set.
+template <bool F32>
+__device__ __forceinline__ double far_value(const Rep& R, int c, double tx, double ty, double tz) {
+    if (F32 && R.M32) {
+        const double4 g = gload(R.cgeo + c);
+        return far_eval_f(g.x - tx, g.y - ty, g.z - tz, R.M32 + (size_t)c * MSTR);
+    }
+    return far_row(grow(R.H + (size_t)c * HSTR), tx, ty, tz);
 }
 
 // Polynomial sum_n C_n d^n and its gradient sum_n C_n n_k d^{n - e_k} for
@@ -238,6 +527,30 @@ __device__ __forceinline__ void poly_rec(double (&D)[NTERM], double dx, double d
         if constexpr (e.z1 >= 0) gz = fma((double)e.n3 * c, D[e.z1], gz);
         poly_rec<K + 1>(D, dx, dy, dz, Cc, v, gx, gy, gz);
     }
+}
+
+// sum_{s <= p} P_s(cos psi) |d|^s / |R|^(s+1), psi the angle between d and -R: the
+// expansion of eq. 3.3 of one unit point source at c + d seen from c - R, order by
+// order equal to sum_{|n| <= p} T_n(R) d^n.  With A_s = P_s(cos psi) |d|^s |R|^s,
+// (s + 1) A_{s+1} = (2s + 1) (-d.R) A_s - s |d|^2 |R|^2 A_{s-1}.
+__device__ __forceinline__ double point_expansion(double Rx, double Ry, double Rz, double dx, double dy, double dz) {
+    const double r2 = Rx * Rx + Ry * Ry + Rz * Rz;
+    const double ir = rsqrt_nr(r2);
+    const double irr = ir * ir;
+    const double c1 = -(dx * Rx + dy * Ry + dz * Rz);
+    const double c2 = (dx * dx + dy * dy + dz * dz) * r2;
+    double a0 = 1.0, a1 = c1;
+    double sc = ir;               // |R|^-(2s+1)
+    double v = a0 * sc;
+    if (P >= 1) { sc *= irr; v = fma(a1, sc, v); }
+#pragma unroll
+    for (int s = 1; s < P; ++s) {
+        const double a2 = fma((2.0 * s + 1.0) / (s + 1.0) * c1, a1, -((double)s / (s + 1.0) * c2) * a0);
+        a0 = a1; a1 = a2;
+        sc *= irr;
+        v = fma(a1, sc, v);
+    }
+    return v;
 }
 
 // ------------------------------------------------------------ traversal state
@@ -267,13 +580,22 @@ struct Trav {
     static constexpr int NEARCAP = 512 + BLOCK;
     static constexpr int OVLCAP = 256;
     static constexpr int NW = BLOCK / 64;
-    uint32_t front[2][FCAP];
-    uint32_t farl[FARCAP];
-    uint32_t nearl[NEARCAP];
-    int near_base[NEARCAP];
-    int near_pre[NEARCAP + 1];       // slot counts, then their exclusive prefix
+    static constexpr int OWNCAP = 2048;  // slots of the near leaves listed one by one
+    // the lists, free once the traversal has ended: then the commit's table of harmonics
+    static constexpr int LISTWORDS = 2 * FCAP + FARCAP + 3 * NEARCAP + 1;
+    static constexpr int HROWS = (LISTWORDS / 2) / NH;
+    union {
+        struct {
+            uint32_t front[2][FCAP];
+            uint32_t farl[FARCAP];
+            uint32_t nearl[NEARCAP];
+            int near_base[NEARCAP];
+            int near_pre[NEARCAP + 1];       // slot counts, then their exclusive prefix
+        };
+        double hrow[HROWS][NH];
+    };
+    uint16_t near_own[OWNCAP];       // near list entry of each of its slots
     uint32_t flagl[2 * NTG];
-    double Mx[2 * NTG][MSTR];
     double tx[NTG], ty[NTG], tz[NTG];
     int ex_i[NTG], ex_k[NTG];
     uint64_t kx_i[NTG], kx_k[NTG];
@@ -287,11 +609,13 @@ struct Trav {
     double red[NW][NTG];
     double res[NTG];
     uint32_t mi[NTERM];              // multi-index of each term, packed (mi_code)
+    HTab ht;                         // tables of the regular harmonics
 };
 
 template <int NTG, int BLOCK>
 __device__ __forceinline__ void fill_mi(Trav<NTG, BLOCK>& S) {
     for (int k = threadIdx.x; k < NTERM; k += BLOCK) S.mi[k] = mi_code(k);
+    fill_htab(S.ht);
 }
 
 template <int NTG>
@@ -301,24 +625,60 @@ __device__ __forceinline__ void add_to(double (&acc)[NTG], int t, double v) {
         if (k == t) acc[k] += v;
 }
 
-// Far cells, then the cells holding an excluded source, whose corrected
-// moments sit in LDS.
-template <int NTG, int BLOCK>
+// Value at (x, y, z) of far cell c without the excluded sources it holds (a flagged cell):
+// its value less their own expansions about its centre, in FP64 also where the other far
+// cells are taken in single precision (then from the moments, which that replica's commits
+// repair in place of its expansion rows).  Out of line: a traversal has a few of these per
+// target, and the far loop keeps its registers.
+template <bool F32>
+__device__ __attribute__((noinline)) double flagged_value(const Rep& R, int c, double x, double y, double z, bool ion,
+                                                          double4 si, bool img, double4 sk) {
+    const double4 g = gload(R.cgeo + c);
+    double v;
+    if (F32 && R.M32) v = cart_eval(g.x - x, g.y - y, g.z - z, grow(R.M + (size_t)c * MSTR));
+    else v = far_row(grow(R.H + (size_t)c * HSTR), x, y, z);
+    if (ion) v -= si.w * point_expansion(g.x - x, g.y - y, g.z - z, si.x - g.x, si.y - g.y, si.z - g.z);
+    if (img) v -= sk.w * point_expansion(g.x - x, g.y - y, g.z - z, sk.x - g.x, sk.y - g.y, sk.z - g.z);
+    return v;
+}
+
+// Far cells, then the cells holding an excluded source, which is taken back out.
+template <bool F32, int NTG, int BLOCK>
 __device__ __forceinline__ void far_pass(const Rep& R, Trav<NTG, BLOCK>& S, int far_n, int nflag,
                                          double (&acc)[NTG]) {
     for (int j = threadIdx.x; j < far_n; j += BLOCK) {
         const uint32_t e = S.farl[j];
         const int c = (int)(e & kCellMask), t = (int)((e >> 24) & 15u);
         if (c >= R.ncell) { S.err = kErrFarCell; continue; }
-        const double4 g = R.cgeo[c];
-        add_to<NTG>(acc, t, far_value(R, c, g.x - S.tx[t], g.y - S.ty[t], g.z - S.tz[t]));
+        add_to<NTG>(acc, t, far_value<F32>(R, c, S.tx[t], S.ty[t], S.tz[t]));
     }
     for (int j = threadIdx.x; j < nflag; j += BLOCK) {
         const uint32_t e = S.flagl[j];
         const int c = (int)(e & kCellMask), t = (int)((e >> 24) & 15u);
         if (c >= R.ncell) { S.err = kErrFarCell; continue; }
-        const double4 g = R.cgeo[c];
-        add_to<NTG>(acc, t, far_eval(g.x - S.tx[t], g.y - S.ty[t], g.z - S.tz[t], lrow(S.Mx[j])));
+        add_to<NTG>(acc, t, flagged_value<F32>(R, c, S.tx[t], S.ty[t], S.tz[t], e & kFlagIon, S.es_i[t], e & kFlagImg,
+                                          S.es_k[t]));
+    }
+}
+
+// The near list entry of flattened slot f: the last j with pre[j] <= f.
+__device__ __forceinline__ int near_search(const int* pre, int near_n, int f) {
+    int lo = 0, hi = near_n - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (pre[mid] <= f) lo = mid; else hi = mid - 1;
+    }
+    return lo;
+}
+
+// The same for every slot at once, where they fit: each entry writes its number to its
+// slots (a handful), so a slot finds it in one read instead of a search of dependent reads.
+template <int BLOCK>
+__device__ __forceinline__ void near_list(uint16_t* own, const int* pre, int near_n, int total, int cap) {
+    if (total > cap) return;  // uniform
+    for (int j = threadIdx.x; j < near_n; j += BLOCK) {
+        const int end = j + 1 < near_n ? pre[j + 1] : total;
+        for (int f = pre[j]; f < end; ++f) own[f] = (uint16_t)j;
     }
 }
 
@@ -362,12 +722,9 @@ template <int NTG, int BLOCK>
 __device__ __forceinline__ void near_pass(const Rep& R, Trav<NTG, BLOCK>& S, int near_n, int total,
                                           double (&acc)[NTG]) {
     const int n_ion = R.n;
+    const bool listed = total <= Trav<NTG, BLOCK>::OWNCAP;  // uniform
     for (int f = threadIdx.x; f < total; f += BLOCK) {
-        int lo = 0, hi = near_n - 1;  // last j with near_pre[j] <= f
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (S.near_pre[mid] <= f) lo = mid; else hi = mid - 1;
-        }
+        const int lo = listed ? (int)S.near_own[f] : near_search(S.near_pre, near_n, f);
         const uint32_t e = S.nearl[lo];
         const int t = (int)((e >> 24) & 15u);
         const int slot = S.near_base[lo] + (f - S.near_pre[lo]);
@@ -450,7 +807,7 @@ __device__ void overlap_below_far(const Rep& R, Trav<NTG, BLOCK>& S, int* cnt2) 
 // S.overlap / S.coincide report hard-core hits at the overlap target.
 // Returns the number of levels processed (hook is called once per level,
 // by every thread, right after the level's first loads are issued).
-template <int NTG, int BLOCK, class Hook>
+template <bool F32, int NTG, int BLOCK, class Hook>
 __device__ int traverse(const Rep& R, Trav<NTG, BLOCK>& S, int nroot, int* cnt2, Hook&& hook) {
     using TS = Trav<NTG, BLOCK>;
     constexpr int NW = TS::NW;
@@ -472,13 +829,15 @@ __device__ int traverse(const Rep& R, Trav<NTG, BLOCK>& S, int nroot, int* cnt2,
         for (int base = 0; base < fs; base += BLOCK) {
             if (far_n > TS::FARCAP - BLOCK) {
                 __syncthreads();
-                far_pass<NTG, BLOCK>(R, S, far_n, 0, acc);
+                far_pass<F32, NTG, BLOCK>(R, S, far_n, 0, acc);
                 far_n = 0;
                 __syncthreads();
             }
             if (near_n > TS::NEARCAP - BLOCK) {
                 __syncthreads();
                 const int total = near_scan<NTG, BLOCK>(S, near_n);
+                near_list<BLOCK>(S.near_own, S.near_pre, near_n, total, TS::OWNCAP);
+                __syncthreads();
                 near_pass<NTG, BLOCK>(R, S, near_n, total, acc);
                 near_n = 0;
                 __syncthreads();
@@ -590,20 +949,10 @@ __device__ int traverse(const Rep& R, Trav<NTG, BLOCK>& S, int nroot, int* cnt2,
         __syncthreads();
         return level;
     }
-    // corrected moments of the far cells that hold an excluded source
-    for (int it = tid; it < nflag * NTERM; it += BLOCK) {
-        const int f = it / NTERM, k = it % NTERM;
-        const uint32_t e = S.flagl[f];
-        const int c = (int)(e & kCellMask), t = (int)((e >> 24) & 15u);
-        if (c >= R.ncell) { S.err = kErrFlagCell; S.Mx[f][k] = 0.0; continue; }
-        const double4 g = R.cgeo[c];
-        double mk = R.M[(size_t)c * MSTR + k];
-        if (e & kFlagIon) { const double4 s = S.es_i[t]; mk = mk - s.w * mono(S.mi[k], s.x - g.x, s.y - g.y, s.z - g.z); }
-        if (e & kFlagImg) { const double4 s = S.es_k[t]; mk = mk - s.w * mono(S.mi[k], s.x - g.x, s.y - g.y, s.z - g.z); }
-        S.Mx[f][k] = mk;
-    }
-    const int total = near_scan<NTG, BLOCK>(S, near_n);  // its barriers also publish Mx
-    far_pass<NTG, BLOCK>(R, S, far_n, nflag, acc);
+    const int total = near_scan<NTG, BLOCK>(S, near_n);
+    near_list<BLOCK>(S.near_own, S.near_pre, near_n, total, TS::OWNCAP);
+    far_pass<F32, NTG, BLOCK>(R, S, far_n, nflag, acc);
+    __syncthreads();  // publishes near_own
     near_pass<NTG, BLOCK>(R, S, near_n, total, acc);
     __syncthreads();
     if (S.ovl_t >= 0 && S.n_ovl > 0 && S.err == 0) overlap_below_far<NTG, BLOCK>(R, S, cnt2);
@@ -633,7 +982,7 @@ __device__ int traverse(const Rep& R, Trav<NTG, BLOCK>& S, int nroot, int* cnt2,
 // lanes that load a source once and evaluate both targets against it.
 constexpr int kMaskSh = 24, kDirSh = 26;
 
-template <int BLOCK>
+template <bool F32, int BLOCK>
 __device__ __forceinline__ void far_pass_mc(const Rep& R, Trav<2, BLOCK>& S, int far_n, int nflag,
                                             double (&acc)[2]) {
     static_assert(BLOCK % 2 == 0, "lane pairs");
@@ -643,17 +992,16 @@ __device__ __forceinline__ void far_pass_mc(const Rep& R, Trav<2, BLOCK>& S, int
         if (!((e >> (kMaskSh + t)) & 1u)) continue;
         const int c = (int)(e & kCellMask);
         if (c >= R.ncell) { S.err = kErrFarCell; continue; }
-        const double4 g = R.cgeo[c];
-        add_to<2>(acc, t, far_value(R, c, g.x - S.tx[t], g.y - S.ty[t], g.z - S.tz[t]));
+        add_to<2>(acc, t, far_value<F32>(R, c, S.tx[t], S.ty[t], S.tz[t]));
     }
-    // the cells holding an excluded source, with their corrected moments in LDS
+    // the cells holding an excluded source, less what it adds
     for (int j2 = threadIdx.x; j2 < 2 * nflag; j2 += BLOCK) {
         const uint32_t e = S.flagl[j2 >> 1];
         if (!((e >> (kMaskSh + t)) & 1u)) continue;
         const int c = (int)(e & kCellMask);
         if (c >= R.ncell) { S.err = kErrFarCell; continue; }
-        const double4 g = R.cgeo[c];
-        add_to<2>(acc, t, far_eval(g.x - S.tx[t], g.y - S.ty[t], g.z - S.tz[t], lrow(S.Mx[j2 >> 1])));
+        add_to<2>(acc, t, flagged_value<F32>(R, c, S.tx[t], S.ty[t], S.tz[t], e & kFlagIon, S.es_i[0], e & kFlagImg,
+                                        S.es_k[0]));
     }
 }
 
@@ -663,12 +1011,9 @@ template <int BLOCK>
 __device__ __forceinline__ void near_pass_mc(const Rep& R, Trav<2, BLOCK>& S, int near_n, int total,
                                              double (&acc)[2]) {
     const int n_ion = R.n;
+    const bool listed = total <= Trav<2, BLOCK>::OWNCAP;  // uniform
     for (int f = threadIdx.x; f < total; f += BLOCK) {
-        int lo = 0, hi = near_n - 1;  // last j with near_pre[j] <= f
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (S.near_pre[mid] <= f) lo = mid; else hi = mid - 1;
-        }
+        const int lo = listed ? (int)S.near_own[f] : near_search(S.near_pre, near_n, f);
         const uint32_t e = S.nearl[lo];
         const uint32_t mask = (e >> kMaskSh) & 3u;
         const int slot = S.near_base[lo] + (f - S.near_pre[lo]);
@@ -694,7 +1039,7 @@ __device__ __forceinline__ void near_pass_mc(const Rep& R, Trav<2, BLOCK>& S, in
 // the fs0 entries of level level0 in front[0]; otherwise as traverse():
 // deterministic lists, hook once per level, res[0..1] the potentials (the
 // same in every thread), S.err / S.overlap / S.coincide as there.
-template <int BLOCK, class Hook>
+template <bool F32, int BLOCK, class Hook>
 __device__ int traverse_mc(const Rep& R, Trav<2, BLOCK>& S, int* cnt2, Hook&& hook, int fs0, int level0,
                            double (&res)[2]) {
     using TS = Trav<2, BLOCK>;
@@ -715,13 +1060,15 @@ __device__ int traverse_mc(const Rep& R, Trav<2, BLOCK>& S, int* cnt2, Hook&& ho
         for (int base = 0; base < fs; base += BLOCK) {
             if (far_n > TS::FARCAP - BLOCK) {
                 __syncthreads();
-                far_pass_mc<BLOCK>(R, S, far_n, 0, acc);
+                far_pass_mc<F32, BLOCK>(R, S, far_n, 0, acc);
                 far_n = 0;
                 __syncthreads();
             }
             if (near_n > TS::NEARCAP - BLOCK) {
                 __syncthreads();
                 const int total = near_scan<2, BLOCK>(S, near_n);
+                near_list<BLOCK>(S.near_own, S.near_pre, near_n, total, TS::OWNCAP);
+                __syncthreads();
                 near_pass_mc<BLOCK>(R, S, near_n, total, acc);
                 near_n = 0;
                 __syncthreads();
@@ -829,20 +1176,10 @@ __device__ int traverse_mc(const Rep& R, Trav<2, BLOCK>& S, int* cnt2, Hook&& ho
         __syncthreads();
         return level;
     }
-    // corrected moments of the far cells that hold an excluded source
-    for (int it = tid; it < nflag * NTERM; it += BLOCK) {
-        const int f = it / NTERM, k = it % NTERM;
-        const uint32_t e = S.flagl[f];
-        const int c = (int)(e & kCellMask);
-        if (c >= R.ncell) { S.err = kErrFlagCell; S.Mx[f][k] = 0.0; continue; }
-        const double4 g = R.cgeo[c];
-        double mk = R.M[(size_t)c * MSTR + k];
-        if (e & kFlagIon) { const double4 s = S.es_i[0]; mk = mk - s.w * mono(S.mi[k], s.x - g.x, s.y - g.y, s.z - g.z); }
-        if (e & kFlagImg) { const double4 s = S.es_k[0]; mk = mk - s.w * mono(S.mi[k], s.x - g.x, s.y - g.y, s.z - g.z); }
-        S.Mx[f][k] = mk;
-    }
-    const int total = near_scan<2, BLOCK>(S, near_n);  // its barriers also publish Mx
-    far_pass_mc<BLOCK>(R, S, far_n, nflag, acc);
+    const int total = near_scan<2, BLOCK>(S, near_n);
+    near_list<BLOCK>(S.near_own, S.near_pre, near_n, total, TS::OWNCAP);
+    far_pass_mc<F32, BLOCK>(R, S, far_n, nflag, acc);
+    __syncthreads();  // publishes near_own
     near_pass_mc<BLOCK>(R, S, near_n, total, acc);
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
@@ -859,30 +1196,6 @@ __device__ int traverse_mc(const Rep& R, Trav<2, BLOCK>& S, int* cnt2, Hook&& ho
         res[k] = sum;
     }
     return level;
-}
-
-// sum_{s <= p} P_s(cos psi) |d|^s / |R|^(s+1), psi the angle between d and -R: the
-// expansion of eq. 3.3 of one unit point source at c + d seen from c - R, order by
-// order equal to sum_{|n| <= p} T_n(R) d^n.  With A_s = P_s(cos psi) |d|^s |R|^s,
-// (s + 1) A_{s+1} = (2s + 1) (-d.R) A_s - s |d|^2 |R|^2 A_{s-1}.
-__device__ __forceinline__ double point_expansion(double Rx, double Ry, double Rz, double dx, double dy, double dz) {
-    const double r2 = Rx * Rx + Ry * Ry + Rz * Rz;
-    const double ir = rsqrt_nr(r2);
-    const double irr = ir * ir;
-    const double c1 = -(dx * Rx + dy * Ry + dz * Rz);
-    const double c2 = (dx * dx + dy * dy + dz * dz) * r2;
-    double a0 = 1.0, a1 = c1;
-    double sc = ir;               // |R|^-(2s+1)
-    double v = a0 * sc;
-    if (P >= 1) { sc *= irr; v = fma(a1, sc, v); }
-#pragma unroll
-    for (int s = 1; s < P; ++s) {
-        const double a2 = ((2.0 * s + 1.0) * c1 * a1 - (double)s * c2 * a0) / (s + 1.0);
-        a0 = a1; a1 = a2;
-        sc *= irr;
-        v = fma(a1, sc, v);
-    }
-    return v;
 }
 
 // What a unit source at sc adds to the potential at (x, y, z) through the tree when
@@ -936,6 +1249,7 @@ struct McShared {
     int nlist;
     int list_cell[kMaxPathCells];
     int list_mask[kMaxPathCells];   // bit jj: contribution jj applies; bit 4: internal cell
+    int list_lev[kMaxPathCells];
     double4 list_geo[kMaxPathCells];
     int ok;
     int err;
@@ -1120,7 +1434,11 @@ struct LineList {
     int nlist;
     int cell[kLineContrib * kMaxLevels];
     uint32_t mask[kLineContrib * kMaxLevels];
+    uint8_t lev[kLineContrib * kMaxLevels];
+    int row0[kLineContrib];  // first table row of each path
+    int pad;
 };
+static_assert(sizeof(LineList) % 8 == 0, "the table of harmonics follows the list");
 constexpr uint32_t kLineInternal = 1u << 16;
 
 template <int BLOCK>
@@ -1128,6 +1446,9 @@ __device__ __forceinline__ LineList& line_list(Trav<2, BLOCK>& S) {
     static_assert(sizeof(LineList) <= sizeof(S.front), "the line-path cell list must fit the frontier buffer");
     return *reinterpret_cast<LineList*>(&S.front[0][0]);
 }
+// the table of the line paths' harmonics after it, in the rest of the list space
+template <int BLOCK>
+constexpr int kLineRows = (int)((sizeof(Trav<2, BLOCK>::hrow) - sizeof(LineList)) / (8 * NH));
 
 // Move one line image between leaf index arrays (or rewrite its slot) from the current
 // state in HBM; false on a broken index.
@@ -1162,11 +1483,17 @@ __device__ __forceinline__ bool line_slot_move(const Rep& R, int s, int lo, int 
 // of them touch a common leaf, else one lane in source order), beside them the distinct
 // cells of their 2M root paths, then every thread repairs those cells' moments and counts,
 // applying to each cell, in order, old line image 0 (-), new line image 0 (+), old 1 ...
-// LL.nlist must be 0 on entry.
-template <int BLOCK>
+template <bool F32, int BLOCK>
 __device__ __forceinline__ void lines_commit(const Rep& R, Trav<2, BLOCK>& S, McShared& MS, int i) {
     LineList& LL = line_list(S);
     const int tid = threadIdx.x, M = R.nline, nc = 2 * M;
+    const bool cart = F32 && R.M32;  // uniform
+    double* const rowtab = (double*)((char*)&LL + sizeof(LineList));
+    int rows = 0;
+    for (int j = 0; j < nc; ++j) rows += MS.lplen[j];
+    const bool use_rows = !cart && rows <= kLineRows<BLOCK>;
+    if (tid == 0) LL.nlist = 0;  // the list space held the ion's and its image's table until now
+    __syncthreads();
     if (wave_id() == 0) {
         const int m = lane_id();
         int lo = -1, ln = -1;
@@ -1202,26 +1529,69 @@ __device__ __forceinline__ void lines_commit(const Rep& R, Trav<2, BLOCK>& S, Mc
             const int slot = atomicAdd(&LL.nlist, 1);
             LL.cell[slot] = c;
             LL.mask[slot] = mask;
+            LL.lev[slot] = (uint8_t)l;
         }
+        if (use_rows)
+            for (int it = tid - 64; it < nc * kMaxLevels; it += BLOCK - 64) {
+                const int j = it / kMaxLevels, l = it % kMaxLevels;
+                if (l >= MS.lplen[j]) continue;
+                int r0 = 0;
+                for (int jj = 0; jj < j; ++jj) r0 += MS.lplen[jj];
+                if (l == 0) LL.row0[j] = r0;
+                const int c = MS.lpath[j][l];
+                const double4 sp = MS.lpos[j], g = gload(R.cgeo + c);
+                reg_row(sp.x - g.x, sp.y - g.y, sp.z - g.z, (j & 1) ? sp.w : -sp.w, rowtab + (r0 + l) * NH);
+            }
     }
     __syncthreads();
-    const int items = LL.nlist * NTERM;
-    for (int it = tid; it < items; it += BLOCK) {
-        const int li = it / NTERM, k = it % NTERM;
-        const int c = LL.cell[li];
-        const uint32_t mask = LL.mask[li];
-        const double4 g = R.cgeo[c];
-        double mk = R.M[(size_t)c * MSTR + k];
-        int dc = 0;
-        for (int j = 0; j < nc; ++j) {
-            if (!(mask & (1u << j))) continue;
-            const double4 sp = MS.lpos[j];
-            const double v = mono(S.mi[k], sp.x - g.x, sp.y - g.y, sp.z - g.z);
-            if (j & 1) { mk = mk + sp.w * v; ++dc; } else { mk = mk - sp.w * v; --dc; }
+    if (use_rows) {
+        for (int it = tid; it < LL.nlist * NH; it += BLOCK) {
+            const int li = it / NH, k = it % NH;
+            const int c = LL.cell[li], l = LL.lev[li];
+            const uint32_t mask = LL.mask[li];
+            double* const hp = R.H + (size_t)c * HSTR + k;
+            double h = *(GRow)hp;
+            for (uint32_t rest = mask & 0xFFFFu; rest; rest &= rest - 1u) h += rowtab[(LL.row0[__builtin_ctz(rest)] + l) * NH + k];
+            *hp = h;
+            const int dc = __popc(mask & 0xAAAAu) - __popc(mask & 0x5555u);
+            if (k == 0 && (mask & kLineInternal) && dc != 0) R.cm[c].x += dc;
         }
-        R.M[(size_t)c * MSTR + k] = mk;
-        if (R.M32) R.M32[(size_t)c * MSTR + k] = (float)mk;
-        if (k == 0 && (mask & kLineInternal) && dc != 0) R.cm[c].x += dc;
+    } else if (!cart) {
+        for (int it = tid; it < LL.nlist * NPAIR; it += BLOCK) {
+            const int li = it / NPAIR, k = it % NPAIR;
+            const int c = LL.cell[li];
+            const uint32_t mask = LL.mask[li];
+            const double4 g = gload(R.cgeo + c);
+            const HPair hp = hpair_load(R, S.ht, c, k);
+            double hc = hp.c, hs = hp.s;
+            for (int j = 0; j < nc; ++j) {
+                if (!(mask & (1u << j))) continue;
+                const double4 sp = MS.lpos[j];
+                hpair_add(S.ht, k, sp.x - g.x, sp.y - g.y, sp.z - g.z, (j & 1) ? sp.w : -sp.w, hc, hs);
+            }
+            hpair_store(R, S.ht, c, k, hc, hs);
+            const int dc = __popc(mask & 0xAAAAu) - __popc(mask & 0x5555u);
+            if (k == 0 && (mask & kLineInternal) && dc != 0) R.cm[c].x += dc;
+        }
+    }
+    if (cart) {  // the moments and their single-precision copy, where the far field reads that
+        for (int it = tid; it < LL.nlist * NTERM; it += BLOCK) {
+            const int li = it / NTERM, k = it % NTERM;
+            const int c = LL.cell[li];
+            const uint32_t mask = LL.mask[li];
+            const double4 g = R.cgeo[c];
+            double mk = R.M[(size_t)c * MSTR + k];
+            for (int j = 0; j < nc; ++j) {
+                if (!(mask & (1u << j))) continue;
+                const double4 sp = MS.lpos[j];
+                const double v = mono(S.mi[k], sp.x - g.x, sp.y - g.y, sp.z - g.z);
+                mk = (j & 1) ? mk + sp.w * v : mk - sp.w * v;
+            }
+            R.M[(size_t)c * MSTR + k] = mk;
+            R.M32[(size_t)c * MSTR + k] = (float)mk;
+            const int dc = __popc(mask & 0xAAAAu) - __popc(mask & 0x5555u);
+            if (k == 0 && (mask & kLineInternal) && dc != 0) R.cm[c].x += dc;
+        }
     }
     __syncthreads();
 }
@@ -1232,11 +1602,25 @@ __device__ __forceinline__ void lines_commit(const Rep& R, Trav<2, BLOCK>& S, Mc
 // traversal; the other threads repair the moments and counts of the distinct
 // cells of the four root paths, applying to each cell, in order, the old ion
 // (-), the new ion (+), the old image (-) and the new image (+).
-template <int BLOCK>
-__device__ __forceinline__ void commit(const Rep& R, const Trav<2, BLOCK>& S, McShared& MS, int i) {
+template <bool F32, int BLOCK>
+__device__ __forceinline__ void commit(const Rep& R, Trav<2, BLOCK>& S, McShared& MS, int i) {
     const int tid = threadIdx.x;
     const bool imgs = R.images != 0;
-    const bool use_pw = MS.nlist <= kPowCells;
+    const bool cart = F32 && R.M32;  // uniform: the Cartesian moments are repaired, not the expansion rows
+    const int nps = imgs ? 4 : 2;
+    int row0[4], rows = 0;  // first table row of each root path
+#pragma unroll
+    for (int jj = 0; jj < 4; ++jj) { row0[jj] = rows; rows += jj < nps ? MS.plen[jj] : 0; }
+    const bool use_rows = !cart && rows <= Trav<2, BLOCK>::HROWS;
+    const bool use_pw = cart && MS.nlist <= kPowCells;
+    if (use_rows) {  // the harmonics of every path entry, a lane each, in the traversal's list space
+        for (int r = tid; r < rows; r += BLOCK) {
+            const int jj = (r >= row0[1] ? 1 : 0) + (nps > 2 ? (r >= row0[2] ? 1 : 0) + (r >= row0[3] ? 1 : 0) : 0);
+            const double4 sc = MS.contrib[jj], g = MS.path_geo[jj][r - row0[jj]];
+            reg_row(sc.x - g.x, sc.y - g.y, sc.z - g.z, (jj & 1) ? sc.w : -sc.w, S.hrow[r]);
+        }
+        __syncthreads();
+    }
     if (use_pw) {
         for (int it = tid; it < MS.nlist * 12; it += BLOCK) {
             const int li = it / 12, r = it % 12, jj = r / 3, ax = r % 3;
@@ -1322,7 +1706,43 @@ __device__ __forceinline__ void commit(const Rep& R, const Trav<2, BLOCK>& S, Mc
             R.src[K] = img_new;
         }
     }
-    // moments and counts of the distinct path cells: all loads first, then stores
+    // expansion rows and counts of the distinct path cells: one coefficient of a cell per item, a
+    // table read per contribution; a list of paths longer than the table forms the harmonics of
+    // each (l, m) pair where it needs them
+    if (use_rows) {
+        for (int it = tid; it < MS.nlist * NH; it += BLOCK) {
+            const int li = it / NH, k = it % NH;
+            const int c = MS.list_cell[li], mask = MS.list_mask[li], l = MS.list_lev[li];
+            double* const hp = R.H + (size_t)c * HSTR + k;
+            double h = *(GRow)hp;
+#pragma unroll
+            for (int jj = 0; jj < 4; ++jj) h += (mask & (1 << jj)) ? S.hrow[row0[jj] + l][k] : 0.0;
+            *hp = h;
+            const int dc = __popc(mask & 10) - __popc(mask & 5);
+            if (k == 0 && (mask & 16) && dc != 0) R.cm[c].x += dc;
+        }
+    } else if (!cart) {
+        for (int it = tid; it < MS.nlist * NPAIR; it += BLOCK) {
+            const int li = it / NPAIR, k = it % NPAIR;
+            const int c = MS.list_cell[li], mask = MS.list_mask[li];
+            const double4 g = MS.list_geo[li];
+            const HPair hp = hpair_load(R, S.ht, c, k);
+            double hc = hp.c, hs = hp.s;
+            for (int jj = 0; jj < 4; ++jj) {
+                if (!(mask & (1 << jj))) continue;
+                const double4 s = MS.contrib[jj];
+                hpair_add(S.ht, k, s.x - g.x, s.y - g.y, s.z - g.z, (jj & 1) ? s.w : -s.w, hc, hs);
+            }
+            hpair_store(R, S.ht, c, k, hc, hs);
+            const int dc = __popc(mask & 10) - __popc(mask & 5);
+            if (k == 0 && (mask & 16) && dc != 0) R.cm[c].x += dc;
+        }
+    }
+    if (!cart) {
+        __syncthreads();
+        return;
+    }
+    // the moments and their single-precision copy: all loads first, then stores
     const int items = MS.nlist * NTERM;
     constexpr int G = 4;
     for (int base = tid; base < items; base += G * BLOCK) {
@@ -1343,7 +1763,6 @@ __device__ __forceinline__ void commit(const Rep& R, const Trav<2, BLOCK>& S, Mc
             const int c = MS.list_cell[li], mask = MS.list_mask[li];
             const double4 g = MS.list_geo[li];
             double m = mk[u];
-            int dc = 0;
 #pragma unroll
             for (int jj = 0; jj < 4; ++jj) {
                 if (!(mask & (1 << jj))) continue;
@@ -1356,10 +1775,11 @@ __device__ __forceinline__ void commit(const Rep& R, const Trav<2, BLOCK>& S, Mc
                 } else {
                     v = mono(S.mi[k], s.x - g.x, s.y - g.y, s.z - g.z);
                 }
-                if (jj & 1) { m = m + s.w * v; ++dc; } else { m = m - s.w * v; --dc; }
+                m = (jj & 1) ? m + s.w * v : m - s.w * v;
             }
             R.M[(size_t)c * MSTR + k] = m;
-            if (R.M32) R.M32[(size_t)c * MSTR + k] = (float)m;
+            R.M32[(size_t)c * MSTR + k] = (float)m;
+            const int dc = __popc(mask & 10) - __popc(mask & 5);
             if (k == 0 && (mask & 16) && dc != 0) R.cm[c].x += dc;
         }
     }
@@ -1372,7 +1792,7 @@ __device__ __forceinline__ void commit(const Rep& R, const Trav<2, BLOCK>& S, Mc
 // si and mo are the mover's ion and image as stored (mo unused without images);
 // inext >= 0 names the next move's ion, whose sources one lane loads into
 // MS.nx_si / MS.nx_mo during the traversal (valid if the ion is not i).
-template <int BLOCK, bool LINES>
+template <int BLOCK, bool LINES, bool F32>
 __device__ __forceinline__ MoveOut one_move(const Rep& R, Trav<2, BLOCK>& S, McShared& MS, int i, double4 si,
                             double4 mo, double rx, double ry, double rz, double alpha, int mode, int inext) {
     static_assert(BLOCK >= 256, "the path descents, the commit prefetch and the next mover's load run on "
@@ -1489,7 +1909,7 @@ __device__ __forceinline__ MoveOut one_move(const Rep& R, Trav<2, BLOCK>& S, McS
             line_lane_steps(R, MS, S.tx, S.ty, S.tz, tid - (BLOCK - 192) - 16, i, 2);
     };
     double pot[2];
-    const int levels = traverse_mc<BLOCK>(R, S, MS.cnt2, hook, MS.fs0, MS.level0, pot);
+    const int levels = traverse_mc<F32, BLOCK>(R, S, MS.cnt2, hook, MS.fs0, MS.level0, pot);
     (void)levels;
     if (S.err) {
         out.stop = (S.err == kErrStack || S.err == kErrFrontier) ? -7 : -8;
@@ -1530,6 +1950,7 @@ __device__ __forceinline__ MoveOut one_move(const Rep& R, Trav<2, BLOCK>& S, McS
         const int slot = atomicAdd(&MS.nlist, 1);
         MS.list_cell[slot] = c;
         MS.list_mask[slot] = mask;
+        MS.list_lev[slot] = l;
         MS.list_geo[slot] = MS.path_geo[j][l];
     }
     const double po = pot[0], pn = pot[1];
@@ -1577,17 +1998,14 @@ __device__ __forceinline__ MoveOut one_move(const Rep& R, Trav<2, BLOCK>& S, McS
         } else {
             MS.err = kErrCommitSlot;
         }
-        if (LINES && R.nline > 0) {
-            if (ok && !lines_fit(R, MS)) ok = false;  // every insertion of the move, in commit order
-            line_list(S).nlist = 0;
-        }
+        if (LINES && R.nline > 0 && ok && !lines_fit(R, MS)) ok = false;  // every insertion of the move, in commit order
         MS.ok = ok;
     }
     __syncthreads();
     if (MS.err) { out.stop = -8; out.detail = MS.err; __syncthreads(); return out; }
     if (!MS.ok) { out.stop = -6; __syncthreads(); return out; }
-    commit<BLOCK>(R, S, MS, i);
-    if (LINES && R.nline > 0 && !MS.err) lines_commit<BLOCK>(R, S, MS, i);
+    commit<F32, BLOCK>(R, S, MS, i);
+    if (LINES && R.nline > 0 && !MS.err) lines_commit<F32, BLOCK>(R, S, MS, i);
     if (MS.err) { out.stop = -8; out.detail = MS.err; }
     out.accepted = 1;
     return out;
@@ -1612,7 +2030,7 @@ __device__ __forceinline__ void load_rep(Rep& dst, const Rep* src) {
 // treecode energy change and the local adjustment of Sec. 3.3).  A replica
 // whose accepted move would overflow a leaf index array stops before that
 // move with mc_status = ECAPACITY; the host rebuilds it and resumes.
-template <int BLOCK, bool LINES>
+template <int BLOCK, bool LINES, bool F32>
 __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2))) k_mc(Rep* reps, McArgs A) {
     __shared__ Trav<2, BLOCK> S;
     __shared__ McShared MS;
@@ -1655,7 +2073,7 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2)))
             const bool use_nx = have_nx && i != prev_i;
             const double4 si = use_nx ? MS.nx_si : Rs.src[i];
             const double4 mo = use_nx ? MS.nx_mo : (imgs ? Rs.src[Rs.n + i] : make_double4(0, 0, 0, 0));
-            const MoveOut o = one_move<BLOCK, LINES>(Rs, S, MS, i, si, mo, si.x + MS.dr_d[b][0], si.y + MS.dr_d[b][1],
+            const MoveOut o = one_move<BLOCK, LINES, F32>(Rs, S, MS, i, si, mo, si.x + MS.dr_d[b][0], si.y + MS.dr_d[b][1],
                                               si.z + MS.dr_d[b][2], MS.dr_d[b][3], 1, inext);
             // a move outside the walls returns before its traversal, so before the load
             have_nx = inext >= 0 && o.reason != 1;
@@ -1681,7 +2099,7 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2)))
     }
 }
 
-template <bool LINES>
+template <bool LINES, bool F32>
 __global__ void __launch_bounds__(kMcBlock) k_move(Rep* reps, int r, MoveIO* io) {
     __shared__ Trav<2, kMcBlock> S;
     __shared__ McShared MS;
@@ -1692,7 +2110,7 @@ __global__ void __launch_bounds__(kMcBlock) k_move(Rep* reps, int r, MoveIO* io)
     const int i = io->i;
     const double4 si = Rs.src[i];
     const double4 mo = Rs.images ? Rs.src[Rs.n + i] : make_double4(0, 0, 0, 0);
-    const MoveOut o = one_move<kMcBlock, LINES>(Rs, S, MS, i, si, mo, io->rn[0], io->rn[1], io->rn[2], 0.0,
+    const MoveOut o = one_move<kMcBlock, LINES, F32>(Rs, S, MS, i, si, mo, io->rn[0], io->rn[1], io->rn[2], 0.0,
                                          io->mode == 0 ? 0 : 2, -1);
     if (threadIdx.x == 0) {
         io->dE = o.dE;
@@ -1709,6 +2127,7 @@ __global__ void __launch_bounds__(kMcBlock) k_move(Rep* reps, int r, MoveIO* io)
 // A workgroup takes kEnergyTargets consecutive positions of the build's key
 // order (a space-filling curve) and traverses for the ions among them, so that
 // its targets are close in space and share most of their interaction lists.
+template <bool F32>
 __global__ void __launch_bounds__(kEnergyBlock) k_energy(Rep* reps, int r, double* phi, double* eterm) {
     constexpr int NTG = kEnergyTargets;
     __shared__ Trav<NTG, kEnergyBlock> S;
@@ -1752,7 +2171,7 @@ __global__ void __launch_bounds__(kEnergyBlock) k_energy(Rep* reps, int r, doubl
         }
         if (tid == 0) { S.ovl_t = -1; S.ovl_ex = -1; S.n_ovl = 0; S.err = 0; S.overlap = 0; S.coincide = 0; }
         __syncthreads();
-        traverse<NTG, kEnergyBlock>(Rs, S, nv, cnt2, [](int) {});
+        traverse<F32, NTG, kEnergyBlock>(Rs, S, nv, cnt2, [](int) {});
         if (tid < nv) {
             const int ion = s_ion[tid];
             const double4 si = Rs.src[ion];
@@ -2447,24 +2866,40 @@ __global__ void __launch_bounds__(256) k_zero(double* p, size_t n) {
         p[k] = 0.0;
 }
 
+template <bool LINES, bool F32>
+void start_mc(hipStream_t s, Rep* reps, const McArgs& a, int grid, int wide) {
+    if (wide) hipLaunchKernelGGL((k_mc<kMcBlock, LINES, F32>), dim3(grid), dim3(kMcBlock), 0, s, reps, a);
+    else hipLaunchKernelGGL((k_mc<kMcBlockBatch, LINES, F32>), dim3(grid), dim3(kMcBlockBatch), 0, s, reps, a);
+}
 void run_mc(hipStream_t s, Rep* reps, const McArgs& a, int grid, int wide) {
-    // handles with line images take the instantiation with their steps; the others keep the
-    // registers of the one-image kernel
+    // handles with line images or a single-precision far field take the instantiations with
+    // their steps; the others keep the registers of the plain kernel
     if (a.lines) {
-        if (wide) hipLaunchKernelGGL((k_mc<kMcBlock, true>), dim3(grid), dim3(kMcBlock), 0, s, reps, a);
-        else hipLaunchKernelGGL((k_mc<kMcBlockBatch, true>), dim3(grid), dim3(kMcBlockBatch), 0, s, reps, a);
+        if (a.far32) start_mc<true, true>(s, reps, a, grid, wide);
+        else start_mc<true, false>(s, reps, a, grid, wide);
     } else {
-        if (wide) hipLaunchKernelGGL((k_mc<kMcBlock, false>), dim3(grid), dim3(kMcBlock), 0, s, reps, a);
-        else hipLaunchKernelGGL((k_mc<kMcBlockBatch, false>), dim3(grid), dim3(kMcBlockBatch), 0, s, reps, a);
+        if (a.far32) start_mc<false, true>(s, reps, a, grid, wide);
+        else start_mc<false, false>(s, reps, a, grid, wide);
     }
 }
-void run_mcb(hipStream_t s, Rep* reps, const McArgs& a, int grid, int wide) {
-    if (wide) hipLaunchKernelGGL(k_mcb<kMcBlock>, dim3(grid), dim3(kMcBlock), 0, s, reps, a);
-    else hipLaunchKernelGGL(k_mcb<kMcBlockBatch>, dim3(grid), dim3(kMcBlockBatch), 0, s, reps, a);
+template <bool F32>
+void start_mcb(hipStream_t s, Rep* reps, const McArgs& a, int grid, int wide) {
+    if (wide) hipLaunchKernelGGL((k_mcb<kMcBlock, F32>), dim3(grid), dim3(kMcBlock), 0, s, reps, a);
+    else hipLaunchKernelGGL((k_mcb<kMcBlockBatch, F32>), dim3(grid), dim3(kMcBlockBatch), 0, s, reps, a);
 }
-void run_move(hipStream_t s, Rep* reps, int r, MoveIO* io, int lines) {
-    if (lines) hipLaunchKernelGGL(k_move<true>, dim3(1), dim3(kMcBlock), 0, s, reps, r, io);
-    else hipLaunchKernelGGL(k_move<false>, dim3(1), dim3(kMcBlock), 0, s, reps, r, io);
+void run_mcb(hipStream_t s, Rep* reps, const McArgs& a, int grid, int wide) {
+    if (a.far32) start_mcb<true>(s, reps, a, grid, wide);
+    else start_mcb<false>(s, reps, a, grid, wide);
+}
+void run_move(hipStream_t s, Rep* reps, int r, MoveIO* io, int lines, int far32) {
+    const dim3 grid(1), block(kMcBlock);
+    if (lines) {
+        if (far32) hipLaunchKernelGGL((k_move<true, true>), grid, block, 0, s, reps, r, io);
+        else hipLaunchKernelGGL((k_move<true, false>), grid, block, 0, s, reps, r, io);
+    } else {
+        if (far32) hipLaunchKernelGGL((k_move<false, true>), grid, block, 0, s, reps, r, io);
+        else hipLaunchKernelGGL((k_move<false, false>), grid, block, 0, s, reps, r, io);
+    }
 }
 // Line images of the multiple-image model (one thread per ion, after k_energy): an
 // ion's own line images stay in its traversal as sources, so each is taken back out of
@@ -2490,12 +2925,13 @@ __global__ void __launch_bounds__(256) k_eline(Rep* reps, int r, double* phi, do
     eterm[ion] += 0.5 * si.w * (self - sub);
 }
 
-void run_energy(hipStream_t s, Rep* reps, int r, int n, double* phi, double* eterm, int max_grid, int nline) {
+void run_energy(hipStream_t s, Rep* reps, int r, int n, double* phi, double* eterm, int max_grid, int nline, int far32) {
     // one workgroup per group of key-order positions: at most (2 + nline) n sources
     const long long positions = (long long)n * (2 + nline);
     int grid = (int)std::min<long long>((positions + kEnergyTargets - 1) / kEnergyTargets, 0x7FFFFFFFll);
     if (max_grid > 0 && grid > max_grid) grid = max_grid;
-    hipLaunchKernelGGL(k_energy, dim3(grid), dim3(kEnergyBlock), 0, s, reps, r, phi, eterm);
+    if (far32) hipLaunchKernelGGL(k_energy<true>, dim3(grid), dim3(kEnergyBlock), 0, s, reps, r, phi, eterm);
+    else hipLaunchKernelGGL(k_energy<false>, dim3(grid), dim3(kEnergyBlock), 0, s, reps, r, phi, eterm);
     if (nline > 0) hipLaunchKernelGGL(k_eline, dim3((n + 255) / 256), dim3(256), 0, s, reps, r, phi, eterm);
 }
 void run_grad(hipStream_t s, Rep* reps, int r, const GradWork& w, double* dEdr, double* dEdq, double* eterm,
@@ -2523,6 +2959,31 @@ void run_grad(hipStream_t s, Rep* reps, int r, const GradWork& w, double* dEdr, 
                        (const double4*)w.G, (const double4*)w.Gt, dEdr, dEdq);
 }
 
+// Expansion rows from the moments: one thread per (cell, row place).
+__global__ void __launch_bounds__(256) k_expand(Rep* reps, const int* list) {
+    const Rep& R = reps[list ? list[blockIdx.y] : blockIdx.y];
+    if (R.status) return;
+    const long long items = (long long)R.ncell * HSTR;
+    for (long long it = blockIdx.x * 256ll + threadIdx.x; it < items; it += (long long)gridDim.x * 256) {
+        const int c = (int)(it / HSTR), k = (int)(it % HSTR);
+        double v = 0.0;
+        if (k < NH) {
+            const double* M = R.M + (size_t)c * MSTR;
+            for (int e = c_hrows.start[k]; e < c_hrows.start[k + 1]; ++e) v = fma(c_hrows.coef[e], M[c_hrows.term[e]], v);
+        } else if (k < NH + 3) {
+            const double4 g = R.cgeo[c];
+            v = k == HCEN ? g.x : (k == HCEN + 1 ? g.y : g.z);
+        }
+        R.H[(size_t)c * HSTR + k] = v;
+    }
+}
+
+void run_expand(hipStream_t s, int nrep, Rep* reps, const int* list, int max_ncell) {
+    const long long blocks = ((long long)max_ncell * HSTR + 255) / 256;
+    hipLaunchKernelGGL(k_expand, dim3((unsigned)std::max(1ll, std::min(blocks, 8192ll)), nrep), dim3(256), 0, s, reps,
+                       list);
+}
+
 // Phase timers of the batched kernel (a build with -DBHMC_PHASE_TIMERS): ticks of the
 // constant clock per phase, then rounds and moves; reset after reading if asked.
 int read_phases(unsigned long long* out, int n, int reset) {
@@ -2541,7 +3002,7 @@ int read_phases(unsigned long long* out, int n, int reset) {
 #endif
 }
 
-const EvalOps kOps = {run_mc, run_mcb, kBM, run_move, run_energy, run_grad, read_phases};
+const EvalOps kOps = {run_mc, run_mcb, kBM, run_expand, run_move, run_energy, run_grad, read_phases};
 
 }  // namespace BHMC_NS
 

@@ -11,6 +11,8 @@ constexpr int kMaxTerms = 364;  // (p+1)(p+2)(p+3)/6 at p = 11 (gradient needs o
 
 inline int nterms_of(int p) { return (p + 1) * (p + 2) * (p + 3) / 6; }
 inline int mstride_of(int p) { return (nterms_of(p) + 3) & ~3; }  // 32-byte aligned rows
+// expansion row: (p + 1)^2 harmonic coefficients, then the cell's centre; 16-byte aligned
+inline int hstride_of(int p) { return ((p + 1) * (p + 1) + 3 + 1) & ~1; }
 
 // Arguments of one Monte Carlo launch.
 struct McArgs {
@@ -24,6 +26,7 @@ struct McArgs {
     long long* sweep_add; // per replica moves added to move_end by the sweep prep kernel
     int bm;               // batched kernel: moves per round (0 = as many as the order allows)
     int lines;            // 1: a replica has line images (the move kernel with their steps)
+    int far32;            // 1: a replica has a single-precision far field (likewise)
 };
 
 // One externally specified move (delta_energy / commit_move).
@@ -78,11 +81,13 @@ struct EvalOps {
     // the same chains with several trial moves per round (N_0 = 0 only)
     void (*mcb)(hipStream_t s, Rep* reps, const McArgs& a, int grid, int wide);
     int moves_per_round;  // the most the batched kernel takes per round at this order
-    void (*move)(hipStream_t s, Rep* reps, int r, MoveIO* io_dev, int lines);
+    // expansion rows H of the replicas in list from their moments M (max_ncell: of the largest)
+    void (*expand)(hipStream_t s, int nrep, Rep* reps, const int* list, int max_ncell);
+    void (*move)(hipStream_t s, Rep* reps, int r, MoveIO* io_dev, int lines, int far32);
     // max_grid > 0 bounds the number of workgroups (each then takes several target groups), so that
     // every workgroup has an HBM frontier region
     // nline > 0: the replica has line images (multiple-image model), corrected after the traversal
-    void (*energy)(hipStream_t s, Rep* reps, int r, int n, double* phi, double* eterm, int max_grid, int nline);
+    void (*energy)(hipStream_t s, Rep* reps, int r, int n, double* phi, double* eterm, int max_grid, int nline, int far32);
     void (*grad)(hipStream_t s, Rep* reps, int r, const GradWork& w, double* dEdr, double* dEdq,
                  double* eterm, int max_grid);
     // phase timers of the batched Metropolis kernel: number of counters, 0 without timers

@@ -72,9 +72,12 @@ struct BTrav {
     static constexpr int NEARCAP = 1024 + kChunk * BLOCK;
     static constexpr int OVLCAP = 512;
     static constexpr int NW = BLOCK / 64;
-    // the traversal's lists, free once it has ended: then per-axis power tables of the commit
+    static constexpr int OWNCAP = 4096;  // slots of the near leaves listed one by one
+    // the traversal's lists, free once it has ended: then the commit's tables, the harmonics of
+    // its path entries or (single-precision far field) their per-axis powers
     static constexpr int LISTWORDS = 2 * FCAP + FARCAP + 3 * NEARCAP + 1;
     static constexpr int PWROWS = (LISTWORDS / 2) / (3 * (P + 1));
+    static constexpr int HROWS = (LISTWORDS / 2) / NH;
     union {
         struct {
             uint32_t front[2][FCAP];
@@ -84,14 +87,16 @@ struct BTrav {
             int near_pre[NEARCAP + 1];
         };
         double pw[PWROWS][3][P + 1];  // (x - c_x)^e, (y - c_y)^e, (z - c_z)^e of a path entry
+        double hrow[HROWS][NH];       // +-q N_lm A_lm(x - c) of a path entry, in row order
     };
+    uint16_t near_own[OWNCAP];        // near list entry of each of its slots
     uint32_t flagl[4 * kBM];
-    double Mx[4 * kBM][MSTR];
     uint32_t ovl[OVLCAP];
     int n_ovl, near_tot, err;
     uint64_t wcnt[2][kChunk][NW];
     double red[NW][kBT];
     uint32_t mi[NTERM];
+    HTab ht;
     int cnt2[2];
 };
 
@@ -100,7 +105,7 @@ struct BMoves {
     int ion[kBM];
     double4 ct[kBM][4];            // contributions: old ion, new ion, old image, new image (position, charge)
     uint64_t key[kBM][4];
-    double alpha[kBM];
+    double alpha[kBM], thr[kBM];   // Metropolis uniform and -log of it
     int wall[kBM];
     double tx[kBT], ty[kBT], tz[kBT];
     int ovl_fixed[kBM];            // overlaps an ion that stays where it is during the round
@@ -146,7 +151,7 @@ struct BMoves {
     int pw_row[4 * kBM];  // first power-table row of the root path of contribution (j, cc), or -1
     // trial moves drawn ahead, one per lane of the first wave
     int dr_i[kDrawBatch];
-    double dr_d[kDrawBatch][4];
+    double dr_d[kDrawBatch][4], dr_t[kDrawBatch];
 };
 
 __device__ __forceinline__ int mv_of(uint32_t e) { return (int)((e >> kMvSh) & 7u); }
@@ -215,7 +220,7 @@ __device__ int near_scan_mb(BTrav<BLOCK>& S, int near_n) {
 // Far cells by lane pairs: the lane of parity tb evaluates target tb (old or new
 // position) of the entry's move, both lanes reading the same moment row; acc[b] of a
 // lane holds its target of move b.
-template <int BLOCK>
+template <bool F32, int BLOCK>
 __device__ __forceinline__ void far_pass_mb(const Rep& R, BTrav<BLOCK>& S, const BMoves& MV, int far_n, int nflag,
                                             double (&acc)[kBM]) {
     const int tb = (int)(threadIdx.x & 1);
@@ -225,8 +230,7 @@ __device__ __forceinline__ void far_pass_mb(const Rep& R, BTrav<BLOCK>& S, const
         const int c = (int)(e & kCellMask);
         if (c >= R.ncell) { S.err = kErrFarCell; continue; }
         const int b = mv_of(e), t = 2 * b + tb;
-        const double4 g = gload(R.cgeo + c);
-        add_to_t<kBM>(acc, b, far_value(R, c, g.x - MV.tx[t], g.y - MV.ty[t], g.z - MV.tz[t]));
+        add_to_t<kBM>(acc, b, far_value<F32>(R, c, MV.tx[t], MV.ty[t], MV.tz[t]));
     }
     for (int j2 = threadIdx.x; j2 < 2 * nflag; j2 += BLOCK) {
         const uint32_t e = S.flagl[j2 >> 1];
@@ -234,8 +238,8 @@ __device__ __forceinline__ void far_pass_mb(const Rep& R, BTrav<BLOCK>& S, const
         const int c = (int)(e & kCellMask);
         if (c >= R.ncell) { S.err = kErrFarCell; continue; }
         const int b = mv_of(e), t = 2 * b + tb;
-        const double4 g = gload(R.cgeo + c);
-        add_to_t<kBM>(acc, b, far_eval(g.x - MV.tx[t], g.y - MV.ty[t], g.z - MV.tz[t], lrow(S.Mx[j2 >> 1])));
+        add_to_t<kBM>(acc, b, flagged_value<F32>(R, c, MV.tx[t], MV.ty[t], MV.tz[t], e & kMbIon, MV.ct[b][0], e & kMbImg,
+                                            MV.ct[b][2]));
     }
 }
 
@@ -246,14 +250,11 @@ template <int BLOCK>
 __device__ __forceinline__ void near_pass_mb(const Rep& R, BTrav<BLOCK>& S, BMoves& MV, int near_n, int total,
                                              double (&acc)[kBM]) {
     const int n_ion = R.n;
+    const bool listed = total <= BTrav<BLOCK>::OWNCAP;  // uniform
     const int tb = (int)(threadIdx.x & 1);
     for (int f2 = threadIdx.x; f2 < 2 * total; f2 += BLOCK) {
         const int f = f2 >> 1;
-        int lo = 0, hi = near_n - 1;  // last j with near_pre[j] <= f
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (S.near_pre[mid] <= f) lo = mid; else hi = mid - 1;
-        }
+        const int lo = listed ? (int)S.near_own[f] : near_search(S.near_pre, near_n, f);
         const uint32_t e = S.nearl[lo];
         if (!((e >> (kOpSh + tb)) & 1u)) continue;
         const int b = mv_of(e);
@@ -325,7 +326,7 @@ __device__ void overlap_below_far_mb(const Rep& R, BTrav<BLOCK>& S, BMoves& MV) 
 // front[0] (as traverse_mc, the two targets of a move sharing an entry); on return
 // MV.pot[t] holds target t's potential.  N_0 = 0: a cell holding a remaining source
 // is far if it passes the MAC, else opened if it has children, else summed directly.
-template <int BLOCK, class Hook>
+template <bool F32, int BLOCK, class Hook>
 __device__ void traverse_mb(const Rep& R, BTrav<BLOCK>& S, BMoves& MV, Hook&& hook) {
     using TS = BTrav<BLOCK>;
     constexpr int NW = TS::NW;
@@ -348,13 +349,15 @@ __device__ void traverse_mb(const Rep& R, BTrav<BLOCK>& S, BMoves& MV, Hook&& ho
         for (int base = 0; base < fs; base += kChunk * BLOCK) {
             if (far_n > TS::FARCAP - kChunk * BLOCK) {
                 __syncthreads();
-                far_pass_mb<BLOCK>(R, S, MV, far_n, 0, acc);
+                far_pass_mb<F32, BLOCK>(R, S, MV, far_n, 0, acc);
                 far_n = 0;
                 __syncthreads();
             }
             if (near_n > TS::NEARCAP - kChunk * BLOCK) {
                 __syncthreads();
                 const int total = near_scan_mb<BLOCK>(S, near_n);
+                near_list<BLOCK>(S.near_own, S.near_pre, near_n, total, TS::OWNCAP);
+                __syncthreads();
                 near_pass_mb<BLOCK>(R, S, MV, near_n, total, acc);
                 near_n = 0;
                 __syncthreads();
@@ -509,25 +512,12 @@ __device__ void traverse_mb(const Rep& R, BTrav<BLOCK>& S, BMoves& MV, Hook&& ho
         __syncthreads();
         return;
     }
-    // corrected moments of the far cells that hold a mover's own ion or image
-    for (int it = tid; it < nflag * NTERM; it += BLOCK) {
-        const int f = it / NTERM, k = it % NTERM;
-        const uint32_t e = S.flagl[f];
-        const int c = (int)(e & kCellMask), b = mv_of(e);
-        if (c >= R.ncell) { S.err = kErrFlagCell; S.Mx[f][k] = 0.0; continue; }
-        const double4 g = R.cgeo[c];
-        double mk = R.M[(size_t)c * MSTR + k];
-        if (e & kMbIon) { const double4 s = MV.ct[b][0]; mk = mk - s.w * mono(S.mi[k], s.x - g.x, s.y - g.y, s.z - g.z); }
-        if (e & kMbImg) { const double4 s = MV.ct[b][2]; mk = mk - s.w * mono(S.mi[k], s.x - g.x, s.y - g.y, s.z - g.z); }
-        S.Mx[f][k] = mk;
-    }
-    const int total = near_scan_mb<BLOCK>(S, near_n);  // its barriers also publish Mx
+    const int total = near_scan_mb<BLOCK>(S, near_n);
+    near_list<BLOCK>(S.near_own, S.near_pre, near_n, total, TS::OWNCAP);
     PHASE(kPhFlagged);
-    far_pass_mb<BLOCK>(R, S, MV, far_n, nflag, acc);
-#ifdef BHMC_PHASE_TIMERS
-    __syncthreads();
+    far_pass_mb<F32, BLOCK>(R, S, MV, far_n, nflag, acc);
+    __syncthreads();  // publishes near_own
     PHASE(kPhFar);
-#endif
     near_pass_mb<BLOCK>(R, S, MV, near_n, total, acc);
 #pragma unroll
     for (int k = 0; k < kBM; ++k) {
@@ -589,7 +579,7 @@ __device__ __forceinline__ void prefetch_stage_mb(const Rep& R, BMoves& MV, int 
 
 // One round of up to nb moves (draws b0 .. b0 + nb - 1 of MV's batch, move indices
 // m .. m + nb - 1).  Returns the number of moves consumed and a stop status.
-template <int BLOCK>
+template <bool F32, int BLOCK>
 __device__ RoundOut round_mb(const Rep& R, BTrav<BLOCK>& S, BMoves& MV, int b0, int nb) {
     static_assert(BLOCK >= 256, "the path descents and the commit prefetch run on the last two waves");
     const int tid = threadIdx.x;
@@ -613,6 +603,7 @@ __device__ RoundOut round_mb(const Rep& R, BTrav<BLOCK>& S, BMoves& MV, int b0, 
         if (j == 0) {
             MV.ion[b] = i;
             MV.alpha[b] = MV.dr_d[b0 + b][3];
+            MV.thr[b] = MV.dr_t[b0 + b];
             MV.wall[b] = outside(R, rx, ry, rz) ? 1 : 0;
             MV.tx[2 * b] = si.x; MV.ty[2 * b] = si.y; MV.tz[2 * b] = si.z;
             MV.tx[2 * b + 1] = rx; MV.ty[2 * b + 1] = ry; MV.tz[2 * b + 1] = rz;
@@ -699,7 +690,7 @@ __device__ RoundOut round_mb(const Rep& R, BTrav<BLOCK>& S, BMoves& MV, int b0, 
 #endif
     };
     PHASE(kPhSetup);
-    traverse_mb<BLOCK>(R, S, MV, hook);
+    traverse_mb<F32, BLOCK>(R, S, MV, hook);
 #ifdef BHMC_PHASE_TIMERS
     ph_t0_ = wall_clock64();
 #endif
@@ -723,26 +714,32 @@ __device__ RoundOut round_mb(const Rep& R, BTrav<BLOCK>& S, BMoves& MV, int b0, 
         __syncthreads();
         return o;
     }
-    // ---- in parallel (threads 0-127, 128-191, 192-199): corrections (thread (j, b, t), j < b: what move j's four contributions add
-    // to target t of move b once j is committed); for every pair, whether b's new position
-    // overlaps j's and how j changes the counts of b's new leaves; for every move, its energy
-    // change on the start-of-round tree and whether its tracked leaves are the ones its keys
-    // lead to
-    if (tid < 2 * nb * nb) {
-        const int j = tid / (2 * nb), b = (tid >> 1) % nb, tb = tid & 1;
-        if (j < b && !MV.wall[j] && !MV.wall[b]) {
-            const int t = 2 * b + tb;
-            const double x = MV.tx[t], y = MV.ty[t], z = MV.tz[t];
-            double v = 0.0;
-            for (int cc = 0; cc < nps; ++cc) {
-                const double w = MV.ct[j][cc].w * path_value(R, MV, j, cc, x, y, z);
-                v = (cc & 1) ? v + w : v - w;
-            }
-            MV.corr[j][b][tb] = v;
-        }
-    } else if (tid >= 128 && tid < 128 + nb * nb) {
-        const int j = (tid - 128) / nb, b = (tid - 128) % nb;
-        if (j < b && !MV.wall[j] && !MV.wall[b]) {
+    // ---- in parallel: corrections (eight lanes per pair j < b, one per target t of move b and
+    // contribution of move j: what committing move j adds to it, summed over the contributions
+    // in their order); on the last wave, for every pair, whether b's new position overlaps j's
+    // and how j changes the counts of b's new leaves; on the wave before it, for every move, its
+    // energy change on the start-of-round tree outside the traversal and whether its tracked
+    // leaves are the ones its keys lead to
+    const int npair = nb * (nb - 1) / 2;
+    auto pair_of = [](int k, int& j, int& b) {  // k = b (b - 1) / 2 + j
+        b = 1;
+        while ((b + 1) * b / 2 <= k) ++b;
+        j = k - b * (b - 1) / 2;
+    };
+    for (int it = tid; it < 8 * npair; it += BLOCK) {
+        int j, b;
+        pair_of(it >> 3, j, b);
+        const int tb = it & 1, cc = (it >> 1) & 3;
+        double w = 0.0;
+        if (!MV.wall[j] && !MV.wall[b] && cc < nps)
+            w = MV.ct[j][cc].w * path_value(R, MV, j, cc, MV.tx[2 * b + tb], MV.ty[2 * b + tb], MV.tz[2 * b + tb]);
+        const double w1 = __shfl_down(w, 2, 64), w2 = __shfl_down(w, 4, 64), w3 = __shfl_down(w, 6, 64);
+        if (cc == 0) MV.corr[j][b][tb] = (((0.0 - w) + w1) - w2) + w3;
+    }
+    for (int it = BLOCK - 1 - tid; it < npair; it += BLOCK) {
+        int j, b;
+        pair_of(it, j, b);
+        if (!MV.wall[j] && !MV.wall[b]) {
             const double4 sn = MV.ct[b][1], s = MV.ct[j][1];
             const double dx = sn.x - s.x, dy = sn.y - s.y, dz = sn.z - s.z;
             if (dx * dx + dy * dy + dz * dz <= R.tau2) atomicOr(&MV.ovl_new[b], 1u << j);
@@ -757,8 +754,9 @@ __device__ RoundOut round_mb(const Rep& R, BTrav<BLOCK>& S, BMoves& MV, int b0, 
             MV.e_ion[b][j] = ei;
             MV.e_img[b][j] = em;
         }
-    } else if (tid >= 192 && tid < 192 + nb) {
-        const int b = tid - 192;
+    }
+    if (BLOCK - 65 - tid >= 0 && BLOCK - 65 - tid < nb) {
+        const int b = BLOCK - 65 - tid;
         if (!MV.wall[b]) {
             const double4 sn = MV.ct[b][1], so = MV.ct[b][0];
             const double q = so.w, l = R.l_B;
@@ -799,7 +797,10 @@ __device__ RoundOut round_mb(const Rep& R, BTrav<BLOCK>& S, BMoves& MV, int b0, 
         const uint32_t my_moved = mine ? MV.ovl_moved[lane] : 0u, my_new = mine ? MV.ovl_new[lane] : 0u;
         const double my_pn = mine ? MV.pot[2 * lane + 1] : 0.0, my_po = mine ? MV.pot[2 * lane] : 0.0;
         const double my_q = mine ? MV.ct[lane][0].w : 0.0, my_d0 = mine ? MV.dE0[lane] : 0.0;
-        const double my_alpha = mine ? MV.alpha[lane] : 0.0;
+        const double my_alpha = mine ? MV.alpha[lane] : 0.0, my_thr = mine ? MV.thr[lane] : 0.0;
+        // alpha <= exp(-dE) is dE <= -log(alpha) but for roundings: within this margin of equality
+        // the exponential itself decides
+        const double my_margin = 1e-9 * (1.0 + fabs(my_thr));
         const int my_sane = mine ? MV.sane[lane] : 0;
         const int my_cio = mine ? MV.tr[lane][0].x : -1;
         const int my_cin = mine ? MV.path[lane][1][MV.plen[lane][1] - 1] : -1;
@@ -812,6 +813,8 @@ __device__ RoundOut round_mb(const Rep& R, BTrav<BLOCK>& S, BMoves& MV, int b0, 
         int my_reason = 0, my_acc = 0;
         double my_dE = kInf;
         bool ended = false;
+        double c1 = 0.0, c0 = 0.0;  // what the moves accepted so far add to this lane's move
+        int ei = 0, em = 0;
 #pragma unroll
         for (int b = 0; b < kBM; ++b) {
             if (b >= nb || ended) continue;  // uniform
@@ -825,14 +828,11 @@ __device__ RoundOut round_mb(const Rep& R, BTrav<BLOCK>& S, BMoves& MV, int b0, 
                 } else if (my_fixed != 0 || (my_moved & ~acc_mask) != 0u || (my_new & acc_mask) != 0u) {
                     reason = 2;
                 } else {
-                    double c1 = 0.0, c0 = 0.0;
-                    int ei = 0, em = 0;
-#pragma unroll
-                    for (int j = 0; j < kBM; ++j)
-                        if (j < b && ((acc_mask >> j) & 1u)) { c1 += cr1[j]; c0 += cr0[j]; ei += ei_r[j]; em += em_r[j]; }
                     const double pn = my_pn + c1, po = my_po + c0;
                     dE = R.l_B * my_q * (pn - po) + my_d0;
-                    if (dE <= 0.0 || my_alpha <= exp(-dE)) {
+                    bool take = dE <= 0.0 || dE < my_thr - my_margin;
+                    if (!take && !(dE > my_thr + my_margin)) take = my_alpha <= exp(-dE);
+                    if (take) {
                         if (!my_sane) {
                             out = 4;
                         } else {
@@ -851,7 +851,11 @@ __device__ RoundOut round_mb(const Rep& R, BTrav<BLOCK>& S, BMoves& MV, int b0, 
             out = __builtin_amdgcn_readlane(out, b);  // uniform from here
             if (out & 4) { err = kErrCommitSlot; done = b; ended = true; continue; }
             if (out & 2) { stop = -6; done = b; ended = true; continue; }
-            if (out & 1) acc_mask |= 1u << b;
+            if (out & 1) {
+                acc_mask |= 1u << b;
+                c1 += cr1[b]; c0 += cr0[b];  // zero in the lanes up to b
+                ei += ei_r[b]; em += em_r[b];
+            }
             if (lane == b) { my_reason = reason; my_dE = dE; my_acc = out & 1; }
         }
         if (mine) {
@@ -885,6 +889,19 @@ __device__ RoundOut round_mb(const Rep& R, BTrav<BLOCK>& S, BMoves& MV, int b0, 
             MV.op_base[lane] = hdr.z;
             MV.op_count[lane] = hdr.x;
         }
+        {   // first table row of each path of the accepted moves: an exclusive scan of the path lengths
+            const int j = lane >> 2, cc = lane & 3;
+            const bool on = lane < 4 * kBM && j < done && ((acc_mask >> j) & 1u) && cc < nps;
+            const int len = on ? MV.plen[j][cc] : 0;
+            int x = len;
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+                const int y = __shfl_up(x, off, 64);
+                if (lane >= off) x += y;
+            }
+            if (lane < 4 * kBM) MV.pw_row[lane] = on ? x - len : -1;
+            if (lane == 63) MV.pw_rows = x;
+        }
     }
     __syncthreads();
     PHASE(kPhDecide);
@@ -899,163 +916,217 @@ __device__ RoundOut round_mb(const Rep& R, BTrav<BLOCK>& S, BMoves& MV, int b0, 
     // A source that fills a hole and leaves the leaf later in the round has its slot followed in
     // op_slot; its final tracking is written by the lane of the leaf it moves to.
     if (tid < 64) {
-        // lane o < 4 kBM holds operation o; the loops below walk the operations in order, the
-        // same for every lane, reading each one's fields from its lane
+        // lane o < 4 kBM holds operation o; the first lane of a leaf takes that leaf's operations
+        // (mostly one or two) in order, the leaves side by side
         const int o = tid;
         const bool has = o < 4 * kBM;
         const int my_type = has ? MV.op_type[o] : 0;
         const int my_cell = has ? MV.op_cell[o] : -1;
-        const int my_src = has ? MV.op_src[o] : -1;
         const int base = has ? MV.op_base[o] : 0;
         int count = has ? MV.op_count[o] : 0;
-        bool lead = my_type != 0;
+        uint32_t ops = 0;  // the operations on this lane's leaf
 #pragma unroll
         for (int o2 = 0; o2 < 4 * kBM; ++o2) {
             const int t2 = __builtin_amdgcn_readlane(my_type, o2), c2 = __builtin_amdgcn_readlane(my_cell, o2);
-            if (o2 < o && t2 != 0 && c2 == my_cell) lead = false;
+            if (t2 != 0 && c2 == my_cell) ops |= 1u << o2;
         }
-        bool touched = false;  // an earlier operation of the round has changed this leaf
-        for (int o2 = 0; o2 < 4 * kBM; ++o2) {
-            const int type = __builtin_amdgcn_readlane(my_type, o2);
-            if (type == 0) continue;  // uniform
-            const int cell = __builtin_amdgcn_readlane(my_cell, o2);
-            const int src = __builtin_amdgcn_readlane(my_src, o2);
-            if (!lead || cell != my_cell) continue;
-            const double4 nv = MV.ct[o2 >> 2][(o2 & 3) == 0 || (o2 & 3) == 1 ? 1 : 3];
-            if (type == 2) {  // append
-                R.pool4[base + count] = nv;
-                R.pidx[base + count] = src;
-                R.track[src] = make_int2(cell, count);
-                ++count;
-            } else {
-                const int k = MV.op_slot[o2];
-                if (type == 3) {  // the source stays in this leaf: new position in place
-                    R.pool4[base + k] = nv;
-                } else {          // delete: the last entry fills the hole
-                    const int last = count - 1;
-                    if (k != last) {
-                        // untouched, the leaf is as it was when its last entry was prefetched
-                        const int jb = o2 >> 2, jj = (o2 & 3) >> 1;
-                        const int moved = touched ? R.pidx[base + last] : MV.last_pidx[jb][jj];
-                        const double4 mv = touched ? R.pool4[base + last] : MV.last_pool[jb][jj];
-                        R.pool4[base + k] = mv;
-                        R.pidx[base + k] = moved;
-                        bool leaves_later = false;
-                        for (int o3 = o2 + 1; o3 < 4 * kBM; ++o3)
-                            if (MV.op_cell[o3] == cell && (MV.op_type[o3] == 1 || MV.op_type[o3] == 3) &&
-                                MV.op_src[o3] == moved) {
-                                MV.op_slot[o3] = k;
-                                leaves_later = MV.op_type[o3] == 1;
+        if (my_type != 0 && __builtin_ctz(ops) == o) {
+            const int cell = my_cell;
+            bool touched = false;  // an earlier operation of the round has changed this leaf
+            for (uint32_t rest = ops; rest; rest &= rest - 1u) {
+                const int o2 = __builtin_ctz(rest);
+                const int type = MV.op_type[o2], src = MV.op_src[o2];
+                const double4 nv = MV.ct[o2 >> 2][(o2 & 2) ? 3 : 1];
+                if (type == 2) {  // append
+                    R.pool4[base + count] = nv;
+                    R.pidx[base + count] = src;
+                    R.track[src] = make_int2(cell, count);
+                    ++count;
+                } else {
+                    const int k = MV.op_slot[o2];
+                    if (type == 3) {  // the source stays in this leaf: new position in place
+                        R.pool4[base + k] = nv;
+                    } else {          // delete: the last entry fills the hole
+                        const int last = count - 1;
+                        if (k != last) {
+                            // untouched, the leaf is as it was when its last entry was prefetched
+                            const int jb = o2 >> 2, jj = (o2 & 3) >> 1;
+                            const int moved = touched ? R.pidx[base + last] : MV.last_pidx[jb][jj];
+                            const double4 mv = touched ? R.pool4[base + last] : MV.last_pool[jb][jj];
+                            R.pool4[base + k] = mv;
+                            R.pidx[base + k] = moved;
+                            bool leaves_later = false;
+                            for (uint32_t later = rest & (rest - 1u); later; later &= later - 1u) {
+                                const int o3 = __builtin_ctz(later);
+                                if (MV.op_type[o3] != 2 && MV.op_src[o3] == moved) {
+                                    MV.op_slot[o3] = k;
+                                    leaves_later = MV.op_type[o3] == 1;
+                                }
                             }
-                        if (moved < 0 || moved >= R.nsrc) MV.err = kErrCommitSource;
-                        else if (!leaves_later) R.track[moved] = make_int2(cell, k);
+                            if (moved < 0 || moved >= R.nsrc) MV.err = kErrCommitSource;
+                            else if (!leaves_later) R.track[moved] = make_int2(cell, k);
+                        }
+                        count = last;
                     }
-                    count = last;
                 }
+                if (type != 1) R.src[src] = nv;
+                touched = true;
             }
-            if (type != 1) R.src[src] = nv;
-            touched = true;
+            R.cm[cell].x = count;
         }
-        if (lead) R.cm[my_cell].x = count;
     }
-    // ---- meanwhile, on the other waves: distinct cells of the accepted moves' root paths, in
-    // (move, contribution) order, each with the contributions that apply to it
-    for (int it = tid - 64; it < ndone * 4 * kMaxLevels; it += BLOCK - 64) {
-        if (it < 0) break;  // the first wave (leaf index arrays above)
-        const int j = it / (4 * kMaxLevels), cc = (it / kMaxLevels) & 3, l = it % kMaxLevels;
-        if (!MV.acc[j] || cc >= nps || l >= MV.plen[j][cc]) continue;
-        const int c = MV.path[j][cc][l];
-        bool owner = true;
-        for (int jj = 0; jj <= j && owner; ++jj) {
-            if (!MV.acc[jj]) continue;
-            const int cmax = jj < j ? nps : cc;
-            for (int c2 = 0; c2 < cmax; ++c2)
-                if (l < MV.plen[jj][c2] && MV.path[jj][c2][l] == c) { owner = false; break; }
+    // ---- meanwhile, on the other waves: the distinct cells of the accepted moves' root paths, a
+    // level per wave at a time (lane 4 j + cc holds the cell of contribution cc of move j; comparing
+    // it with every other lane's gives the contributions that apply to the cell), and the first
+    // table of the path entries' harmonics
+    constexpr int HROWS = BTrav<BLOCK>::HROWS;
+    const bool cart = F32 && R.M32;  // uniform: the commit repairs the Cartesian moments (below)
+    if (tid >= 64) {
+        const int lane = lane_id(), j = lane >> 2, cc = lane & 3;
+        const bool on = lane < 4 * kBM && MV.pw_row[lane < 4 * kBM ? lane : 0] >= 0;
+        const int len = on ? MV.plen[j][cc] : 0;
+        int maxlen = len;
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) maxlen = max(maxlen, __shfl_xor(maxlen, off, 64));
+        for (int l = wave_id() - 1; l < maxlen; l += BLOCK / 64 - 1) {  // uniform in a wave
+            const int c = l < len ? MV.path[j][cc][l] : -1 - lane;
+            uint32_t mask = 0;
+#pragma unroll
+            for (int k = 0; k < 4 * kBM; ++k) {
+                const uint32_t m = (uint32_t)__ballot(c == __builtin_amdgcn_readlane(c, k));
+                if (lane == k) mask = m;
+            }
+            const bool owner = l < len && __builtin_ctz(mask) == lane;
+            const uint64_t owners = __ballot(owner);
+            int at = 0;
+            if (lane == 0) at = atomicAdd(&MV.nlist, __popcll(owners));
+            at = __shfl(at, 0, 64);
+            if (owner) {
+                const int slot = at + __popcll(owners & lanemask_lt());
+                MV.list_cell[slot] = c;
+                MV.list_mask[slot] = mask;
+                MV.list_at[slot] = (lane * kMaxLevels + l) | (l < len - 1 ? (1 << 30) : 0);
+            }
         }
-        if (!owner) continue;
-        uint32_t mask = 0;
-        for (int jj = j; jj < ndone; ++jj) {
-            if (!MV.acc[jj]) continue;
-            for (int c2 = (jj == j ? cc : 0); c2 < nps; ++c2)
-                if (l < MV.plen[jj][c2] && MV.path[jj][c2][l] == c) mask |= 1u << (4 * jj + c2);
-        }
-        const int slot = atomicAdd(&MV.nlist, 1);
-        MV.list_cell[slot] = c;
-        MV.list_mask[slot] = mask;
-        MV.list_at[slot] = ((j * 4 + cc) * kMaxLevels + l) | (l < MV.plen[j][cc] - 1 ? (1 << 30) : 0);
     }
+    // Table rows r0 .. r0 + HROWS - 1 of the path entries: a lane forms the whole row of one entry
+    auto fill_rows = [&](int r0, int first, int stride) {
+        const int r1 = min(MV.pw_rows, r0 + HROWS);
+        for (int r = r0 + first; r < r1; r += stride) {
+            int jc = 0;  // the last path whose first row is at most r
+#pragma unroll
+            for (int k = 1; k < 4 * kBM; ++k) {
+                const int f = MV.pw_row[k];
+                if (f >= 0 && f <= r) jc = k;
+            }
+            // paths before the first accepted move have no row; jc = 0 then is not one of them
+            const double4 sc = (&MV.ct[0][0])[jc], g = (&MV.path_geo[0][0][0])[jc * kMaxLevels + (r - MV.pw_row[jc])];
+            reg_row(sc.x - g.x, sc.y - g.y, sc.z - g.z, (jc & 1) ? sc.w : -sc.w, S.hrow[r - r0]);
+        }
+    };
+    if (!cart && tid >= 64) fill_rows(0, tid - 64, BLOCK - 64);
     __syncthreads();
     PHASE(kPhSlots);
-    // ---- moments and counts of the distinct path cells, contributions in move order.  The powers
-    // of each path entry's offset from its cell centre are tabulated first (in the traversal's
-    // list space), so a term is three table reads per contribution; without room, d^n is
-    // formed by repeated multiplication.
-    if (tid < 64) {  // first power-table row of each path entry: an exclusive scan of the path lengths
-        const int jc = tid, j = jc >> 2, cc = jc & 3;
-        const bool on = jc < 4 * kBM && j < ndone && MV.acc[j] && cc < nps;
-        const int len = on ? MV.plen[j][cc] : 0;
-        int x = len;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const int y = __shfl_up(x, off, 64);
-            if (tid >= off) x += y;
-        }
-        if (jc < 4 * kBM) MV.pw_row[jc] = on ? x - len : -1;
-        if (tid == 63) MV.pw_rows = x;
-    }
-    __syncthreads();
-    const bool use_pw = MV.pw_rows <= BTrav<BLOCK>::PWROWS;
-    if (use_pw) {
-        for (int it = tid; it < 4 * kBM * kMaxLevels * 3; it += BLOCK) {
-            const int jc = it / (kMaxLevels * 3), l = (it / 3) % kMaxLevels, ax = it % 3;
-            const int j = jc >> 2, cc = jc & 3;
-            if (MV.pw_row[jc] < 0 || l >= MV.plen[j][cc]) continue;
-            const double4 sc = MV.ct[j][cc], g = MV.path_geo[j][cc][l];
-            const double d = ax == 0 ? sc.x - g.x : (ax == 1 ? sc.y - g.y : sc.z - g.z);
-            double* row = S.pw[MV.pw_row[jc] + l][ax];
-            double v = 1.0;
-            row[0] = 1.0;
-            for (int e = 1; e <= P; ++e) { v *= d; row[e] = v; }
-        }
-        __syncthreads();
-    }
-    const int items = MV.nlist * NTERM;
-    constexpr int G = 4;
-    for (int base = tid; base < items; base += G * BLOCK) {
-        double mk[G];
-#pragma unroll
-        for (int u = 0; u < G; ++u) {
-            const int it = base + u * BLOCK;
-            if (it < items) mk[u] = R.M[(size_t)MV.list_cell[it / NTERM] * MSTR + it % NTERM];
-        }
-#pragma unroll
-        for (int u = 0; u < G; ++u) {
-            const int it = base + u * BLOCK;
-            if (it >= items) continue;
-            const int li = it / NTERM, k = it % NTERM;
-            const int c = MV.list_cell[li];
-            const int at = MV.list_at[li];
-            const int l = (at & ((1 << 30) - 1)) % kMaxLevels;
-            const uint32_t code = S.mi[k];
-            const int n1 = (int)(code & 255u), n2 = (int)((code >> 8) & 255u), n3 = (int)(code >> 16);
-            double m = mk[u];
-            int dc = 0;
-            for (uint32_t rest = MV.list_mask[li]; rest; rest &= rest - 1u) {
-                const int bit = __builtin_ctz(rest);
-                const double4 sc = MV.ct[bit >> 2][bit & 3];
-                double v;
-                if (use_pw) {
-                    const int row = MV.pw_row[bit] + l;
-                    v = S.pw[row][0][n1] * S.pw[row][1][n2] * S.pw[row][2][n3];
-                } else {
-                    const double4 g = MV.path_geo[bit >> 2][bit & 3][l];
-                    v = mono(code, sc.x - g.x, sc.y - g.y, sc.z - g.z);
+    // ---- expansion rows and counts of the distinct path cells, contributions in move order: one
+    // coefficient of a cell per item, a table read per contribution.  Paths with more entries than
+    // the table holds (at high orders) are taken in several tables, the rows of the earlier moves first.
+    if (!cart) {
+        for (int r0 = 0;;) {
+            const int items = MV.nlist * NH;
+            for (int it = tid; it < items; it += BLOCK) {
+                const int li = it / NH, k = it % NH;
+                const int c = MV.list_cell[li], at = MV.list_at[li];
+                const int l = (at & ((1 << 30) - 1)) % kMaxLevels;
+                double* const hp = R.H + (size_t)c * HSTR + k;
+                double h = *(GRow)hp;
+                uint32_t rest = MV.list_mask[li];
+                if (r0 == 0 && k == 0 && (at & (1 << 30))) {
+                    const int dc = __popc(rest & 0xAAAAAAAAu) - __popc(rest & 0x55555555u);
+                    if (dc != 0) R.cm[c].x += dc;
                 }
-                if (bit & 1) { m = m + sc.w * v; ++dc; } else { m = m - sc.w * v; --dc; }
+                while (rest) {  // four contributions at a time, so that their reads overlap
+                    int row[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        row[u] = rest ? MV.pw_row[__builtin_ctz(rest)] + l - r0 : -1;
+                        rest &= rest - 1u;
+                    }
+                    double v[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) v[u] = (row[u] >= 0 && row[u] < HROWS) ? S.hrow[row[u]][k] : 0.0;
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) h += v[u];
+                }
+                *hp = h;
             }
-            R.M[(size_t)c * MSTR + k] = m;
-            if (R.M32) R.M32[(size_t)c * MSTR + k] = (float)m;
-            if (k == 0 && (at & (1 << 30)) && dc != 0) R.cm[c].x += dc;
+            r0 += HROWS;
+            if (r0 >= MV.pw_rows) break;  // uniform
+            __syncthreads();
+            fill_rows(r0, tid, BLOCK);
+            __syncthreads();
+        }
+    }
+    // the Cartesian moments and their single-precision copy, kept where the far field reads that
+    // copy.  The powers of each path entry's offset from its cell centre are tabulated first (in
+    // the traversal's list space), so a term is three table reads per contribution; without room,
+    // d^n is formed by repeated multiplication.
+    if (cart) {
+        const bool use_pw = MV.pw_rows <= BTrav<BLOCK>::PWROWS;
+        if (use_pw) {
+            for (int it = tid; it < 4 * kBM * kMaxLevels * 3; it += BLOCK) {
+                const int jc = it / (kMaxLevels * 3), l = (it / 3) % kMaxLevels, ax = it % 3;
+                const int j = jc >> 2, cc = jc & 3;
+                if (MV.pw_row[jc] < 0 || l >= MV.plen[j][cc]) continue;
+                const double4 sc = MV.ct[j][cc], g = MV.path_geo[j][cc][l];
+                const double d = ax == 0 ? sc.x - g.x : (ax == 1 ? sc.y - g.y : sc.z - g.z);
+                double* row = S.pw[MV.pw_row[jc] + l][ax];
+                double v = 1.0;
+                row[0] = 1.0;
+                for (int e = 1; e <= P; ++e) { v *= d; row[e] = v; }
+            }
+            __syncthreads();
+        }
+        const int items = MV.nlist * NTERM;
+        constexpr int G = 4;
+        for (int base = tid; base < items; base += G * BLOCK) {
+            double mk[G];
+#pragma unroll
+            for (int u = 0; u < G; ++u) {
+                const int it = base + u * BLOCK;
+                if (it < items) mk[u] = R.M[(size_t)MV.list_cell[it / NTERM] * MSTR + it % NTERM];
+            }
+#pragma unroll
+            for (int u = 0; u < G; ++u) {
+                const int it = base + u * BLOCK;
+                if (it >= items) continue;
+                const int li = it / NTERM, k = it % NTERM;
+                const int c = MV.list_cell[li];
+                const int at = MV.list_at[li];
+                const int l = (at & ((1 << 30) - 1)) % kMaxLevels;
+                const uint32_t code = S.mi[k];
+                const int n1 = (int)(code & 255u), n2 = (int)((code >> 8) & 255u), n3 = (int)(code >> 16);
+                double m = mk[u];
+                for (uint32_t rest = MV.list_mask[li]; rest; rest &= rest - 1u) {
+                    const int bit = __builtin_ctz(rest);
+                    const double4 sc = MV.ct[bit >> 2][bit & 3];
+                    double v;
+                    if (use_pw) {
+                        const int row = MV.pw_row[bit] + l;
+                        v = S.pw[row][0][n1] * S.pw[row][1][n2] * S.pw[row][2][n3];
+                    } else {
+                        const double4 g = MV.path_geo[bit >> 2][bit & 3][l];
+                        v = mono(code, sc.x - g.x, sc.y - g.y, sc.z - g.z);
+                    }
+                    m = (bit & 1) ? m + sc.w * v : m - sc.w * v;
+                }
+                R.M[(size_t)c * MSTR + k] = m;
+                R.M32[(size_t)c * MSTR + k] = (float)m;
+                if (k == 0 && (at & (1 << 30))) {
+                    const uint32_t mask = MV.list_mask[li];
+                    const int dc = __popc(mask & 0xAAAAAAAAu) - __popc(mask & 0x55555555u);
+                    if (dc != 0) R.cm[c].x += dc;
+                }
+            }
         }
     }
     __syncthreads();
@@ -1070,7 +1141,7 @@ __device__ RoundOut round_mb(const Rep& R, BTrav<BLOCK>& S, BMoves& MV, int b0, 
 // Persistent Metropolis kernel with batched rounds (same queue, statistics and stop
 // protocol as k_mc): each workgroup takes replicas from the queue and advances its
 // chain round by round.  A.bm caps the moves per round (at most kBM).
-template <int BLOCK>
+template <int BLOCK, bool F32>
 __global__ void __launch_bounds__(BLOCK) k_mcb(Rep* reps, McArgs A) {
     __shared__ BTrav<BLOCK> S;
     __shared__ BMoves MV;
@@ -1078,6 +1149,7 @@ __global__ void __launch_bounds__(BLOCK) k_mcb(Rep* reps, McArgs A) {
     __shared__ int s_r;
     const int tid = threadIdx.x;
     for (int k = tid; k < NTERM; k += BLOCK) S.mi[k] = mi_code(k);
+    fill_htab(S.ht);
 #ifdef BHMC_PHASE_TIMERS
     for (int k = tid; k < kNumPhases; k += BLOCK) s_phase[k] = 0;
 #endif
@@ -1104,6 +1176,7 @@ __global__ void __launch_bounds__(BLOCK) k_mcb(Rep* reps, McArgs A) {
                     MV.dr_i[tid] = d.i;
                     MV.dr_d[tid][0] = d.dx; MV.dr_d[tid][1] = d.dy; MV.dr_d[tid][2] = d.dz;
                     MV.dr_d[tid][3] = d.alpha;
+                    MV.dr_t[tid] = -log(d.alpha);
                 }
                 __syncthreads();
             }
@@ -1117,7 +1190,7 @@ __global__ void __launch_bounds__(BLOCK) k_mcb(Rep* reps, McArgs A) {
                 for (int j = 0; j < b; ++j) rep = rep || MV.dr_i[b0 + b] == MV.dr_i[b0 + j];
                 if (rep) { nb = b; break; }
             }
-            const RoundOut o = round_mb<BLOCK>(Rs, S, MV, b0, nb);
+            const RoundOut o = round_mb<F32, BLOCK>(Rs, S, MV, b0, nb);
             if (tid == 0) {
                 for (int b = 0; b < o.done; ++b) {
                     ++st_moves;
