@@ -331,9 +331,11 @@ bhmc_status bhmc_get_state(bhmc_tree* tree, int32_t replica, double* x, double* 
 
 /* Recompute a replica's moments (eq. 3.3) from the current members of its
  * leaves, on the tree as it stands (no change of cells or leaf index
- * arrays): P2M at the leaves, then M2M up the tree.  Accepted moves repair the
- * moments incrementally (Sec. 3.3); this replaces them by a fresh sum, which
- * differs from the repaired one only by rounding. */
+ * arrays): P2M at the leaves, then M2M up the tree, then the rows that the
+ * traversals read (the expansion's harmonic coefficients, formed from the
+ * moments).  Accepted moves repair those rows incrementally (Sec. 3.3); this
+ * replaces them by fresh ones, which differ from the repaired ones only by
+ * rounding. */
 bhmc_status bhmc_refresh_moments(bhmc_tree* tree, int32_t replica);
 
 /* Rebuild a replica's tree from its current positions. */
@@ -346,7 +348,9 @@ bhmc_status bhmc_rebuild(bhmc_tree* tree, int32_t replica);
  *     (u64), current count N_A (i32), link (i32: first child >= 0, or -1-leaf
  *     for a leaf), geometry (4 f64: centre x y z, half side h), moments
  *     (nterms f64 per cell, graded multi-index order s = 0..p, n1 = s..0,
- *     n2 = s-n1..0).  Cells are numbered level by level, children of a cell
+ *     n2 = s-n1..0; of the cell's current members: after moves they are summed
+ *     afresh by this call, except with far_fp32, whose moves repair them).
+ *     Cells are numbered level by level, children of a cell
  *     consecutive in digit order 4 x + 2 y + z.
  *   bhmc_get_leaves: per leaf (nleaf): cell (i32), slot base (i32), capacity
  *     (i32), build range begin/end in the sorted order (i32).
