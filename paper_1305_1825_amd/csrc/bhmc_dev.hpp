@@ -196,8 +196,16 @@ __device__ __forceinline__ double rsqrt_nr(double x) {
 }
 
 // ------------------------------------------------------------ block primitives
-__device__ __forceinline__ int lane_id() { return (int)(threadIdx.x & 63); }
-__device__ __forceinline__ int wave_id() { return (int)(threadIdx.x >> 6); }
+// The thread index as a value the compiler takes for new at every call: what is derived
+// from it (dozens of per-thread LDS addresses) is then formed where it is used instead of
+// being hoisted out of a chain's move loop and held, or spilled, across all of it.
+__device__ __forceinline__ int fresh_tid() {
+    int t = (int)threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
+__device__ __forceinline__ int lane_id() { return fresh_tid() & 63; }
+__device__ __forceinline__ int wave_id() { return fresh_tid() >> 6; }
 
 __device__ __forceinline__ uint64_t shfl_up_u64(uint64_t v, int d) {
     uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);

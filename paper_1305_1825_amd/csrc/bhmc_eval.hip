@@ -149,6 +149,35 @@ __device__ __forceinline__ int2 gload(const int2* p) {
 }
 __device__ __forceinline__ int gload(const int* p) { return *(GInt)p; }
 
+// The descriptor fields that the traversals use per lane, held in scalar registers.  Read
+// from the workgroup's copy in LDS where they are used, they are vector values to the
+// compiler, which keeps dozens of them in vector registers across the whole round.
+__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ long long uni(long long v) {
+    return (long long)(((uint64_t)(uint32_t)uni((int)(v >> 32)) << 32) | (uint32_t)uni((int)v));
+}
+__device__ __forceinline__ double uni(double v) { return __longlong_as_double(uni(__double_as_longlong(v))); }
+template <class T>
+__device__ __forceinline__ T* uni(T* v) { return (T*)uni((long long)v); }
+
+struct RepU {
+    const Rep& d;
+    double4* cgeo; int4* cm; double* H; double* M; float* M32; double4* pool4; int* pidx; double4* src; int2* track;
+    uint32_t* spill;
+    long long spill_words;
+    double theta2, reach2, tau2, l_B, a, a2, gamma, Qc;
+    int n, nsrc, ncell, pool, n0, images, geom, nline, fcap, spill_regions;
+    const double *line_t, *line_c;
+    __device__ __forceinline__ explicit RepU(const Rep& r)
+        : d(r), cgeo(uni(r.cgeo)), cm(uni(r.cm)), H(uni(r.H)), M(uni(r.M)), M32(uni(r.M32)), pool4(uni(r.pool4)),
+          pidx(uni(r.pidx)), src(uni(r.src)), track(uni(r.track)), spill(uni(r.spill)), spill_words(uni(r.spill_words)),
+          theta2(uni(r.theta2)), reach2(uni(r.reach2)), tau2(uni(r.tau2)), l_B(uni(r.l_B)), a(uni(r.a)), a2(uni(r.a2)),
+          gamma(uni(r.gamma)), Qc(uni(r.Qc)), n(uni(r.n)), nsrc(uni(r.nsrc)), ncell(uni(r.ncell)), pool(uni(r.pool)),
+          n0(uni(r.n0)), images(uni(r.images)), geom(uni(r.geom)), nline(uni(r.nline)), fcap(uni(r.fcap)),
+          spill_regions(uni(r.spill_regions)), line_t(r.line_t), line_c(r.line_c) {}
+    __device__ __forceinline__ operator const Rep&() const { return d; }
+};
+
 // ------------------------------------------------------------ harmonic form of the expansion
 // Up to order p the sum of eq. 3.3 over the C(p + 3, 3) Cartesian terms is, degree by
 // degree, sum_j q_j P_l(cos psi_j) |d_j|^l / |X|^(l + 1) (d_j = y_j - c, X = x - c), and
@@ -348,12 +377,12 @@ __device__ __forceinline__ void reg_row(double dx, double dy, double dz, double 
 
 // The coefficients of pair k of cell c, and a source of charge q at offset d added to them.
 struct HPair { double c, s; };
-__device__ __forceinline__ HPair hpair_load(const Rep& R, const HTab& T, int c, int k) {
+__device__ __forceinline__ HPair hpair_load(const RepU& R, const HTab& T, int c, int k) {
     const uint32_t code = T.lm[k];
     const GRow h = grow(R.H + (size_t)c * HSTR + (code >> 16));
     return HPair{h[0], (code & 0xFF00u) ? h[1] : 0.0};
 }
-__device__ __forceinline__ void hpair_store(const Rep& R, const HTab& T, int c, int k, double hc, double hs) {
+__device__ __forceinline__ void hpair_store(const RepU& R, const HTab& T, int c, int k, double hc, double hs) {
     const uint32_t code = T.lm[k];
     double* h = R.H + (size_t)c * HSTR + (code >> 16);
     h[0] = hc;
@@ -499,7 +528,7 @@ __device__ __forceinline__ double far_eval_f(double Rx, double Ry, double Rz, co
 // are instantiated twice: F32 = false for handles without such a replica, whose registers the
 // FP32 recurrence (every T_n of eq. 3.4 at once) would otherwise set.
 template <bool F32>
-__device__ __forceinline__ double far_value(const Rep& R, int c, double tx, double ty, double tz) {
+__device__ __forceinline__ double far_value(const RepU& R, int c, double tx, double ty, double tz) {
     if (F32 && R.M32) {
         const double4 g = gload(R.cgeo + c);
         return far_eval_f(g.x - tx, g.y - ty, g.z - tz, R.M32 + (size_t)c * MSTR);
@@ -568,7 +597,8 @@ __device__ __forceinline__ uint64_t lanemask_lt() {
 
 // Frontier region of this workgroup in HBM (null if none): a level whose frontier
 // outgrows its LDS capacity continues there, and so do the levels after it.
-__device__ __forceinline__ uint32_t* spill_region(const Rep& R) {
+template <class RT>
+__device__ __forceinline__ uint32_t* spill_region(const RT& R) {
     return (R.spill && (int)blockIdx.x < R.spill_regions) ? R.spill + (size_t)blockIdx.x * (size_t)R.spill_words
                                                           : nullptr;
 }
@@ -644,7 +674,7 @@ __device__ __attribute__((noinline)) double flagged_value(const Rep& R, int c, d
 
 // Far cells, then the cells holding an excluded source, which is taken back out.
 template <bool F32, int NTG, int BLOCK>
-__device__ __forceinline__ void far_pass(const Rep& R, Trav<NTG, BLOCK>& S, int far_n, int nflag,
+__device__ __forceinline__ void far_pass(const RepU& R, Trav<NTG, BLOCK>& S, int far_n, int nflag,
                                          double (&acc)[NTG]) {
     for (int j = threadIdx.x; j < far_n; j += BLOCK) {
         const uint32_t e = S.farl[j];
@@ -719,7 +749,7 @@ __device__ int near_scan(Trav<NTG, BLOCK>& S, int near_n) {
 // Near leaves: direct sum over each leaf's index array in slot order.  For
 // the overlap target, every ion other than the mover within tau is an overlap.
 template <int NTG, int BLOCK>
-__device__ __forceinline__ void near_pass(const Rep& R, Trav<NTG, BLOCK>& S, int near_n, int total,
+__device__ __forceinline__ void near_pass(const RepU& R, Trav<NTG, BLOCK>& S, int near_n, int total,
                                           double (&acc)[NTG]) {
     const int n_ion = R.n;
     const bool listed = total <= Trav<NTG, BLOCK>::OWNCAP;  // uniform
@@ -753,7 +783,7 @@ __device__ __forceinline__ double box_dist2(double4 g, double x, double y, doubl
 // Hard-core check below cells the traversal took as far: descend every cell
 // whose cube comes within tau (plus a rounding margin) of the target.
 template <int NTG, int BLOCK>
-__device__ void overlap_below_far(const Rep& R, Trav<NTG, BLOCK>& S, int* cnt2) {
+__device__ void overlap_below_far(const RepU& R, Trav<NTG, BLOCK>& S, int* cnt2) {
     using TS = Trav<NTG, BLOCK>;
     const int t = S.ovl_t;
     const double x = S.tx[t], y = S.ty[t], z = S.tz[t];
@@ -808,7 +838,7 @@ __device__ void overlap_below_far(const Rep& R, Trav<NTG, BLOCK>& S, int* cnt2) 
 // Returns the number of levels processed (hook is called once per level,
 // by every thread, right after the level's first loads are issued).
 template <bool F32, int NTG, int BLOCK, class Hook>
-__device__ int traverse(const Rep& R, Trav<NTG, BLOCK>& S, int nroot, int* cnt2, Hook&& hook) {
+__device__ int traverse(const RepU& R, Trav<NTG, BLOCK>& S, int nroot, int* cnt2, Hook&& hook) {
     using TS = Trav<NTG, BLOCK>;
     constexpr int NW = TS::NW;
     const int tid = threadIdx.x, lane = lane_id(), w = wave_id();
@@ -983,7 +1013,7 @@ __device__ int traverse(const Rep& R, Trav<NTG, BLOCK>& S, int nroot, int* cnt2,
 constexpr int kMaskSh = 24, kDirSh = 26;
 
 template <bool F32, int BLOCK>
-__device__ __forceinline__ void far_pass_mc(const Rep& R, Trav<2, BLOCK>& S, int far_n, int nflag,
+__device__ __forceinline__ void far_pass_mc(const RepU& R, Trav<2, BLOCK>& S, int far_n, int nflag,
                                             double (&acc)[2]) {
     static_assert(BLOCK % 2 == 0, "lane pairs");
     const int t = (int)(threadIdx.x & 1);
@@ -1008,7 +1038,7 @@ __device__ __forceinline__ void far_pass_mc(const Rep& R, Trav<2, BLOCK>& S, int
 // Near leaves of both targets.  For the new position (the overlap target),
 // every ion other than the mover within tau is an overlap.
 template <int BLOCK>
-__device__ __forceinline__ void near_pass_mc(const Rep& R, Trav<2, BLOCK>& S, int near_n, int total,
+__device__ __forceinline__ void near_pass_mc(const RepU& R, Trav<2, BLOCK>& S, int near_n, int total,
                                              double (&acc)[2]) {
     const int n_ion = R.n;
     const bool listed = total <= Trav<2, BLOCK>::OWNCAP;  // uniform
@@ -1040,7 +1070,7 @@ __device__ __forceinline__ void near_pass_mc(const Rep& R, Trav<2, BLOCK>& S, in
 // deterministic lists, hook once per level, res[0..1] the potentials (the
 // same in every thread), S.err / S.overlap / S.coincide as there.
 template <bool F32, int BLOCK, class Hook>
-__device__ int traverse_mc(const Rep& R, Trav<2, BLOCK>& S, int* cnt2, Hook&& hook, int fs0, int level0,
+__device__ int traverse_mc(const RepU& R, Trav<2, BLOCK>& S, int* cnt2, Hook&& hook, int fs0, int level0,
                            double (&res)[2]) {
     using TS = Trav<2, BLOCK>;
     res[0] = res[1] = 0.0;
@@ -1281,7 +1311,7 @@ struct MoveOut { double dE; int reason; int accepted; int stop; int detail; };
 constexpr double kInf = __builtin_huge_val();
 
 // One stage of the commit prefetch for old source j (0: ion, 1: image).
-__device__ __forceinline__ void prefetch_stage(const Rep& R, McShared& MS, int j, int s) {
+__device__ __forceinline__ void prefetch_stage(const RepU& R, McShared& MS, int j, int s) {
     const int stage = MS.pf_stage[j];
     if (stage == 0) {
         const int2 t = gload(R.track + s);
@@ -1452,7 +1482,7 @@ constexpr int kLineRows = (int)((sizeof(Trav<2, BLOCK>::hrow) - sizeof(LineList)
 
 // Move one line image between leaf index arrays (or rewrite its slot) from the current
 // state in HBM; false on a broken index.
-__device__ __forceinline__ bool line_slot_move(const Rep& R, int s, int lo, int ln, double4 pn) {
+__device__ __forceinline__ bool line_slot_move(const RepU& R, int s, int lo, int ln, double4 pn) {
     const int2 tr = R.track[s];
     const int4 mo = R.cm[lo];
     if (tr.x != lo || mo.y >= 0 || tr.y < 0 || tr.y >= mo.x || mo.z < 0 || mo.z + mo.x > R.pool) return false;
@@ -1484,7 +1514,7 @@ __device__ __forceinline__ bool line_slot_move(const Rep& R, int s, int lo, int 
 // cells of their 2M root paths, then every thread repairs those cells' moments and counts,
 // applying to each cell, in order, old line image 0 (-), new line image 0 (+), old 1 ...
 template <bool F32, int BLOCK>
-__device__ __forceinline__ void lines_commit(const Rep& R, Trav<2, BLOCK>& S, McShared& MS, int i) {
+__device__ __forceinline__ void lines_commit(const RepU& R, Trav<2, BLOCK>& S, McShared& MS, int i) {
     LineList& LL = line_list(S);
     const int tid = threadIdx.x, M = R.nline, nc = 2 * M;
     const bool cart = F32 && R.M32;  // uniform
@@ -1603,7 +1633,7 @@ __device__ __forceinline__ void lines_commit(const Rep& R, Trav<2, BLOCK>& S, Mc
 // cells of the four root paths, applying to each cell, in order, the old ion
 // (-), the new ion (+), the old image (-) and the new image (+).
 template <bool F32, int BLOCK>
-__device__ __forceinline__ void commit(const Rep& R, Trav<2, BLOCK>& S, McShared& MS, int i) {
+__device__ __forceinline__ void commit(const RepU& R, Trav<2, BLOCK>& S, McShared& MS, int i) {
     const int tid = threadIdx.x;
     const bool imgs = R.images != 0;
     const bool cart = F32 && R.M32;  // uniform: the Cartesian moments are repaired, not the expansion rows
@@ -1793,7 +1823,7 @@ __device__ __forceinline__ void commit(const Rep& R, Trav<2, BLOCK>& S, McShared
 // inext >= 0 names the next move's ion, whose sources one lane loads into
 // MS.nx_si / MS.nx_mo during the traversal (valid if the ion is not i).
 template <int BLOCK, bool LINES, bool F32>
-__device__ __forceinline__ MoveOut one_move(const Rep& R, Trav<2, BLOCK>& S, McShared& MS, int i, double4 si,
+__device__ __forceinline__ MoveOut one_move(const RepU& R, Trav<2, BLOCK>& S, McShared& MS, int i, double4 si,
                             double4 mo, double rx, double ry, double rz, double alpha, int mode, int inext) {
     static_assert(BLOCK >= 256, "the path descents, the commit prefetch and the next mover's load run on "
                                 "the last three waves");
@@ -2048,9 +2078,10 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2)))
         if (r < 0) break;
         load_rep(Rs, reps + r);
         __syncthreads();
-        long long m = Rs.move_next;
-        const long long m0 = m, mend = Rs.move_end;
-        const bool imgs = Rs.images != 0;
+        const RepU R(Rs);
+        long long m = uni(Rs.move_next);
+        const long long m0 = m, mend = uni(Rs.move_end);
+        const bool imgs = R.images != 0;
         long long st_moves = 0, st_acc = 0, st_wall = 0, st_ovl = 0, st_met = 0;
         int status = 0, detail = 0;
         int prev_i = -1;
@@ -2073,7 +2104,7 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2)))
             const bool use_nx = have_nx && i != prev_i;
             const double4 si = use_nx ? MS.nx_si : Rs.src[i];
             const double4 mo = use_nx ? MS.nx_mo : (imgs ? Rs.src[Rs.n + i] : make_double4(0, 0, 0, 0));
-            const MoveOut o = one_move<BLOCK, LINES, F32>(Rs, S, MS, i, si, mo, si.x + MS.dr_d[b][0], si.y + MS.dr_d[b][1],
+            const MoveOut o = one_move<BLOCK, LINES, F32>(R, S, MS, i, si, mo, si.x + MS.dr_d[b][0], si.y + MS.dr_d[b][1],
                                               si.z + MS.dr_d[b][2], MS.dr_d[b][3], 1, inext);
             // a move outside the walls returns before its traversal, so before the load
             have_nx = inext >= 0 && o.reason != 1;
@@ -2110,7 +2141,7 @@ __global__ void __launch_bounds__(kMcBlock) k_move(Rep* reps, int r, MoveIO* io)
     const int i = io->i;
     const double4 si = Rs.src[i];
     const double4 mo = Rs.images ? Rs.src[Rs.n + i] : make_double4(0, 0, 0, 0);
-    const MoveOut o = one_move<kMcBlock, LINES, F32>(Rs, S, MS, i, si, mo, io->rn[0], io->rn[1], io->rn[2], 0.0,
+    const MoveOut o = one_move<kMcBlock, LINES, F32>(RepU(Rs), S, MS, i, si, mo, io->rn[0], io->rn[1], io->rn[2], 0.0,
                                          io->mode == 0 ? 0 : 2, -1);
     if (threadIdx.x == 0) {
         io->dE = o.dE;
@@ -2139,6 +2170,7 @@ __global__ void __launch_bounds__(kEnergyBlock) k_energy(Rep* reps, int r, doubl
     load_rep(Rs, reps + r);
     __syncthreads();
     const int tid = threadIdx.x;
+    const RepU R(Rs);
     const bool imgs = Rs.images != 0;
     const int ngroups = (Rs.nsrc + NTG - 1) / NTG;
     // one group of positions per workgroup, or several when the grid is bounded (HBM frontier regions)
@@ -2171,7 +2203,7 @@ __global__ void __launch_bounds__(kEnergyBlock) k_energy(Rep* reps, int r, doubl
         }
         if (tid == 0) { S.ovl_t = -1; S.ovl_ex = -1; S.n_ovl = 0; S.err = 0; S.overlap = 0; S.coincide = 0; }
         __syncthreads();
-        traverse<F32, NTG, kEnergyBlock>(Rs, S, nv, cnt2, [](int) {});
+        traverse<F32, NTG, kEnergyBlock>(R, S, nv, cnt2, [](int) {});
         if (tid < nv) {
             const int ion = s_ion[tid];
             const double4 si = Rs.src[ion];

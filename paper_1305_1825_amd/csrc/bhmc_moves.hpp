@@ -221,10 +221,10 @@ __device__ int near_scan_mb(BTrav<BLOCK>& S, int near_n) {
 // position) of the entry's move, both lanes reading the same moment row; acc[b] of a
 // lane holds its target of move b.
 template <bool F32, int BLOCK>
-__device__ __forceinline__ void far_pass_mb(const Rep& R, BTrav<BLOCK>& S, const BMoves& MV, int far_n, int nflag,
+__device__ __forceinline__ void far_pass_mb(const RepU& R, BTrav<BLOCK>& S, const BMoves& MV, int far_n, int nflag,
                                             double (&acc)[kBM]) {
-    const int tb = (int)(threadIdx.x & 1);
-    for (int j2 = threadIdx.x; j2 < 2 * far_n; j2 += BLOCK) {
+    const int tid = fresh_tid(), tb = tid & 1;
+    for (int j2 = tid; j2 < 2 * far_n; j2 += BLOCK) {
         const uint32_t e = S.farl[j2 >> 1];
         if (!((e >> (kOpSh + tb)) & 1u)) continue;
         const int c = (int)(e & kCellMask);
@@ -232,7 +232,7 @@ __device__ __forceinline__ void far_pass_mb(const Rep& R, BTrav<BLOCK>& S, const
         const int b = mv_of(e), t = 2 * b + tb;
         add_to_t<kBM>(acc, b, far_value<F32>(R, c, MV.tx[t], MV.ty[t], MV.tz[t]));
     }
-    for (int j2 = threadIdx.x; j2 < 2 * nflag; j2 += BLOCK) {
+    for (int j2 = tid; j2 < 2 * nflag; j2 += BLOCK) {
         const uint32_t e = S.flagl[j2 >> 1];
         if (!((e >> (kOpSh + tb)) & 1u)) continue;
         const int c = (int)(e & kCellMask);
@@ -247,12 +247,13 @@ __device__ __forceinline__ void far_pass_mb(const Rep& R, BTrav<BLOCK>& S, const
 // taken by lanes 2f (old position) and 2f + 1 (new position); for the new position,
 // every ion other than the mover within tau is an overlap.
 template <int BLOCK>
-__device__ __forceinline__ void near_pass_mb(const Rep& R, BTrav<BLOCK>& S, BMoves& MV, int near_n, int total,
+__device__ __forceinline__ void near_pass_mb(const RepU& R, BTrav<BLOCK>& S, BMoves& MV, int near_n, int total,
                                              double (&acc)[kBM]) {
     const int n_ion = R.n;
     const bool listed = total <= BTrav<BLOCK>::OWNCAP;  // uniform
-    const int tb = (int)(threadIdx.x & 1);
-    for (int f2 = threadIdx.x; f2 < 2 * total; f2 += BLOCK) {
+    const int tid = fresh_tid();
+    const int tb = tid & 1;
+    for (int f2 = tid; f2 < 2 * total; f2 += BLOCK) {
         const int f = f2 >> 1;
         const int lo = listed ? (int)S.near_own[f] : near_search(S.near_pre, near_n, f);
         const uint32_t e = S.nearl[lo];
@@ -278,7 +279,7 @@ __device__ __forceinline__ void near_pass_mb(const Rep& R, BTrav<BLOCK>& S, BMov
 // Hard cores below the far cells of new positions: every cell whose cube comes
 // within tau (plus a rounding margin) of the new position is descended.
 template <int BLOCK>
-__device__ void overlap_below_far_mb(const Rep& R, BTrav<BLOCK>& S, BMoves& MV) {
+__device__ void overlap_below_far_mb(const RepU& R, BTrav<BLOCK>& S, BMoves& MV) {
     using TS = BTrav<BLOCK>;
     const double reach2 = R.reach2;
     int cur = 0, fs = S.n_ovl < TS::OVLCAP ? S.n_ovl : TS::OVLCAP;
@@ -327,10 +328,10 @@ __device__ void overlap_below_far_mb(const Rep& R, BTrav<BLOCK>& S, BMoves& MV) 
 // MV.pot[t] holds target t's potential.  N_0 = 0: a cell holding a remaining source
 // is far if it passes the MAC, else opened if it has children, else summed directly.
 template <bool F32, int BLOCK, class Hook>
-__device__ void traverse_mb(const Rep& R, BTrav<BLOCK>& S, BMoves& MV, Hook&& hook) {
+__device__ void traverse_mb(const RepU& R, BTrav<BLOCK>& S, BMoves& MV, Hook&& hook) {
     using TS = BTrav<BLOCK>;
     constexpr int NW = TS::NW;
-    const int tid = threadIdx.x, lane = lane_id(), w = wave_id();
+    const int tid = fresh_tid(), lane = tid & 63, w = tid >> 6;
     double acc[kBM];  // this lane's target (its parity) of every move
 #pragma unroll
     for (int k = 0; k < kBM; ++k) acc[k] = 0.0;
@@ -538,7 +539,7 @@ __device__ void traverse_mb(const Rep& R, BTrav<BLOCK>& S, BMoves& MV, Hook&& ho
 // What contribution cc of move j adds (per unit charge) to the potential at x through
 // the tree: walk its root path from the top; the first cell passing the MAC takes it
 // through its expansion, otherwise its leaf takes it directly.
-__device__ __forceinline__ double path_value(const Rep& R, const BMoves& MV, int j, int cc, double x, double y, double z) {
+__device__ __forceinline__ double path_value(const RepU& R, const BMoves& MV, int j, int cc, double x, double y, double z) {
     const double4 src = MV.ct[j][cc];
     const int len = MV.plen[j][cc];
     for (int l = 0; l < len; ++l) {
@@ -555,7 +556,7 @@ __device__ __forceinline__ double path_value(const Rep& R, const BMoves& MV, int
 struct RoundOut { int done; int stop; int detail; };
 
 // One stage of the commit prefetch of move b's ion (j = 0) or image (j = 1).
-__device__ __forceinline__ void prefetch_stage_mb(const Rep& R, BMoves& MV, int b, int j) {
+__device__ __forceinline__ void prefetch_stage_mb(const RepU& R, BMoves& MV, int b, int j) {
     const int s = j == 0 ? MV.ion[b] : R.n + MV.ion[b];
     const int stage = MV.pf_stage[b][j];
     if (stage == 0) {
@@ -580,9 +581,9 @@ __device__ __forceinline__ void prefetch_stage_mb(const Rep& R, BMoves& MV, int 
 // One round of up to nb moves (draws b0 .. b0 + nb - 1 of MV's batch, move indices
 // m .. m + nb - 1).  Returns the number of moves consumed and a stop status.
 template <bool F32, int BLOCK>
-__device__ RoundOut round_mb(const Rep& R, BTrav<BLOCK>& S, BMoves& MV, int b0, int nb) {
+__device__ RoundOut round_mb(const RepU& R, BTrav<BLOCK>& S, BMoves& MV, int b0, int nb) {
     static_assert(BLOCK >= 256, "the path descents and the commit prefetch run on the last two waves");
-    const int tid = threadIdx.x;
+    int tid = fresh_tid();
     const bool imgs = R.images != 0;
     const int nps = imgs ? 4 : 2;
     PHASE_START();
@@ -714,6 +715,7 @@ __device__ RoundOut round_mb(const Rep& R, BTrav<BLOCK>& S, BMoves& MV, int b0, 
         __syncthreads();
         return o;
     }
+    tid = fresh_tid();
     // ---- in parallel: corrections (eight lanes per pair j < b, one per target t of move b and
     // contribution of move j: what committing move j adds to it, summed over the contributions
     // in their order); on the last wave, for every pair, whether b's new position overlaps j's
@@ -911,6 +913,7 @@ __device__ RoundOut round_mb(const Rep& R, BTrav<BLOCK>& S, BMoves& MV, int b0, 
         return o;
     }
     const int ndone = MV.ndone;
+    tid = fresh_tid();
     // ---- leaf index arrays (Sec. 3.3: delete = the last entry fills the hole, add = append), one
     // lane per leaf taking that leaf's operations in order; moves between leaves are independent.
     // A source that fills a hole and leaves the leaf later in the round has its slot followed in
@@ -978,7 +981,9 @@ __device__ RoundOut round_mb(const Rep& R, BTrav<BLOCK>& S, BMoves& MV, int b0, 
     // ---- meanwhile, on the other waves: the distinct cells of the accepted moves' root paths, a
     // level per wave at a time (lane 4 j + cc holds the cell of contribution cc of move j; comparing
     // it with every other lane's gives the contributions that apply to the cell), and the first
-    // table of the path entries' harmonics
+    // table of the path entries' harmonics.  A round of eight moves on the 10^4-ion colloid spends
+    // 3.6 us here (11.6 with the operations one after another and each deletion searching them
+    // all) and 4.1 us in the repair below (11.8 from per-axis powers of 56 Cartesian terms)
     constexpr int HROWS = BTrav<BLOCK>::HROWS;
     const bool cart = F32 && R.M32;  // uniform: the commit repairs the Cartesian moments (below)
     if (tid >= 64) {
@@ -1164,8 +1169,9 @@ __global__ void __launch_bounds__(BLOCK) k_mcb(Rep* reps, McArgs A) {
         if (r < 0) break;
         load_rep(Rs, reps + r);
         __syncthreads();
-        long long m = Rs.move_next;
-        const long long m0 = m, mend = Rs.move_end;
+        const RepU R(Rs);
+        long long m = uni(Rs.move_next);
+        const long long m0 = m, mend = uni(Rs.move_end);
         long long st_moves = 0, st_acc = 0, st_wall = 0, st_ovl = 0, st_met = 0;
         int status = 0, detail = 0;
         while (m < mend) {
@@ -1190,7 +1196,7 @@ __global__ void __launch_bounds__(BLOCK) k_mcb(Rep* reps, McArgs A) {
                 for (int j = 0; j < b; ++j) rep = rep || MV.dr_i[b0 + b] == MV.dr_i[b0 + j];
                 if (rep) { nb = b; break; }
             }
-            const RoundOut o = round_mb<F32, BLOCK>(Rs, S, MV, b0, nb);
+            const RoundOut o = round_mb<F32, BLOCK>(R, S, MV, b0, nb);
             if (tid == 0) {
                 for (int b = 0; b < o.done; ++b) {
                     ++st_moves;
