@@ -253,42 +253,53 @@ __device__ __forceinline__ void far_column(const double (&h)[N], int base, doubl
     }
 }
 
-template <int M, int LAST, int N>
-__device__ __forceinline__ void far_columns(const double (&h)[N], int base, double u, double w, double zx, double zy,
-                                            double& a, double& b) {
+// One target's place in a cell's expansion, and its sum so far.
+struct FarAt { double u, w, zx, zy, ir, a, b; };
+__device__ __forceinline__ void far_at(FarAt& f, double x, double y, double z) {
+    const double r2 = x * x + y * y + z * z;
+    f.ir = rsqrt_nr(r2);
+    f.w = f.ir * f.ir; f.u = z * f.w; f.zx = x * f.w; f.zy = y * f.w;
+    f.a = 0.0; f.b = 0.0;
+}
+
+template <int M, int LAST, int NT, int N>
+__device__ __forceinline__ void far_columns(const double (&h)[N], int base, FarAt (&f)[NT]) {
     if constexpr (M >= LAST) {
-        double qc, qs;
-        far_column<M>(h, base, u, w, qc, qs);
-        if constexpr (M == P) {
-            a = qc; b = qs;
-        } else {
-            const double ta = fma(b, zy, fma(a, zx, qc));
-            if constexpr (M > 0) b = fma(b, zx, fma(-a, zy, qs));
-            a = ta;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            double qc, qs;
+            far_column<M>(h, base, f[t].u, f[t].w, qc, qs);
+            if constexpr (M == P) {
+                f[t].a = qc; f[t].b = qs;
+            } else {
+                const double ta = fma(f[t].b, f[t].zy, fma(f[t].a, f[t].zx, qc));
+                if constexpr (M > 0) f[t].b = fma(f[t].b, f[t].zx, fma(-f[t].a, f[t].zy, qs));
+                f[t].a = ta;
+            }
         }
         __builtin_amdgcn_sched_barrier(0);
-        far_columns<M - 1, LAST>(h, base, u, w, zx, zy, a, b);
+        far_columns<M - 1, LAST>(h, base, f);
     }
 }
 
-// Value at (tx, ty, tz) of an expansion row, its own centre included.
-template <class HP>
-__device__ __forceinline__ double far_row(HP __restrict__ H, double tx, double ty, double tz) {
+// Values at NT targets of an expansion row, its own centre included; the row is read once.
+template <int NT, class HP>
+__device__ __forceinline__ void far_rows(HP __restrict__ H, const double (&tx)[NT], const double (&ty)[NT],
+                                         const double (&tz)[NT], double (&v)[NT]) {
     // the columns of the first run take places 0 .. n1 - 1 (m = 1 .. p lie in this order in the
     // row, so a first run of the columns m >= kHSplit is the tail of the pairs)
     constexpr int lo = kHSplit ? hplace(kHSplit, kHSplit) : 0;         // first place of the first run
     constexpr int n1 = (kHSplit ? NH - (P + 1) : NH) - lo;
-    const double x = tx - H[HCEN], y = ty - H[HCEN + 1], z = tz - H[HCEN + 2];
-    double a = 0.0, b = 0.0, u, w, zx, zy, ir;
+    const double cx = H[HCEN], cy = H[HCEN + 1], cz = H[HCEN + 2];
+    FarAt f[NT];
     {
         double h[n1];
 #pragma unroll
         for (int k = 0; k < n1; ++k) h[k] = H[lo + k];
-        const double r2 = x * x + y * y + z * z;
-        ir = rsqrt_nr(r2);
-        w = ir * ir; u = z * w; zx = x * w; zy = y * w;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) far_at(f[t], tx[t] - cx, ty[t] - cy, tz[t] - cz);
         __builtin_amdgcn_sched_barrier(0);
-        far_columns<P, kHSplit>(h, lo, u, w, zx, zy, a, b);
+        far_columns<P, kHSplit>(h, lo, f);
     }
     if constexpr (kHSplit > 0) {
         // the columns below the split: their pairs at places 0 .. lo - 1, then those of m = 0
@@ -298,9 +309,17 @@ __device__ __forceinline__ double far_row(HP __restrict__ H, double tx, double t
 #pragma unroll
         for (int k = NH - (P + 1); k < NH; ++k) h[k] = H[k];
         __builtin_amdgcn_sched_barrier(0);
-        far_columns<kHSplit - 1, 0>(h, 0, u, w, zx, zy, a, b);
+        far_columns<kHSplit - 1, 0>(h, 0, f);
     }
-    return ir * a;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) v[t] = f[t].ir * f[t].a;
+}
+template <class HP>
+__device__ __forceinline__ double far_row(HP H, double tx, double ty, double tz) {
+    const double x[1] = {tx}, y[1] = {ty}, z[1] = {tz};
+    double v[1];
+    far_rows<1>(H, x, y, z, v);
+    return v[0];
 }
 
 // Tables of the regular harmonics for terms picked at run time, copied to LDS: beta_lm
@@ -535,6 +554,19 @@ __device__ __forceinline__ double far_value(const RepU& R, int c, double tx, dou
     }
     return far_row(grow(R.H + (size_t)c * HSTR), tx, ty, tz);
 }
+// The same at the two targets of a move.
+template <bool F32>
+__device__ __forceinline__ void far_value2(const RepU& R, int c, const double (&tx)[2], const double (&ty)[2],
+                                           const double (&tz)[2], double (&v)[2]) {
+    if (F32 && R.M32) {
+        const double4 g = gload(R.cgeo + c);
+        v[0] = far_eval_f(g.x - tx[0], g.y - ty[0], g.z - tz[0], R.M32 + (size_t)c * MSTR);
+        __builtin_amdgcn_sched_barrier(0);  // one recurrence's T_n in registers at a time
+        v[1] = far_eval_f(g.x - tx[1], g.y - ty[1], g.z - tz[1], R.M32 + (size_t)c * MSTR);
+        return;
+    }
+    far_rows<2>(grow(R.H + (size_t)c * HSTR), tx, ty, tz, v);
+}
 
 // Polynomial sum_n C_n d^n and its gradient sum_n C_n n_k d^{n - e_k} for
 // stored coefficients C; the monomials d^n are built by the graded
@@ -582,6 +614,43 @@ __device__ __forceinline__ double point_expansion(double Rx, double Ry, double R
     return v;
 }
 
+// A double read from another lane of the same 16-lane row by a DPP control
+// (two 32-bit moves), no memory traffic; every control used here has a source
+// lane inside the row for every lane.
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_mov_dpp((int)b, CTRL, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xF, 0xF, true);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
+// Reduce-scatter over the 16 lanes of a row: before, every lane holds x[0..15];
+// after, x[0] of lane l holds the row's sum of x[i(l)], with
+// i(l) = b3 << 3 | (b0 ^ b2) << 2 | (b1 ^ b2) << 1 | b2 for the bits b_j of l in
+// its row.  Four exchange stages with the partners l ^ 8, l ^ 1, l ^ 2 and
+// l ^ 7 (DPP row_ror:8, two quad permutations, row_half_mirror); at each stage
+// a lane keeps the half of its values that its partner does not keep and adds
+// the partner's copy of that half.  15 exchanges instead of the 64 of sixteen
+// row sums, and every lane ends with a distinct index.
+template <int CTRL, int M>
+__device__ __forceinline__ void rs_stage(double (&x)[16], bool up) {
+#pragma unroll
+    for (int j = 0; j < M / 2; ++j) {
+        const double lo = x[j], hi = x[j + M / 2];
+        x[j] = (up ? hi : lo) + dpp_f64<CTRL>(up ? lo : hi);
+    }
+}
+__device__ __forceinline__ int rs_index(int l) {
+    return (((l >> 3) & 1) << 3) | (((l ^ (l >> 2)) & 1) << 2) | ((((l >> 1) ^ (l >> 2)) & 1) << 1) | ((l >> 2) & 1);
+}
+__device__ __forceinline__ double row_reduce_scatter16(double (&x)[16], int l) {
+    rs_stage<0x128, 16>(x, (l >> 3) & 1);
+    rs_stage<0xB1, 8>(x, (l ^ (l >> 2)) & 1);
+    rs_stage<0x4E, 4>(x, ((l >> 1) ^ (l >> 2)) & 1);
+    rs_stage<0x141, 2>(x, (l >> 2) & 1);
+    return x[0];
+}
 // ------------------------------------------------------------ traversal state
 constexpr uint32_t kCellMask = 0xFFFFFFu;
 constexpr uint32_t kFlagIon = 1u << 28, kFlagImg = 1u << 29, kFlagDirect = 1u << 30;
@@ -1007,24 +1076,26 @@ __device__ int traverse(const RepU& R, Trav<NTG, BLOCK>& S, int nroot, int* cnt2
 // mask of the targets for which it is still open (bits 24-25), a 2-bit mask of
 // the targets summing every source below it directly by the N_0 rule (bits
 // 26-27) and the two exclusion flags.  Each target takes exactly the decisions
-// of its own traversal.  Far cells are evaluated by lane pairs (lane 2j the
-// old position, 2j+1 the new one) reading the same moment row; near sources by
-// lanes that load a source once and evaluate both targets against it.
+// of its own traversal.  A lane reads a far cell's row once and evaluates both
+// targets from it (the rows' way through the CU's L1, 64 B a clock, is what
+// bounds the far cells), and likewise near sources.
 constexpr int kMaskSh = 24, kDirSh = 26;
 
 template <bool F32, int BLOCK>
 __device__ __forceinline__ void far_pass_mc(const RepU& R, Trav<2, BLOCK>& S, int far_n, int nflag,
                                             double (&acc)[2]) {
-    static_assert(BLOCK % 2 == 0, "lane pairs");
-    const int t = (int)(threadIdx.x & 1);
-    for (int j2 = threadIdx.x; j2 < 2 * far_n; j2 += BLOCK) {
-        const uint32_t e = S.farl[j2 >> 1];
-        if (!((e >> (kMaskSh + t)) & 1u)) continue;
+    for (int j = threadIdx.x; j < far_n; j += BLOCK) {
+        const uint32_t e = S.farl[j];
         const int c = (int)(e & kCellMask);
         if (c >= R.ncell) { S.err = kErrFarCell; continue; }
-        add_to<2>(acc, t, far_value<F32>(R, c, S.tx[t], S.ty[t], S.tz[t]));
+        const double tx[2] = {S.tx[0], S.tx[1]}, ty[2] = {S.ty[0], S.ty[1]}, tz[2] = {S.tz[0], S.tz[1]};
+        double v[2];
+        far_value2<F32>(R, c, tx, ty, tz, v);
+        acc[0] += ((e >> kMaskSh) & 1u) ? v[0] : 0.0;
+        acc[1] += ((e >> kMaskSh) & 2u) ? v[1] : 0.0;
     }
-    // the cells holding an excluded source, less what it adds
+    // the cells holding an excluded source, less what it adds: a lane per target
+    const int t = (int)(threadIdx.x & 1);
     for (int j2 = threadIdx.x; j2 < 2 * nflag; j2 += BLOCK) {
         const uint32_t e = S.flagl[j2 >> 1];
         if (!((e >> (kMaskSh + t)) & 1u)) continue;
@@ -2268,43 +2339,6 @@ struct GradShared {
     int err;
 };
 
-// A double read from another lane of the same 16-lane row by a DPP control
-// (two 32-bit moves), no memory traffic; every control used here has a source
-// lane inside the row for every lane.
-template <int CTRL>
-__device__ __forceinline__ double dpp_f64(double v) {
-    const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_mov_dpp((int)b, CTRL, 0xF, 0xF, true);
-    const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xF, 0xF, true);
-    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-
-// Reduce-scatter over the 16 lanes of a row: before, every lane holds x[0..15];
-// after, x[0] of lane l holds the row's sum of x[i(l)], with
-// i(l) = b3 << 3 | (b0 ^ b2) << 2 | (b1 ^ b2) << 1 | b2 for the bits b_j of l in
-// its row.  Four exchange stages with the partners l ^ 8, l ^ 1, l ^ 2 and
-// l ^ 7 (DPP row_ror:8, two quad permutations, row_half_mirror); at each stage
-// a lane keeps the half of its values that its partner does not keep and adds
-// the partner's copy of that half.  15 exchanges instead of the 64 of sixteen
-// row sums, and every lane ends with a distinct index.
-template <int CTRL, int M>
-__device__ __forceinline__ void rs_stage(double (&x)[16], bool up) {
-#pragma unroll
-    for (int j = 0; j < M / 2; ++j) {
-        const double lo = x[j], hi = x[j + M / 2];
-        x[j] = (up ? hi : lo) + dpp_f64<CTRL>(up ? lo : hi);
-    }
-}
-__device__ __forceinline__ int rs_index(int l) {
-    return (((l >> 3) & 1) << 3) | (((l ^ (l >> 2)) & 1) << 2) | ((((l >> 1) ^ (l >> 2)) & 1) << 1) | ((l >> 2) & 1);
-}
-__device__ __forceinline__ double row_reduce_scatter16(double (&x)[16], int l) {
-    rs_stage<0x128, 16>(x, (l >> 3) & 1);
-    rs_stage<0xB1, 8>(x, (l ^ (l >> 2)) & 1);
-    rs_stage<0x4E, 4>(x, ((l >> 1) ^ (l >> 2)) & 1);
-    rs_stage<0x141, 2>(x, (l >> 2) & 1);
-    return x[0];
-}
 // Row sums of four values by the first two stages above and two plain sums:
 // every lane gets the sum of value b3 << 1 | (b0 ^ b2), so lanes 0, 1, 8 and 9
 // of the row hold the sums of a, b, c and d.

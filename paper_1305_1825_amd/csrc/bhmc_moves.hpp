@@ -34,7 +34,7 @@ constexpr uint32_t kMbIon = 1u << 29, kMbImg = 1u << 30;
 constexpr int kPathCells = kBM * 4 * kMaxLevels;
 constexpr int kChunk = 2;  // frontier entries per lane per chunk of the traversal's level loop
 
-static_assert(kBM <= 8, "the move index has three bits");
+static_assert(kBM <= 8, "the move index has three bits, and a round at most 16 targets");
 
 // Phase timers of a round (built with -DBHMC_PHASE_TIMERS only): thread 0 adds the
 // constant-clock ticks of each phase, and the level loop its counts, to the workgroup's
@@ -94,7 +94,7 @@ struct BTrav {
     uint32_t ovl[OVLCAP];
     int n_ovl, near_tot, err;
     uint64_t wcnt[2][kChunk][NW];
-    double red[NW][kBT];
+    double red[4 * NW][kBT];
     uint32_t mi[NTERM];
     HTab ht;
     int cnt2[2];
@@ -156,20 +156,12 @@ struct BMoves {
 
 __device__ __forceinline__ int mv_of(uint32_t e) { return (int)((e >> kMvSh) & 7u); }
 
-template <int NT>
-__device__ __forceinline__ void add_to_t(double (&acc)[NT], int t, double v) {
+__device__ __forceinline__ void add_pair(double (&acc)[kBT], int b, double v0, double v1) {
 #pragma unroll
-    for (int k = 0; k < NT; ++k)
-        if (k == t) acc[k] += v;
-}
-
-// Sum over the lanes of a wave with the same parity as this one: a lane of parity tb
-// accumulates target tb of every move (see far_pass_mb), so lanes 0 and 1 end with the
-// wave's sums for the old and the new positions.
-__device__ __forceinline__ double wave_sum_parity(double v) {
-#pragma unroll
-    for (int off = 32; off >= 2; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
+    for (int k = 0; k < kBM; ++k) {
+        acc[2 * k] += k == b ? v0 : 0.0;
+        acc[2 * k + 1] += k == b ? v1 : 0.0;
+    }
 }
 
 // An overlap of move b's new position with source sid (an ion other than the mover,
@@ -217,62 +209,65 @@ __device__ int near_scan_mb(BTrav<BLOCK>& S, int near_n) {
     return carry;
 }
 
-// Far cells by lane pairs: the lane of parity tb evaluates target tb (old or new
-// position) of the entry's move, both lanes reading the same moment row; acc[b] of a
-// lane holds its target of move b.
+// Far cells, a lane per entry: the row is read once and evaluated at both targets of the
+// entry's move; acc[2b + t] of a lane holds its sum for target t of move b.  (Lane pairs
+// reading the same row, one target each, are bound by the rows' way through the CU's L1.)
 template <bool F32, int BLOCK>
 __device__ __forceinline__ void far_pass_mb(const RepU& R, BTrav<BLOCK>& S, const BMoves& MV, int far_n, int nflag,
-                                            double (&acc)[kBM]) {
-    const int tid = fresh_tid(), tb = tid & 1;
-    for (int j2 = tid; j2 < 2 * far_n; j2 += BLOCK) {
-        const uint32_t e = S.farl[j2 >> 1];
-        if (!((e >> (kOpSh + tb)) & 1u)) continue;
-        const int c = (int)(e & kCellMask);
+                                            double (&acc)[kBT]) {
+    const int tid = fresh_tid();
+    for (int j = tid; j < far_n; j += BLOCK) {
+        const uint32_t e = S.farl[j];
+        const int c = (int)(e & kCellMask), b = mv_of(e);
         if (c >= R.ncell) { S.err = kErrFarCell; continue; }
-        const int b = mv_of(e), t = 2 * b + tb;
-        add_to_t<kBM>(acc, b, far_value<F32>(R, c, MV.tx[t], MV.ty[t], MV.tz[t]));
+        const double tx[2] = {MV.tx[2 * b], MV.tx[2 * b + 1]}, ty[2] = {MV.ty[2 * b], MV.ty[2 * b + 1]};
+        const double tz[2] = {MV.tz[2 * b], MV.tz[2 * b + 1]};
+        double v[2];
+        far_value2<F32>(R, c, tx, ty, tz, v);
+        add_pair(acc, b, ((e >> kOpSh) & 1u) ? v[0] : 0.0, ((e >> kOpSh) & 2u) ? v[1] : 0.0);
     }
+    const int tb = tid & 1;
     for (int j2 = tid; j2 < 2 * nflag; j2 += BLOCK) {
         const uint32_t e = S.flagl[j2 >> 1];
         if (!((e >> (kOpSh + tb)) & 1u)) continue;
         const int c = (int)(e & kCellMask);
         if (c >= R.ncell) { S.err = kErrFarCell; continue; }
         const int b = mv_of(e), t = 2 * b + tb;
-        add_to_t<kBM>(acc, b, flagged_value<F32>(R, c, MV.tx[t], MV.ty[t], MV.tz[t], e & kMbIon, MV.ct[b][0], e & kMbImg,
-                                            MV.ct[b][2]));
+        const double v = flagged_value<F32>(R, c, MV.tx[t], MV.ty[t], MV.tz[t], e & kMbIon, MV.ct[b][0], e & kMbImg,
+                                            MV.ct[b][2]);
+        add_pair(acc, b, tb ? 0.0 : v, tb ? v : 0.0);
     }
 }
 
-// Near leaves by lane pairs as the far cells: slot f of the flattened near leaves is
-// taken by lanes 2f (old position) and 2f + 1 (new position); for the new position,
-// every ion other than the mover within tau is an overlap.
+// Near leaves, a lane per slot of the flattened leaves for both targets of the entry's
+// move; for the new position, every ion other than the mover within tau is an overlap.
 template <int BLOCK>
 __device__ __forceinline__ void near_pass_mb(const RepU& R, BTrav<BLOCK>& S, BMoves& MV, int near_n, int total,
-                                             double (&acc)[kBM]) {
+                                             double (&acc)[kBT]) {
     const int n_ion = R.n;
     const bool listed = total <= BTrav<BLOCK>::OWNCAP;  // uniform
     const int tid = fresh_tid();
-    const int tb = tid & 1;
-    for (int f2 = tid; f2 < 2 * total; f2 += BLOCK) {
-        const int f = f2 >> 1;
+    for (int f = tid; f < total; f += BLOCK) {
         const int lo = listed ? (int)S.near_own[f] : near_search(S.near_pre, near_n, f);
         const uint32_t e = S.nearl[lo];
-        if (!((e >> (kOpSh + tb)) & 1u)) continue;
         const int b = mv_of(e);
         const int slot = S.near_base[lo] + (f - S.near_pre[lo]);
         const double4 s = gload(R.pool4 + slot);
         const int sid = gload(R.pidx + slot);
         const int ion = MV.ion[b];
         if (((e & kMbIon) && sid == ion) || ((e & kMbImg) && sid == n_ion + ion)) continue;
-        const int t = 2 * b + tb;
-        const double dx = MV.tx[t] - s.x, dy = MV.ty[t] - s.y, dz = MV.tz[t] - s.z;
-        const double d2 = dx * dx + dy * dy + dz * dz;
-        if (tb == 1 && sid < n_ion && sid != ion && d2 <= R.tau2) record_overlap(MV, b, sid, n_ion);
-        if (d2 == 0.0) {
-            if (!(tb == 1 && sid < n_ion)) record_overlap(MV, b, sid, n_ion);
-            continue;
+        double v[2];
+#pragma unroll
+        for (int tb = 0; tb < 2; ++tb) {
+            const int t = 2 * b + tb;
+            const double dx = MV.tx[t] - s.x, dy = MV.ty[t] - s.y, dz = MV.tz[t] - s.z;
+            const double d2 = dx * dx + dy * dy + dz * dz;
+            const bool on = (e >> (kOpSh + tb)) & 1u;
+            if (on && tb == 1 && sid < n_ion && sid != ion && d2 <= R.tau2) record_overlap(MV, b, sid, n_ion);
+            if (on && d2 == 0.0 && !(tb == 1 && sid < n_ion)) record_overlap(MV, b, sid, n_ion);
+            v[tb] = on && d2 != 0.0 ? s.w * rsqrt_nr(d2) : 0.0;
         }
-        add_to_t<kBM>(acc, b, s.w * rsqrt_nr(d2));
+        add_pair(acc, b, v[0], v[1]);
     }
 }
 
@@ -332,9 +327,9 @@ __device__ void traverse_mb(const RepU& R, BTrav<BLOCK>& S, BMoves& MV, Hook&& h
     using TS = BTrav<BLOCK>;
     constexpr int NW = TS::NW;
     const int tid = fresh_tid(), lane = tid & 63, w = tid >> 6;
-    double acc[kBM];  // this lane's target (its parity) of every move
+    double acc[kBT];
 #pragma unroll
-    for (int k = 0; k < kBM; ++k) acc[k] = 0.0;
+    for (int k = 0; k < kBT; ++k) acc[k] = 0.0;
     int cur = 0, fs = MV.fs0, far_n = 0, near_n = 0, nflag = 0, buf = 0;
     bool failed = false, frontier_full = false;
     uint32_t* const gfr = spill_region(R);
@@ -520,10 +515,13 @@ __device__ void traverse_mb(const RepU& R, BTrav<BLOCK>& S, BMoves& MV, Hook&& h
     __syncthreads();  // publishes near_own
     PHASE(kPhFar);
     near_pass_mb<BLOCK>(R, S, MV, near_n, total, acc);
+    {   // each 16-lane row leaves the sums of its lanes, one target a lane
+        double x[16];
 #pragma unroll
-    for (int k = 0; k < kBM; ++k) {
-        const double sum = wave_sum_parity(acc[k]);
-        if (lane < 2) S.red[w][2 * k + lane] = sum;
+        for (int k = 0; k < 16; ++k) x[k] = k < kBT ? acc[k] : 0.0;
+        const double sum = row_reduce_scatter16(x, lane & 15);
+        const int t = rs_index(lane & 15);
+        if (t < kBT) S.red[4 * w + (lane >> 4)][t] = sum;
     }
     __syncthreads();
     PHASE(kPhNear);
@@ -531,7 +529,7 @@ __device__ void traverse_mb(const RepU& R, BTrav<BLOCK>& S, BMoves& MV, Hook&& h
     PHASE(kPhOverlap);
     if (tid < kBT) {
         double sum = 0.0;
-        for (int ww = 0; ww < NW; ++ww) sum += S.red[ww][tid];
+        for (int r = 0; r < 4 * NW; ++r) sum += S.red[r][tid];
         MV.pot[tid] = sum;
     }
 }
@@ -628,16 +626,22 @@ __device__ RoundOut round_mb(const RepU& R, BTrav<BLOCK>& S, BMoves& MV, int b0,
     if (th >= 0 && th < 4 * nb) { MV.path[th >> 2][th & 3][0] = 0; MV.plen[th >> 2][th & 3] = 0; }
     if (tp >= 0 && tp < 2 * nb) MV.pf_stage[tp >> 1][tp & 1] = ((tp & 1) && !imgs) ? 3 : 0;
     __syncthreads();
-    // first frontier: the eight children of the root (or the root) for every move inside the walls
+    // first frontier: the eight children of the root (or the root) for every move inside the walls,
+    // the moves of a cell side by side: they keep to that order down the tree, so the moves that
+    // open a cell read its children's headers, and then their rows, at the same time
     if (tid < 8 * nb) {
         const int b = tid >> 3, d = tid & 7;
         if (!MV.wall[b]) {
-            int before = 0;
-            for (int bb = 0; bb < b; ++bb) before += MV.wall[bb] ? 0 : 1;
+            int before = 0, act = 0;
+            for (int bb = 0; bb < nb; ++bb) {
+                const int in = MV.wall[bb] ? 0 : 1;
+                act += in;
+                before += bb < b ? in : 0;
+            }
             const uint32_t hdr = ((uint32_t)b << kMvSh) | (3u << kOpSh);
             if (MV.level0 == 1) {
                 const int di = key_digit(MV.key[b][0], 1), dk = imgs ? key_digit(MV.key[b][2], 1) : -1;
-                S.front[0][8 * before + d] = (uint32_t)(1 + d) | hdr | (d == di ? kMbIon : 0u) | (d == dk ? kMbImg : 0u);
+                S.front[0][act * d + before] = (uint32_t)(1 + d) | hdr | (d == di ? kMbIon : 0u) | (d == dk ? kMbImg : 0u);
             } else if (d == 0) {
                 S.front[0][before] = hdr | kMbIon | (imgs ? kMbImg : 0u);
             }
