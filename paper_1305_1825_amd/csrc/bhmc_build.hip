@@ -273,6 +273,40 @@ k_sort_scatter(Rep* reps, int r, int pass, int tiles_per_block, const int* hist)
     for (int base = (int)lo; base < hi; base += kBuildBlock) sort_tile(ka, va, kb, vb, base, hi, shift, off, wcnt, tile_tot);
 }
 
+// The ions in the order of the sorted keys (images left out): the targets of the energy and
+// gradient traversals are cut from this list.  Block b counts the ions among its sorted
+// positions (in ptmp, free after the sort); the second launch sums the counts before its own
+// block and writes the list.
+constexpr int kOrderBlock = 1024;
+
+__global__ void __launch_bounds__(kOrderBlock) k_ion_count(Rep* reps, const int* rep_list) {
+    Rep& R = reps[rep_list ? rep_list[blockIdx.y] : blockIdx.y];
+    const int k = blockIdx.x * kOrderBlock + threadIdx.x;
+    if (blockIdx.x * kOrderBlock >= R.nsrc) return;  // uniform
+    const bool ion = k < R.nsrc && (unsigned)R.perm[k] < (unsigned)R.n;
+    const int c = __syncthreads_count(ion);
+    if (threadIdx.x == 0) R.ptmp[blockIdx.x] = c;
+}
+
+__global__ void __launch_bounds__(kOrderBlock) k_ion_fill(Rep* reps, const int* rep_list) {
+    Rep& R = reps[rep_list ? rep_list[blockIdx.y] : blockIdx.y];
+    if (blockIdx.x * kOrderBlock >= R.nsrc) return;  // uniform
+    __shared__ uint64_t wsum[kOrderBlock / 64 + 1];
+    __shared__ int first;
+    if (threadIdx.x == 0) first = 0;
+    __syncthreads();
+    int sum = 0;
+    for (int b = threadIdx.x; b < (int)blockIdx.x; b += kOrderBlock) sum += R.ptmp[b];
+    if (sum) atomicAdd(&first, sum);
+    const int k = blockIdx.x * kOrderBlock + threadIdx.x;
+    const int i = k < R.nsrc ? R.perm[k] : -1;
+    const bool ion = (unsigned)i < (unsigned)R.n;
+    uint64_t tot;
+    const uint64_t ex = block_exscan<kOrderBlock>(ion ? 1ull : 0ull, wsum, tot);  // its barriers publish first
+    const int at = first + (int)ex;
+    if (ion && at < R.n) R.iord[at] = i;
+}
+
 // first index in [lo, hi) whose key is >= v
 __device__ __forceinline__ int lower_bound_key(const uint64_t* keys, int lo, int hi, uint64_t v) {
     while (lo < hi) {
@@ -691,6 +725,11 @@ void launch_count_wide(hipStream_t s, Rep* reps, int r, int nsrc, int* cnt) {
     hipLaunchKernelGGL(k_count_wide, dim3(std::max(1, (nsrc + kBuildBlock - 1) / kBuildBlock)), dim3(kBuildBlock), 0, s,
                        reps, r, cnt);
     hipLaunchKernelGGL(k_count_finish, dim3(1), dim3(1), 0, s, reps, r, cnt);
+}
+void launch_ion_order(hipStream_t s, int nrep, Rep* reps, const int* list, int max_nsrc) {
+    const dim3 grid((max_nsrc + kOrderBlock - 1) / kOrderBlock, nrep);
+    hipLaunchKernelGGL(k_ion_count, grid, dim3(kOrderBlock), 0, s, reps, list);
+    hipLaunchKernelGGL(k_ion_fill, grid, dim3(kOrderBlock), 0, s, reps, list);
 }
 void launch_topology(hipStream_t s, int nrep, Rep* reps, const int* list) {
     hipLaunchKernelGGL(k_topology, dim3(nrep), dim3(kBuildBlock), 0, s, reps, list);

@@ -55,6 +55,7 @@ struct Rep {
     double4* src;                  // (x, y, z, q) per source, home copy
     uint64_t* keys; int* perm;     // sorted keys and source index, as built
     uint64_t* ktmp; int* ptmp;     // radix-sort ping-pong
+    int* iord;                     // ions in the order of the sorted keys
     int2* track;                   // tracking of each source: (its leaf's cell, slot)
     double4* cgeo;                 // centre x, y, z and half side h
     int4* cm;                      // (N_A, link, leaf slot base, leaf capacity); link is the

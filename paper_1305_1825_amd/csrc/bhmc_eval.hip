@@ -741,25 +741,6 @@ __device__ __attribute__((noinline)) double flagged_value(const Rep& R, int c, d
     return v;
 }
 
-// Far cells, then the cells holding an excluded source, which is taken back out.
-template <bool F32, int NTG, int BLOCK>
-__device__ __forceinline__ void far_pass(const RepU& R, Trav<NTG, BLOCK>& S, int far_n, int nflag,
-                                         double (&acc)[NTG]) {
-    for (int j = threadIdx.x; j < far_n; j += BLOCK) {
-        const uint32_t e = S.farl[j];
-        const int c = (int)(e & kCellMask), t = (int)((e >> 24) & 15u);
-        if (c >= R.ncell) { S.err = kErrFarCell; continue; }
-        add_to<NTG>(acc, t, far_value<F32>(R, c, S.tx[t], S.ty[t], S.tz[t]));
-    }
-    for (int j = threadIdx.x; j < nflag; j += BLOCK) {
-        const uint32_t e = S.flagl[j];
-        const int c = (int)(e & kCellMask), t = (int)((e >> 24) & 15u);
-        if (c >= R.ncell) { S.err = kErrFarCell; continue; }
-        add_to<NTG>(acc, t, flagged_value<F32>(R, c, S.tx[t], S.ty[t], S.tz[t], e & kFlagIon, S.es_i[t], e & kFlagImg,
-                                          S.es_k[t]));
-    }
-}
-
 // The near list entry of flattened slot f: the last j with pre[j] <= f.
 __device__ __forceinline__ int near_search(const int* pre, int near_n, int f) {
     int lo = 0, hi = near_n - 1;
@@ -815,33 +796,6 @@ __device__ int near_scan(Trav<NTG, BLOCK>& S, int near_n) {
     return carry;
 }
 
-// Near leaves: direct sum over each leaf's index array in slot order.  For
-// the overlap target, every ion other than the mover within tau is an overlap.
-template <int NTG, int BLOCK>
-__device__ __forceinline__ void near_pass(const RepU& R, Trav<NTG, BLOCK>& S, int near_n, int total,
-                                          double (&acc)[NTG]) {
-    const int n_ion = R.n;
-    const bool listed = total <= Trav<NTG, BLOCK>::OWNCAP;  // uniform
-    for (int f = threadIdx.x; f < total; f += BLOCK) {
-        const int lo = listed ? (int)S.near_own[f] : near_search(S.near_pre, near_n, f);
-        const uint32_t e = S.nearl[lo];
-        const int t = (int)((e >> 24) & 15u);
-        const int slot = S.near_base[lo] + (f - S.near_pre[lo]);
-        const double4 s = R.pool4[slot];
-        const bool check_ovl = (t == S.ovl_t);
-        int sid = -1;
-        if ((e & (kFlagIon | kFlagImg)) || check_ovl) {
-            sid = R.pidx[slot];
-            if (((e & kFlagIon) && sid == S.ex_i[t]) || ((e & kFlagImg) && sid == S.ex_k[t])) continue;
-        }
-        const double dx = S.tx[t] - s.x, dy = S.ty[t] - s.y, dz = S.tz[t] - s.z;
-        const double d2 = dx * dx + dy * dy + dz * dz;
-        if (check_ovl && sid < n_ion && sid != S.ovl_ex && d2 <= R.tau2) S.overlap = 1;
-        if (d2 == 0.0) { S.coincide = 1; continue; }
-        add_to<NTG>(acc, t, s.w * rsqrt_nr(d2));
-    }
-}
-
 // squared distance from a point to the closed cube of centre g and half side g.w
 __device__ __forceinline__ double box_dist2(double4 g, double x, double y, double z) {
     double ax = fabs(x - g.x) - g.w, ay = fabs(y - g.y) - g.w, az = fabs(z - g.z) - g.w;
@@ -895,179 +849,6 @@ __device__ void overlap_below_far(const RepU& R, Trav<NTG, BLOCK>& S, int* cnt2)
         cur ^= 1;
         __syncthreads();
     }
-}
-
-// Breadth-first MAC traversal (Sec. 3.2) from the entries already in
-// front[0].  Each chunk of BLOCK entries is classified lane by lane; wave
-// ballots and one barrier hand out list slots in a fixed order, so every sum
-// below is taken in the same order on every run.  On return S.res[t] holds
-// the potential at target t from every source except the target's excluded
-// ones; S.err reports an overflowed list or a failed index check;
-// S.overlap / S.coincide report hard-core hits at the overlap target.
-// Returns the number of levels processed (hook is called once per level,
-// by every thread, right after the level's first loads are issued).
-template <bool F32, int NTG, int BLOCK, class Hook>
-__device__ int traverse(const RepU& R, Trav<NTG, BLOCK>& S, int nroot, int* cnt2, Hook&& hook) {
-    using TS = Trav<NTG, BLOCK>;
-    constexpr int NW = TS::NW;
-    const int tid = threadIdx.x, lane = lane_id(), w = wave_id();
-    double acc[NTG];
-#pragma unroll
-    for (int k = 0; k < NTG; ++k) acc[k] = 0.0;
-    int cur = 0, fs = nroot, far_n = 0, near_n = 0, nflag = 0, buf = 0;
-    bool failed = false, frontier_full = false;
-    // the frontier: front[] in LDS up to lcap entries, then the workgroup's HBM region (two halves
-    // of gcap entries); rg / wg: the level read / the level written is in HBM (uniform)
-    uint32_t* const gfr = spill_region(R);
-    const int gcap = gfr ? (int)(R.spill_words / 2 < 0x7FFFFFFF ? R.spill_words / 2 : 0x7FFFFFFF) : 0;
-    const int lcap = R.fcap < TS::FCAP ? R.fcap : TS::FCAP;
-    bool rg = false, wg = false;
-    int level = 0;
-    for (; fs > 0 && !failed; ++level) {
-        int next_n = 0;
-        for (int base = 0; base < fs; base += BLOCK) {
-            if (far_n > TS::FARCAP - BLOCK) {
-                __syncthreads();
-                far_pass<F32, NTG, BLOCK>(R, S, far_n, 0, acc);
-                far_n = 0;
-                __syncthreads();
-            }
-            if (near_n > TS::NEARCAP - BLOCK) {
-                __syncthreads();
-                const int total = near_scan<NTG, BLOCK>(S, near_n);
-                near_list<BLOCK>(S.near_own, S.near_pre, near_n, total, TS::OWNCAP);
-                __syncthreads();
-                near_pass<NTG, BLOCK>(R, S, near_n, total, acc);
-                near_n = 0;
-                __syncthreads();
-            }
-            const int j = base + tid;
-            const bool valid = j < fs;
-            const uint32_t e = valid ? (rg ? gfr[(size_t)cur * gcap + j] : S.front[cur][j]) : 0u;
-            const int c = (int)(e & kCellMask), t = (int)((e >> 24) & 15u);
-            const int fi = (e & kFlagIon) ? 1 : 0, fk = (e & kFlagImg) ? 1 : 0;
-            int kind = 0;
-            int4 m = make_int4(0, -1, 0, 0);
-            double4 g = make_double4(0.0, 0.0, 0.0, 0.0);
-            if (valid && c < R.ncell) { m = R.cm[c]; g = R.cgeo[c]; }
-            // once per level, in the shadow of the loads just issued
-            if (base == 0) hook(level);
-            uint32_t cdir = e & kFlagDirect;
-            if (valid && c >= R.ncell) {
-                S.err = kErrFrontCell;
-            } else if (valid) {
-                const int np = m.x - fi - fk;
-                if (m.y >= 0 && m.y + 8 > R.ncell) {
-                    S.err = kErrChildLink;
-                } else if (np > 0) {
-                    if (cdir) {
-                        kind = m.y >= 0 ? 3 : 2;
-                    } else {
-                        const double dx = g.x - S.tx[t], dy = g.y - S.ty[t], dz = g.z - S.tz[t];
-                        const double d2 = dx * dx + dy * dy + dz * dz;
-                        const bool mac = 3.0 * (g.w * g.w) <= R.theta2 * d2;
-                        if (mac && np >= R.n0) {
-                            kind = (fi | fk) ? 4 : 1;
-                            if (t == S.ovl_t) {
-                                if (box_dist2(g, S.tx[t], S.ty[t], S.tz[t]) <= R.reach2) {
-                                    const int slot = atomicAdd(&S.n_ovl, 1);
-                                    if (slot < TS::OVLCAP) S.ovl[slot] = (uint32_t)c; else S.err = kErrStack;
-                                }
-                            }
-                        } else if (np > R.n0 && m.y >= 0) {
-                            kind = 3;
-                        } else if (m.y < 0) {
-                            kind = 2;
-                        } else {
-                            kind = 3;
-                            cdir = kFlagDirect;  // N_A <= N_0: sum every source below directly
-                        }
-                    }
-                }
-            }
-            const uint64_t lt = lanemask_lt();
-            const uint64_t bf = __ballot(kind == 1), bn = __ballot(kind == 2);
-            const uint64_t bs = __ballot(kind == 3), bg = __ballot(kind == 4);
-            if (lane == 0)
-                S.wcnt[buf][w] = (uint64_t)__popcll(bf) | ((uint64_t)__popcll(bn) << 16) |
-                                 ((uint64_t)__popcll(bs) << 32) | ((uint64_t)__popcll(bg) << 48);
-            __syncthreads();
-            uint64_t before = 0, tot = 0;
-#pragma unroll
-            for (int ww = 0; ww < NW; ++ww) {
-                const uint64_t v = S.wcnt[buf][ww];
-                before += ww < w ? v : 0ull;
-                tot += v;
-            }
-            buf ^= 1;
-            const int tf = (int)(tot & 0xffff), tn = (int)((tot >> 16) & 0xffff);
-            const int ts = (int)((tot >> 32) & 0xffff), tg = (int)(tot >> 48);
-            if (nflag + tg > 2 * NTG) {  // uniform
-                failed = true;
-                break;
-            }
-            if (next_n + 8 * ts > (wg ? gcap : lcap)) {  // uniform
-                if (wg || next_n + 8 * ts > gcap) {
-                    failed = frontier_full = true;
-                    break;
-                }
-                // the next level moves to HBM: what this level wrote so far first
-                for (int k = tid; k < next_n; k += BLOCK) gfr[(size_t)(cur ^ 1) * gcap + k] = S.front[cur ^ 1][k];
-                wg = true;
-            }
-            if (kind == 1) {
-                S.farl[far_n + (int)(before & 0xffff) + __popcll(bf & lt)] = e;
-            } else if (kind == 2) {
-                const int o = near_n + (int)((before >> 16) & 0xffff) + __popcll(bn & lt);
-                S.nearl[o] = e;
-                S.near_base[o] = m.z;
-                S.near_pre[o] = m.x;
-                if (m.x < 0 || m.z < 0 || m.z + m.x > R.pool) { S.near_pre[o] = 0; S.err = kErrNearSlots; }
-            } else if (kind == 4) {
-                S.flagl[nflag + (int)(before >> 48) + __popcll(bg & lt)] = e;
-            } else if (kind == 3) {
-                const int o = next_n + 8 * ((int)((before >> 32) & 0xffff) + __popcll(bs & lt));
-                const int dig_i = fi ? key_digit(S.kx_i[t], level + 1) : -1;
-                const int dig_k = fk ? key_digit(S.kx_k[t], level + 1) : -1;
-#pragma unroll
-                for (int d = 0; d < 8; ++d) {
-                    const uint32_t fl = (d == dig_i ? kFlagIon : 0u) | (d == dig_k ? kFlagImg : 0u) | cdir;
-                    if (wg) gfr[(size_t)(cur ^ 1) * gcap + o + d] = pack(m.y + d, t, fl);
-                    else S.front[cur ^ 1][o + d] = pack(m.y + d, t, fl);
-                }
-            }
-            far_n += tf; near_n += tn; nflag += tg; next_n += 8 * ts;
-        }
-        __syncthreads();  // the next level reads what this one wrote
-        cur ^= 1;
-        fs = next_n;
-        rg = wg;
-    }
-    if (failed) {
-        if (tid == 0) S.err = frontier_full ? kErrFrontier : kErrStack;
-        __syncthreads();
-        return level;
-    }
-    const int total = near_scan<NTG, BLOCK>(S, near_n);
-    near_list<BLOCK>(S.near_own, S.near_pre, near_n, total, TS::OWNCAP);
-    far_pass<F32, NTG, BLOCK>(R, S, far_n, nflag, acc);
-    __syncthreads();  // publishes near_own
-    near_pass<NTG, BLOCK>(R, S, near_n, total, acc);
-    __syncthreads();
-    if (S.ovl_t >= 0 && S.n_ovl > 0 && S.err == 0) overlap_below_far<NTG, BLOCK>(R, S, cnt2);
-#pragma unroll
-    for (int k = 0; k < NTG; ++k) {
-        const double sum = wave_sum(acc[k]);
-        if (lane == 0) S.red[w][k] = sum;
-    }
-    __syncthreads();
-    if (tid < NTG) {
-        double sum = 0.0;
-        for (int ww = 0; ww < NW; ++ww) sum += S.red[ww][tid];
-        S.res[tid] = sum;
-    }
-    __syncthreads();
-    return level;
 }
 
 // ------------------------------------------------------------ the move traversal
@@ -2115,8 +1896,6 @@ __device__ __forceinline__ MoveOut one_move(const RepU& R, Trav<2, BLOCK>& S, Mc
 // ------------------------------------------------------------ kernels
 constexpr int kMcBlock = 512;      // a single chain: the widest traversal per move
 constexpr int kMcBlockBatch = 256; // replicas: two workgroups per CU hide each other's latency
-constexpr int kEnergyBlock = 256;
-constexpr int kEnergyTargets = 4;
 
 __device__ __forceinline__ void load_rep(Rep& dst, const Rep* src) {
     constexpr int W = (int)(sizeof(Rep) / 8);
@@ -2224,74 +2003,7 @@ __global__ void __launch_bounds__(kMcBlock) k_move(Rep* reps, int r, MoveIO* io)
 
 #include "bhmc_moves.hpp"
 
-// Potential at every ion, with the ion and its image excluded, and each ion's term of
-//   E / l_B = 1/2 q phi + 1/2 gamma a q^2 / (r^2 - a^2) + Q q / r.
-// A workgroup takes kEnergyTargets consecutive positions of the build's key
-// order (a space-filling curve) and traverses for the ions among them, so that
-// its targets are close in space and share most of their interaction lists.
-template <bool F32>
-__global__ void __launch_bounds__(kEnergyBlock) k_energy(Rep* reps, int r, double* phi, double* eterm) {
-    constexpr int NTG = kEnergyTargets;
-    __shared__ Trav<NTG, kEnergyBlock> S;
-    __shared__ Rep Rs;
-    __shared__ int cnt2[2];
-    __shared__ int s_ion[NTG];
-    __shared__ int s_nv;
-    fill_mi(S);
-    load_rep(Rs, reps + r);
-    __syncthreads();
-    const int tid = threadIdx.x;
-    const RepU R(Rs);
-    const bool imgs = Rs.images != 0;
-    const int ngroups = (Rs.nsrc + NTG - 1) / NTG;
-    // one group of positions per workgroup, or several when the grid is bounded (HBM frontier regions)
-    for (int grp = blockIdx.x; grp < ngroups; grp += gridDim.x) {
-        const int k0 = grp * NTG;
-        if (tid == 0) {
-            int nv = 0;
-            for (int j = 0; j < NTG && k0 + j < Rs.nsrc; ++j) {
-                const int sid = Rs.perm[k0 + j];
-                if ((unsigned)sid < (unsigned)Rs.n) s_ion[nv++] = sid;
-            }
-            s_nv = nv;
-        }
-        __syncthreads();
-        const int nv = s_nv;
-        if (nv == 0) {  // uniform: only images at these positions
-            __syncthreads();
-            continue;
-        }
-        if (tid < nv) {
-            const int ion = s_ion[tid];
-            const double4 si = Rs.src[ion];
-            const double4 mo = imgs ? Rs.src[Rs.n + ion] : make_double4(0, 0, 0, 0);
-            S.tx[tid] = si.x; S.ty[tid] = si.y; S.tz[tid] = si.z;
-            S.ex_i[tid] = ion; S.ex_k[tid] = imgs ? Rs.n + ion : -1;
-            S.kx_i[tid] = morton_key(Rs, si.x, si.y, si.z);
-            S.kx_k[tid] = imgs ? morton_key(Rs, mo.x, mo.y, mo.z) : 0;
-            S.es_i[tid] = si; S.es_k[tid] = mo;
-            S.front[0][tid] = pack(0, tid, kFlagIon | (imgs ? kFlagImg : 0u));
-        }
-        if (tid == 0) { S.ovl_t = -1; S.ovl_ex = -1; S.n_ovl = 0; S.err = 0; S.overlap = 0; S.coincide = 0; }
-        __syncthreads();
-        traverse<F32, NTG, kEnergyBlock>(R, S, nv, cnt2, [](int) {});
-        if (tid < nv) {
-            const int ion = s_ion[tid];
-            const double4 si = Rs.src[ion];
-            const double ph = S.err ? __builtin_nan("") : S.res[tid];
-            if (S.err && tid == 0) reps[r].err_detail = S.err;
-            double e = 0.5 * si.w * ph;
-            if (Rs.geom == 1) {
-                const double r2 = si.x * si.x + si.y * si.y + si.z * si.z;
-                if (imgs) e += 0.5 * Rs.gamma * Rs.a * si.w * si.w / (r2 - Rs.a2);
-                if (Rs.Qc != 0.0) e += Rs.Qc * si.w / sqrt(r2);
-            }
-            if (phi) phi[ion] = ph;
-            eterm[ion] = e;
-        }
-        __syncthreads();  // the next group reuses the traversal state
-    }
-}
+#include "bhmc_group.hpp"
 
 // Gradient of the treecode energy, step 1.  The ions, in the order of the
 // build's key sort, are cut into groups of 16; one workgroup
@@ -2313,7 +2025,6 @@ __global__ void __launch_bounds__(kEnergyBlock) k_energy(Rep* reps, int r, doubl
 // and eterm gets the ion's energy term as in k_energy.
 constexpr int kGradBlock = 256;
 constexpr int kGradRows = kGradBlock / 16;
-constexpr int kGT = 16;
 
 struct GradShared {
     static constexpr int FCAP = 2048;  // on chip; larger levels continue in the HBM regions
@@ -2991,13 +2702,17 @@ __global__ void __launch_bounds__(256) k_eline(Rep* reps, int r, double* phi, do
     eterm[ion] += 0.5 * si.w * (self - sub);
 }
 
+// Ions per group of the energy traversal: 16 once that fills the chip, fewer (more workgroups)
+// for small systems.  Measured with 4 / 8 / 16: 500 ions 39 / 44 / 53 us, 2,000 43 / 47 / 61,
+// 4,500 92 / 79 / 85, 10,000 176 / 139 / 147, 30,000 474 / 326 / 280, 100,000 1558 / 1068 / 898.
+int energy_group_log2(int n) { return n >= 16384 ? 4 : (n >= 4096 ? 3 : 2); }
+
 void run_energy(hipStream_t s, Rep* reps, int r, int n, double* phi, double* eterm, int max_grid, int nline, int far32) {
-    // one workgroup per group of key-order positions: at most (2 + nline) n sources
-    const long long positions = (long long)n * (2 + nline);
-    int grid = (int)std::min<long long>((positions + kEnergyTargets - 1) / kEnergyTargets, 0x7FFFFFFFll);
+    const int lg = energy_group_log2(n);
+    int grid = (n + (1 << lg) - 1) >> lg;
     if (max_grid > 0 && grid > max_grid) grid = max_grid;
-    if (far32) hipLaunchKernelGGL(k_energy<true>, dim3(grid), dim3(kEnergyBlock), 0, s, reps, r, phi, eterm);
-    else hipLaunchKernelGGL(k_energy<false>, dim3(grid), dim3(kEnergyBlock), 0, s, reps, r, phi, eterm);
+    if (far32) hipLaunchKernelGGL(k_energy<true>, dim3(grid), dim3(kGroupBlock), 0, s, reps, r, lg, phi, eterm);
+    else hipLaunchKernelGGL(k_energy<false>, dim3(grid), dim3(kGroupBlock), 0, s, reps, r, lg, phi, eterm);
     if (nline > 0) hipLaunchKernelGGL(k_eline, dim3((n + 255) / 256), dim3(256), 0, s, reps, r, phi, eterm);
 }
 void run_grad(hipStream_t s, Rep* reps, int r, const GradWork& w, double* dEdr, double* dEdq, double* eterm,

@@ -56,6 +56,8 @@ void launch_sources_wide(hipStream_t s, Rep* reps, int r, int n, const double* x
 void launch_sort_wide(hipStream_t s, Rep* reps, int r, int nsrc, int* hist);
 void launch_count_wide(hipStream_t s, Rep* reps, int r, int nsrc, int* cnt);
 void launch_leaves_wide(hipStream_t s, Rep* reps, const int* list, int r, int nleaf);
+// ions in key order (Rep.iord) from the sorted keys; max_nsrc: of the largest replica in list
+void launch_ion_order(hipStream_t s, int nrep, Rep* reps, const int* list, int max_nsrc);
 void launch_topology(hipStream_t s, int nrep, Rep* reps, const int* list);
 void launch_leaves(hipStream_t s, int nrep, Rep* reps, const int* list);
 // host / host_list: the host mirror of the descriptors (sizes and levels as counted) and the replicas
