@@ -26,6 +26,10 @@ P_MAX = 10
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # the kernels' unrolled recurrences hold dozens of FP64 constants: hoisted out of a chain's
+    # loop by the machine-code LICM they took its vector registers (k_mcb<512> at p = 5 spilled 42
+    # of them and 185 scalar ones); rematerialised where used they cost a scalar move each
+    "-mllvm", "-disable-machine-licm",
     "-Wall", "-Wno-unused-function", "-Wno-unused-variable",
     "-I" + INCLUDE, "-I" + CSRC,
 ]
