@@ -806,16 +806,19 @@ extern "C" bhmc_status bhmc_energy_grad(bhmc_tree* t, int32_t replica, double* d
     if (st) return st;
     if (!dEdr_dev || !dEdq_dev) return fail(BHMC_EINVAL, "null gradient output");
     if (!t->ops->grad) return fail(BHMC_EINVAL, "gradient not available for p = %d", t->p);
-    if ((st = current_moments(t, replica))) return st;
+    if (t->h_stale[replica]) {  // moves repaired the moments of its single-precision far field instead
+        if ((st = h2d(t, t->list_one, &replica, sizeof(int)))) return st;
+        const int r = replica;
+        expand(t, &r, 1, t->list_one);
+    }
     const Rep& h = t->host[replica];
     const int n = h.n;
     if ((st = ensure_eterm(t, n))) return st;
-    const size_t lb = align256(sizeof(double) * (size_t)h.ncell * t->mstride);
+    const size_t lb = align256(sizeof(double) * (size_t)h.ncell * t->hstride);
     const size_t gb = align256(sizeof(double) * 4 * (size_t)h.nsrc);
     const size_t tb = align256(sizeof(double) * 4 * (size_t)n);
-    const size_t ob = align256(sizeof(int) * ((size_t)h.nsrc + 1));
     const size_t ib = align256(sizeof(int) * (size_t)n);
-    const size_t need = lb + gb + tb + ob + 2 * ib;
+    const size_t need = lb + gb + tb + ib;
     if (t->gwork_bytes < need) {
         hipFree(t->gwork);
         t->gwork = nullptr;
@@ -827,9 +830,7 @@ extern "C" bhmc_status bhmc_energy_grad(bhmc_tree* t, int32_t replica, double* d
     w.L = (double*)t->gwork;
     w.G = (double4*)(t->gwork + lb);
     w.Gt = (double4*)(t->gwork + lb + gb);
-    w.rank = (int*)(t->gwork + lb + gb + tb);
-    w.islot = (int*)(t->gwork + lb + gb + tb + ob);
-    w.fcell = (int*)(t->gwork + lb + gb + tb + ob + ib);
+    w.fcell = (int*)(t->gwork + lb + gb + tb);
     w.ncell = h.ncell; w.nleaf = h.nleaf; w.nsrc = h.nsrc; w.n = n; w.nline = h.nline;
     for (;;) {
         t->ops->grad(t->stream, t->reps, replica, w, dEdr_dev, dEdq_dev, t->eterm, energy_grid_bound(t));

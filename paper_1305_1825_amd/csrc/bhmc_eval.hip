@@ -568,28 +568,6 @@ __device__ __forceinline__ void far_value2(const RepU& R, int c, const double (&
     far_rows<2>(grow(R.H + (size_t)c * HSTR), tx, ty, tz, v);
 }
 
-// Polynomial sum_n C_n d^n and its gradient sum_n C_n n_k d^{n - e_k} for
-// stored coefficients C; the monomials d^n are built by the graded
-// recurrence, each from one of order |n| - 1.
-template <int K>
-__device__ __forceinline__ void poly_rec(double (&D)[NTERM], double dx, double dy, double dz,
-                                         const double* __restrict__ Cc, double& v, double& gx, double& gy,
-                                         double& gz) {
-    if constexpr (K < NTERM) {
-        constexpr TEnt e = TT.e[K];
-        const double c = Cc[K];
-        if constexpr (K == 0) D[0] = 1.0;
-        else if constexpr (e.n1 >= 1) D[K] = D[e.x1] * dx;
-        else if constexpr (e.n2 >= 1) D[K] = D[e.y1] * dy;
-        else D[K] = D[e.z1] * dz;
-        v = fma(c, D[K], v);
-        if constexpr (e.x1 >= 0) gx = fma((double)e.n1 * c, D[e.x1], gx);
-        if constexpr (e.y1 >= 0) gy = fma((double)e.n2 * c, D[e.y1], gy);
-        if constexpr (e.z1 >= 0) gz = fma((double)e.n3 * c, D[e.z1], gz);
-        poly_rec<K + 1>(D, dx, dy, dz, Cc, v, gx, gy, gz);
-    }
-}
-
 // sum_{s <= p} P_s(cos psi) |d|^s / |R|^(s+1), psi the angle between d and -R: the
 // expansion of eq. 3.3 of one unit point source at c + d seen from c - R, order by
 // order equal to sum_{|n| <= p} T_n(R) d^n.  With A_s = P_s(cos psi) |d|^s |R|^s,
@@ -651,6 +629,20 @@ __device__ __forceinline__ double row_reduce_scatter16(double (&x)[16], int l) {
     rs_stage<0x141, 2>(x, (l >> 2) & 1);
     return x[0];
 }
+// Row sums of four values by the first two stages above and two plain sums:
+// every lane gets the sum of value b3 << 1 | (b0 ^ b2), so lanes 0, 1, 8 and 9
+// of the row hold the sums of a, b, c and d.
+__device__ __forceinline__ double row_sum4_scatter(double a, double b, double c, double d, int l) {
+    const bool u1 = (l >> 3) & 1;
+    const double s0 = (u1 ? c : a) + dpp_f64<0x128>(u1 ? a : c);
+    const double s1 = (u1 ? d : b) + dpp_f64<0x128>(u1 ? b : d);
+    const bool u2 = (l ^ (l >> 2)) & 1;
+    double v = (u2 ? s1 : s0) + dpp_f64<0xB1>(u2 ? s0 : s1);
+    v += dpp_f64<0x4E>(v);
+    v += dpp_f64<0x141>(v);
+    return v;
+}
+
 // ------------------------------------------------------------ traversal state
 constexpr uint32_t kCellMask = 0xFFFFFFu;
 constexpr uint32_t kFlagIon = 1u << 28, kFlagImg = 1u << 29, kFlagDirect = 1u << 30;
@@ -2005,97 +1997,6 @@ __global__ void __launch_bounds__(kMcBlock) k_move(Rep* reps, int r, MoveIO* io)
 
 #include "bhmc_group.hpp"
 
-// Gradient of the treecode energy, step 1.  The ions, in the order of the
-// build's key sort, are cut into groups of 16; one workgroup
-// takes a group as the targets of one shared traversal: a frontier entry is a
-// cell with four 16-bit masks (targets for which the cell is still open,
-// targets summing every source below it directly (the N_0 rule), targets
-// whose own image lies inside the cell, targets whose own ion does).  Each
-// target takes exactly the decisions its own traversal would take (Sec. 3.2),
-// so the interaction lists are the same.
-// Far cells and near leaves are then evaluated by 16-lane rows with lane k
-// serving target k: a row evaluates one far cell for all its targets, giving
-// each the potential P and the field F_k = sum_m m_k T_m M^{m - e_k} (T up
-// to order p + 1), and sums the targets' adjoint coefficients w T_n across the
-// row before one device atomic per term; a near leaf is walked source by
-// source, each pair's source side summed across the row before it is added
-// to G.  The far cell that holds a target's own image is corrected afterwards
-// (its pair terms with the image are taken out of P, F and G).  Per target:
-//   dE/dx_t += -1/2 l_B q_t F_t,   dE/dq_t += 1/2 l_B P_t,
-// and eterm gets the ion's energy term as in k_energy.
-constexpr int kGradBlock = 256;
-constexpr int kGradRows = kGradBlock / 16;
-
-struct GradShared {
-    static constexpr int FCAP = 2048;  // on chip; larger levels continue in the HBM regions
-    static constexpr int FARCAP = 512 + kGradBlock;
-    static constexpr int NEARCAP = 256 + kGradBlock;
-    static constexpr int NW = kGradBlock / 64;
-    // first in the block, so that every term's LDS address is a row base plus an
-    // immediate offset below 64 KiB (no per-term address registers)
-    union {
-        double mrow[kGradRows][MSTR];        // the moment rows of the far cells of one step, one per row
-        double red[kGradRows][kGT][4];       // the rows' sums of each target at the end
-    };
-    uint32_t fc[2][FCAP];          // cell
-    uint64_t fm[2][FCAP];          // open | direct << 16 | image inside << 32 | ion inside << 48
-    uint32_t farc[FARCAP], farm[FARCAP];
-    uint32_t nearc[NEARCAP], nearm[NEARCAP];
-    double tx[kGT], ty[kGT], tz[kGT], tq[kGT];
-    int ion[kGT];
-    uint64_t kimg[kGT], kion[kGT];
-    int flag_cell[kGT];
-    int nt;
-    uint64_t wcnt[2][NW];
-    int err;
-};
-
-// Row sums of four values by the first two stages above and two plain sums:
-// every lane gets the sum of value b3 << 1 | (b0 ^ b2), so lanes 0, 1, 8 and 9
-// of the row hold the sums of a, b, c and d.
-__device__ __forceinline__ double row_sum4_scatter(double a, double b, double c, double d, int l) {
-    const bool u1 = (l >> 3) & 1;
-    const double s0 = (u1 ? c : a) + dpp_f64<0x128>(u1 ? a : c);
-    const double s1 = (u1 ? d : b) + dpp_f64<0x128>(u1 ? b : d);
-    const bool u2 = (l ^ (l >> 2)) & 1;
-    double v = (u2 ? s1 : s0) + dpp_f64<0xB1>(u2 ? s0 : s1);
-    v += dpp_f64<0x4E>(v);
-    v += dpp_f64<0x141>(v);
-    return v;
-}
-
-// T up to order p + 1 for one (far cell, target) pair of a row: P and F for
-// the lane's target; the row's sums of w T_n go to L sixteen terms at a time,
-// reduce-scattered across the row so that each lane adds one term.
-template <int K, class MP>
-__device__ __forceinline__ void far_rec_row(double (&T)[NTERM1], double (&C)[16], double Rx, double Ry, double Rz,
-                                            double ir2, MP __restrict__ Mc, double* __restrict__ Lc, double w,
-                                            int k, double& phi, double& fx, double& fy, double& fz) {
-    if constexpr (K < NTERM1) {
-        constexpr TEnt e = TT1.e[K];
-        if constexpr (K > 0) t_step<K>(T, Rx, Ry, Rz, ir2);
-        if constexpr (K < NTERM) {
-            phi = fma(T[K], Mc[K], phi);
-            C[K & 15] = w * T[K];
-            if constexpr ((K & 15) == 15 || K == NTERM - 1) {
-#pragma unroll
-                for (int j = (K & 15) + 1; j < 16; ++j) C[j] = 0.0;
-                const double v = row_reduce_scatter16(C, k);
-                const int idx = (K & ~15) + rs_index(k);
-                if constexpr ((K & ~15) + 16 <= NTERM) gatomic_add(Lc + idx, v);
-                else if (idx < NTERM) gatomic_add(Lc + idx, v);
-            }
-        }
-        if constexpr (e.x1 >= 0) fx = fma((double)e.n1 * T[K], Mc[e.x1], fx);
-        if constexpr (e.y1 >= 0) fy = fma((double)e.n2 * T[K], Mc[e.y1], fy);
-        if constexpr (e.z1 >= 0) fz = fma((double)e.n3 * T[K], Mc[e.z1], fz);
-        // a scheduling boundary every 16 terms keeps the T_n of one stretch from being
-        // computed far ahead of their use (measured 3 % faster at p = 6)
-        if constexpr ((K & 15) == 15) __builtin_amdgcn_sched_barrier(0);
-        far_rec_row<K + 1>(T, C, Rx, Ry, Rz, ir2, Mc, Lc, w, k, phi, fx, fy, fz);
-    }
-}
-
 // Pair terms of a target with its own image y inside a far cell: with
 // D_n = (y - c)^n, v = sum_{|n|<=p} T_n D_n, F_k = sum_{|m|<=p+1} m_k T_m D_{m-e_k}
 // (the image's part of the target's field) and G_k = sum_{|n|<=p} n_k T_n D_{n-e_k}
@@ -2121,297 +2022,6 @@ __device__ __forceinline__ void flag_rec(double (&T)[NTERM1], double (&D)[NTERM]
         if constexpr (e.y1 >= 0) F[1] = fma((double)e.n2 * T[K], D[e.y1], F[1]);
         if constexpr (e.z1 >= 0) F[2] = fma((double)e.n3 * T[K], D[e.z1], F[2]);
         flag_rec<K + 1>(T, D, Rx, Ry, Rz, ir2, dx, dy, dz, v, F, G);
-    }
-}
-
-// Far list, then near list, of the group: rows of 16 lanes, lane k = target k.
-__device__ __forceinline__ void grad_rows(const Rep& R, GradShared& S, int far_n, int near_n, double* L, double4* G,
-                                          double half_lB, double (&acc)[4]) {
-    const int row = threadIdx.x >> 4, k = threadIdx.x & 15;
-    const int nt = S.nt;
-    const bool tk = k < nt;
-    const int kk = tk ? k : 0;
-    const double xk = S.tx[kk], yk = S.ty[kk], zk = S.tz[kk];
-    const double wk = half_lB * S.tq[kk];
-    // a step takes the next kGradRows far cells, one per row: the workgroup first copies
-    // their moment rows to LDS (consecutive threads, consecutive words), so that a row reads
-    // its cell's moments as it needs them instead of holding them in registers
-    for (int j0 = 0; j0 < far_n; j0 += kGradRows) {
-        const int nstep = far_n - j0 < kGradRows ? far_n - j0 : kGradRows;
-        for (int it = threadIdx.x; it < nstep * MSTR; it += kGradBlock) {
-            const int f = it / MSTR, t = it - f * MSTR;
-            const int c = (int)S.farc[j0 + f];
-            S.mrow[f][t] = c < R.ncell ? R.M[(size_t)c * MSTR + t] : 0.0;
-        }
-        __syncthreads();
-        const int j = j0 + row;
-        if (row < nstep) {
-            const int c = (int)S.farc[j];
-            if (c >= R.ncell) {
-                S.err = kErrFarCell;
-            } else {
-                const bool act = tk && ((S.farm[j] >> k) & 1u);
-                const double4 g = R.cgeo[c];
-                const double Rx = g.x - xk, Ry = g.y - yk, Rz = g.z - zk;
-                double T[NTERM1], C[16];
-                T[0] = rsqrt_nr(Rx * Rx + Ry * Ry + Rz * Rz);
-                const double ir2 = T[0] * T[0];
-                double phi = 0.0, fx = 0.0, fy = 0.0, fz = 0.0;
-                far_rec_row<0>(T, C, Rx, Ry, Rz, ir2, lrow(S.mrow[row]), L + (size_t)c * MSTR, act ? wk : 0.0, k,
-                               phi, fx, fy, fz);
-                if (act) { acc[0] += phi; acc[1] += fx; acc[2] += fy; acc[3] += fz; }
-            }
-        }
-        __syncthreads();
-    }
-    const int n_ion = R.n;
-    const int own_img = R.images ? n_ion + S.ion[kk] : -1;
-    for (int j = row; j < near_n; j += kGradRows) {
-        const int c = (int)S.nearc[j];
-        if (c >= R.ncell) { S.err = kErrNearLeaf; continue; }
-        const int4 m = R.cm[c];
-        if (m.y >= 0 || m.x < 0 || m.z < 0 || m.z + m.x > R.pool) { S.err = kErrNearSlots; continue; }
-        const bool act = tk && ((S.nearm[j] >> k) & 1u);
-        for (int s = 0; s < m.x; ++s) {
-            const double4 src = R.pool4[m.z + s];
-            const int sid = R.pidx[m.z + s];
-            if (sid < 0 || sid >= R.nsrc) { S.err = kErrNearSlots; break; }
-            const double dx = xk - src.x, dy = yk - src.y, dz = zk - src.z;
-            const double d2 = dx * dx + dy * dy + dz * dz;
-            const bool use = act && sid != S.ion[kk] && sid != own_img && d2 != 0.0;
-            double sx = 0.0, sy = 0.0, sz = 0.0, sq = 0.0;
-            if (use) {
-                const double ir = rsqrt_nr(d2);
-                const double qi3 = src.w * (ir * ir * ir);
-                acc[0] += src.w * ir; acc[1] += qi3 * dx; acc[2] += qi3 * dy; acc[3] += qi3 * dz;
-                sx = wk * qi3 * dx; sy = wk * qi3 * dy; sz = wk * qi3 * dz; sq = wk * ir;
-            }
-            const double sv = row_sum4_scatter(sx, sy, sz, sq, k);
-            if ((k & 6) == 0) gatomic_add(&G[sid].x + (((k >> 3) << 1) | (k & 1)), sv);
-        }
-    }
-}
-
-__global__ void __launch_bounds__(kGradBlock) k_grad(Rep* reps, int r, const int* islot, int nion, double* L,
-                                                     double4* G, double4* Gt, double* eterm, int* fcell) {
-    using GS = GradShared;
-    constexpr int NW = GS::NW;
-    __shared__ GS S;
-    __shared__ Rep Rs;
-    load_rep(Rs, reps + r);
-    __syncthreads();
-    const Rep& R = Rs;
-    const int tid = threadIdx.x, lane = lane_id(), w = wave_id();
-    const bool imgs = R.images != 0;
-    const double half_lB = 0.5 * R.l_B;
-    // frontier entries past the LDS capacity go to this workgroup's HBM region: cells, then masks
-    uint32_t* const gfr = spill_region(R);
-    const int gcap = gfr ? (int)((R.spill_words - 2) / 6 < 0x7FFFFFFF ? (R.spill_words - 2) / 6 : 0x7FFFFFFF) : 0;
-    uint32_t* const gfc = gfr;
-    uint64_t* const gfm = gfr ? (uint64_t*)(gfr + 2 * (size_t)gcap) : nullptr;
-    const int lcap = R.fcap < GS::FCAP ? R.fcap : GS::FCAP;
-    const int ngroups = (nion + kGT - 1) / kGT;
-    // one group of 16 ions per workgroup, or several when the grid is bounded (HBM frontier regions)
-    for (int grp = blockIdx.x; grp < ngroups; grp += gridDim.x) {
-        const int g0 = grp * kGT;
-        if (tid == 0) { S.nt = min(kGT, nion - g0); S.err = 0; }
-        __syncthreads();
-        const int nt = S.nt;
-        if (tid < nt) {
-            const int slot = islot[g0 + tid];
-            const int sid = (slot >= 0 && slot < R.pool) ? R.pidx[slot] : -1;
-            if (sid < 0 || sid >= R.n) {
-                S.err = kErrNearSlots;
-                S.ion[tid] = 0;
-                S.tx[tid] = 0.0; S.ty[tid] = 0.0; S.tz[tid] = 0.0; S.tq[tid] = 0.0;
-                S.kion[tid] = 0;
-            } else {
-                const double4 p = R.pool4[slot];
-                S.ion[tid] = sid;
-                S.tx[tid] = p.x; S.ty[tid] = p.y; S.tz[tid] = p.z; S.tq[tid] = p.w;
-                S.kion[tid] = morton_key(R, p.x, p.y, p.z);
-            }
-            const double4 mo = (imgs && sid >= 0 && sid < R.n) ? R.src[R.n + sid] : make_double4(0, 0, 0, 0);
-            S.kimg[tid] = imgs ? morton_key(R, mo.x, mo.y, mo.z) : 0;
-            S.flag_cell[tid] = -1;
-        }
-        if (tid == 0) {
-            const uint64_t all = (1ull << nt) - 1ull;
-            S.fc[0][0] = 0u;
-            S.fm[0][0] = all | (imgs ? all << 32 : 0ull) | (all << 48);
-        }
-        __syncthreads();
-        // ---- breadth-first traversal with target masks
-        int cur = 0, fs = 1, far_n = 0, near_n = 0, buf = 0;
-        double acc[4] = {0.0, 0.0, 0.0, 0.0};
-        bool failed = false, frontier_full = false, rg = false, wg = false;
-        for (int level = 0; fs > 0 && !failed; ++level) {
-            int next_n = 0;
-            for (int base = 0; base < fs; base += kGradBlock) {
-                if (far_n > GS::FARCAP - kGradBlock || near_n > GS::NEARCAP - kGradBlock) {
-                    __syncthreads();
-                    grad_rows(R, S, far_n, near_n, L, G, half_lB, acc);
-                    far_n = 0; near_n = 0;
-                    __syncthreads();
-                }
-                const int j = base + tid;
-                const bool valid = j < fs;
-                const uint32_t ec = valid ? (rg ? gfc[(size_t)cur * gcap + j] : S.fc[cur][j]) : 0u;
-                const uint64_t em = valid ? (rg ? gfm[(size_t)cur * gcap + j] : S.fm[cur][j]) : 0ull;
-                const int c = (int)(ec & kCellMask);
-                uint32_t farb = 0, nearb = 0, copen = 0, cdir = 0;
-                int4 m = make_int4(0, -1, 0, 0);
-                if (valid && c >= R.ncell) {
-                    S.err = kErrFrontCell;
-                } else if (valid) {
-                    m = R.cm[c];
-                    const double4 g = R.cgeo[c];
-                    if (m.y >= 0 && m.y + 8 > R.ncell) {
-                        S.err = kErrChildLink;
-                    } else {
-                        const uint32_t open = (uint32_t)(em & 0xFFFFu), dir = (uint32_t)((em >> 16) & 0xFFFFu);
-                        const uint32_t inimg = (uint32_t)((em >> 32) & 0xFFFFu);
-                        const uint32_t inion = (uint32_t)(em >> 48);
-                        uint32_t todo = open | dir;
-                        while (todo) {
-                            const int t = __builtin_ctz(todo);
-                            todo &= todo - 1u;
-                            const uint32_t bit = 1u << t;
-                            const int np = m.x - (int)((inion >> t) & 1u) - (int)((inimg >> t) & 1u);
-                            if (np <= 0) continue;
-                            if (dir & bit) {
-                                if (m.y >= 0) cdir |= bit; else nearb |= bit;
-                                continue;
-                            }
-                            const double dx = g.x - S.tx[t], dy = g.y - S.ty[t], dz = g.z - S.tz[t];
-                            const double d2 = dx * dx + dy * dy + dz * dz;
-                            const bool mac = 3.0 * (g.w * g.w) <= R.theta2 * d2;
-                            if (mac && np >= R.n0) {
-                                farb |= bit;
-                                if (inimg & bit) S.flag_cell[t] = c;
-                            } else if (np > R.n0 && m.y >= 0) {
-                                copen |= bit;
-                            } else if (m.y < 0) {
-                                nearb |= bit;
-                            } else {
-                                cdir |= bit;
-                            }
-                        }
-                    }
-                }
-                const bool kf = farb != 0, kn = nearb != 0, ks = (copen | cdir) != 0;
-                const uint64_t lt = lanemask_lt();
-                const uint64_t bf = __ballot(kf), bn = __ballot(kn), bs = __ballot(ks);
-                if (lane == 0)
-                    S.wcnt[buf][w] = (uint64_t)__popcll(bf) | ((uint64_t)__popcll(bn) << 16) |
-                                     ((uint64_t)__popcll(bs) << 32);
-                __syncthreads();
-                uint64_t before = 0, tot = 0;
-#pragma unroll
-                for (int ww = 0; ww < NW; ++ww) {
-                    const uint64_t v = S.wcnt[buf][ww];
-                    before += ww < w ? v : 0ull;
-                    tot += v;
-                }
-                buf ^= 1;
-                const int tf = (int)(tot & 0xffff), tn = (int)((tot >> 16) & 0xffff), ts = (int)((tot >> 32) & 0xffff);
-                if (next_n + 8 * ts > (wg ? gcap : lcap)) {  // uniform
-                    if (wg || next_n + 8 * ts > gcap) {
-                        failed = frontier_full = true;
-                        break;
-                    }
-                    // the next level moves to HBM: what this level wrote so far first
-                    for (int k = tid; k < next_n; k += kGradBlock) {
-                        gfc[(size_t)(cur ^ 1) * gcap + k] = S.fc[cur ^ 1][k];
-                        gfm[(size_t)(cur ^ 1) * gcap + k] = S.fm[cur ^ 1][k];
-                    }
-                    wg = true;
-                }
-                if (kf) {
-                    const int o = far_n + (int)(before & 0xffff) + __popcll(bf & lt);
-                    S.farc[o] = (uint32_t)c;
-                    S.farm[o] = farb;
-                }
-                if (kn) {
-                    const int o = near_n + (int)((before >> 16) & 0xffff) + __popcll(bn & lt);
-                    S.nearc[o] = (uint32_t)c;
-                    S.nearm[o] = nearb;
-                }
-                if (ks) {
-                    const int o = next_n + 8 * ((int)((before >> 32) & 0xffff) + __popcll(bs & lt));
-                    const uint32_t live = copen | cdir;
-                    const uint32_t inimg = (uint32_t)((em >> 32) & 0xFFFFu) & live;
-                    const uint32_t inion = (uint32_t)(em >> 48) & live;
-                    // the child digit of every live target's image and ion
-                    uint64_t dimg = 0, dion = 0;
-                    for (uint32_t rest = inimg; rest; rest &= rest - 1u) {
-                        const int t = __builtin_ctz(rest);
-                        dimg |= (uint64_t)key_digit(S.kimg[t], level + 1) << (4 * t);
-                    }
-                    for (uint32_t rest = inion; rest; rest &= rest - 1u) {
-                        const int t = __builtin_ctz(rest);
-                        dion |= (uint64_t)key_digit(S.kion[t], level + 1) << (4 * t);
-                    }
-#pragma unroll
-                    for (int d = 0; d < 8; ++d) {
-                        uint32_t im = 0, io = 0;
-                        for (uint32_t rest = inimg; rest; rest &= rest - 1u) {
-                            const int t = __builtin_ctz(rest);
-                            if ((int)((dimg >> (4 * t)) & 15u) == d) im |= 1u << t;
-                        }
-                        for (uint32_t rest = inion; rest; rest &= rest - 1u) {
-                            const int t = __builtin_ctz(rest);
-                            if ((int)((dion >> (4 * t)) & 15u) == d) io |= 1u << t;
-                        }
-                        const uint64_t mk = (uint64_t)copen | ((uint64_t)cdir << 16) | ((uint64_t)im << 32) |
-                                            ((uint64_t)io << 48);
-                        if (wg) {
-                            gfc[(size_t)(cur ^ 1) * gcap + o + d] = (uint32_t)(m.y + d);
-                            gfm[(size_t)(cur ^ 1) * gcap + o + d] = mk;
-                        } else {
-                            S.fc[cur ^ 1][o + d] = (uint32_t)(m.y + d);
-                            S.fm[cur ^ 1][o + d] = mk;
-                        }
-                    }
-                }
-                far_n += tf; near_n += tn; next_n += 8 * ts;
-            }
-            __syncthreads();
-            cur ^= 1;
-            fs = next_n;
-            rg = wg;
-        }
-        if (failed && tid == 0) S.err = frontier_full ? kErrFrontier : kErrStack;
-        __syncthreads();
-        grad_rows(R, S, far_n, near_n, L, G, half_lB, acc);
-        // (the far cell holding a target's own image is corrected by k_gflag)
-        {
-            const int row = tid >> 4, k = tid & 15;
-            S.red[row][k][0] = acc[0]; S.red[row][k][1] = acc[1]; S.red[row][k][2] = acc[2]; S.red[row][k][3] = acc[3];
-        }
-        __syncthreads();
-        if (tid < nt) {
-            double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-            for (int rr = 0; rr < kGradRows; ++rr) {
-                a0 += S.red[rr][tid][0]; a1 += S.red[rr][tid][1]; a2 += S.red[rr][tid][2]; a3 += S.red[rr][tid][3];
-            }
-            const int ion = S.ion[tid];
-            const double q = S.tq[tid];
-            const bool bad = S.err != 0;
-            if (bad && tid == 0) reps[r].err_detail = S.err;
-            const double ph = bad ? __builtin_nan("") : a0;
-            double e = 0.5 * q * ph;
-            if (R.geom == 1) {
-                const double r2 = S.tx[tid] * S.tx[tid] + S.ty[tid] * S.ty[tid] + S.tz[tid] * S.tz[tid];
-                if (imgs) e += 0.5 * R.gamma * R.a * q * q / (r2 - R.a2);
-                if (R.Qc != 0.0) e += R.Qc * q / sqrt(r2);
-            }
-            eterm[ion] = e;
-            const double wq = half_lB * q;
-            Gt[ion] = make_double4(-wq * a1, -wq * a2, -wq * a3, half_lB * ph);
-            fcell[ion] = S.flag_cell[tid];
-        }
-        __syncthreads();
     }
 }
 
@@ -2518,71 +2128,6 @@ __global__ void __launch_bounds__(256) k_gline(Rep* reps, int r, double4* G, dou
     for (int m = 0; m < R.nline; ++m) e += 0.5 * x.w * (R.line_c[m] * R.gamma * R.a * x.w / (r2 - R.line_t[m] * R.a2));
     Gt[ion] = gt;
     eterm[ion] = e;
-}
-
-// Ion groups of the gradient traversal: the ions in the order of the build's
-// key sort (a space-filling curve, so consecutive ions are close in space).
-// rank[k] counts the ions before sorted position k; islot[rank] is the
-// current slot of that ion.
-__global__ void __launch_bounds__(256) k_gcount(const Rep* reps, int r, int* rank) {
-    const Rep& R = reps[r];
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < R.nsrc) rank[k] = (unsigned)R.perm[k] < (unsigned)R.n ? 1 : 0;
-}
-
-__global__ void __launch_bounds__(1024) k_gscan(int* v, int nv) {
-    __shared__ uint64_t wsum[1024 / 64 + 1];
-    int carry = 0;
-    for (int base = 0; base < nv; base += 1024) {
-        const int j = base + threadIdx.x;
-        const int x = j < nv ? v[j] : 0;
-        uint64_t tot;
-        const uint64_t ex = block_exscan<1024>((uint64_t)x, wsum, tot);
-        if (j < nv) v[j] = carry + (int)ex;
-        carry += (int)tot;
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) v[nv] = carry;
-}
-
-__global__ void __launch_bounds__(256) k_gfill(const Rep* reps, int r, const int* rank, int* islot) {
-    const Rep& R = reps[r];
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= R.nsrc) return;
-    const int i = R.perm[k];
-    if ((unsigned)i >= (unsigned)R.n) return;
-    const int rk = rank[k];
-    if (rk < 0 || rk >= R.n) return;
-    const int2 tr = R.track[i];
-    int slot = -1;
-    if (tr.x >= 0 && tr.x < R.ncell) {
-        const int4 m = R.cm[tr.x];
-        if (m.y < 0 && tr.y >= 0 && tr.y < m.x && m.z >= 0 && m.z + m.x <= R.pool) slot = m.z + tr.y;
-    }
-    islot[rk] = slot;
-}
-
-// Step 2, one thread per source: the source side of every far cell holding
-// it, sum over its ancestors A of L_A^n (y - c_A)^n, differentiated in y
-// (times q) and in q.
-__global__ void __launch_bounds__(256) k_adj_down(const Rep* reps, int r, const double* L, double4* G) {
-    const Rep& R = reps[r];
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= R.nsrc) return;
-    const double4 y = R.src[s];
-    int c = R.track[s].x;
-    double v = 0.0, gx = 0.0, gy = 0.0, gz = 0.0;
-    for (int guard = 0; c >= 0 && guard < kMaxLevels; ++guard) {
-        if (c >= R.ncell) { v = __builtin_nan(""); break; }
-        const double4 g = R.cgeo[c];
-        double D[NTERM];
-        poly_rec<0>(D, y.x - g.x, y.y - g.y, y.z - g.z,
-                    (const double*)__builtin_assume_aligned(L + (size_t)c * MSTR, 32), v, gx, gy, gz);
-        c = R.cparent[c];
-    }
-    double4 o = G[s];
-    o.x += y.w * gx; o.y += y.w * gy; o.z += y.w * gz; o.w += v;
-    G[s] = o;
 }
 
 // Step 3, one thread per ion: both roles of the ion, its image mapped back
@@ -2717,19 +2262,12 @@ void run_energy(hipStream_t s, Rep* reps, int r, int n, double* phi, double* ete
 }
 void run_grad(hipStream_t s, Rep* reps, int r, const GradWork& w, double* dEdr, double* dEdq, double* eterm,
               int max_grid) {
-    const size_t nl = (size_t)w.ncell * MSTR, ng = 4 * (size_t)w.nsrc;
-    hipLaunchKernelGGL(k_zero, dim3((unsigned)std::min<size_t>(4096, (nl + 255) / 256)), dim3(256), 0, s, w.L, nl);
-    hipLaunchKernelGGL(k_zero, dim3((unsigned)std::min<size_t>(4096, (ng + 255) / 256)), dim3(256), 0, s,
-                       (double*)w.G, ng);
-    // ion groups: ranks of the ions in key order, then their slots
-    hipLaunchKernelGGL(k_gcount, dim3((w.nsrc + 255) / 256), dim3(256), 0, s, (const Rep*)reps, r, w.rank);
-    hipLaunchKernelGGL(k_gscan, dim3(1), dim3(1024), 0, s, w.rank, w.nsrc);
-    hipLaunchKernelGGL(k_gfill, dim3((w.nsrc + 255) / 256), dim3(256), 0, s, (const Rep*)reps, r,
-                       (const int*)w.rank, w.islot);
+    // L and G are adjacent in the workspace
+    const size_t nz = (size_t)(w.G - (double4*)w.L) * 4 + 4 * (size_t)w.nsrc;
+    hipLaunchKernelGGL(k_zero, dim3((unsigned)std::min<size_t>(4096, (nz + 255) / 256)), dim3(256), 0, s, w.L, nz);
     int ggrid = (w.n + kGT - 1) / kGT;
     if (max_grid > 0 && ggrid > max_grid) ggrid = max_grid;
-    hipLaunchKernelGGL(k_grad, dim3(ggrid), dim3(kGradBlock), 0, s, reps, r, (const int*)w.islot, w.n,
-                       w.L, w.G, w.Gt, eterm, w.fcell);
+    hipLaunchKernelGGL(k_grad, dim3(ggrid), dim3(kGroupBlock), 0, s, reps, r, w.L, w.G, w.Gt, eterm, w.fcell);
     hipLaunchKernelGGL(k_gflag, dim3((w.n + 255) / 256), dim3(256), 0, s, reps, r, (const int*)w.fcell, w.G,
                        w.Gt, eterm);
     if (w.nline > 0)

@@ -66,11 +66,9 @@ void launch_moments(hipStream_t s, int nrep, Rep* reps, const int* list, int nte
 
 // Workspace of one gradient evaluation (device memory, library-owned).
 struct GradWork {
-    double* L;            // adjoint coefficients, ncell rows of mstride
-    double4* G;           // per source: dE/dx, dE/dy, dE/dz, dE/dq through its source role
+    double* L;            // adjoint coefficients, ncell rows of hstride
+    double4* G;           // per source: dE/dx, dE/dy, dE/dz, dE/dq through its source role; follows L
     double4* Gt;          // per ion: the same through its target role
-    int* rank;            // per sorted source: ions before it (nsrc + 1)
-    int* islot;           // per ion rank: its current slot (n)
     int* fcell;           // per ion: the far cell holding its own image in its traversal, or -1 (n)
     int ncell, nleaf, nsrc, n;
     int nline;            // line images per ion (multiple-image model), 0 without

@@ -1,4 +1,4 @@
-"""Energies of whole systems at the edges of the group traversal: fewer ions than a group,
+"""Energies and gradients of whole systems at the edges of the group traversal: fewer ions than a group,
 one more or less than a multiple, the sizes at which the group grows, the N_0 rule, systems
 without images, the single-precision far field, and frontiers that leave the chip."""
 import numpy as np
@@ -67,3 +67,49 @@ def test_single_precision_far_field_excludes_the_own_image_exactly(n):
     for i in range(0, n, max(1, n // 40)):
         mag = o.far_magnitude(np.array([x[i], y[i], z[i]]), (i, n + i))
         assert abs(float(phi[i] - phi32[i])) <= K * mag + 1e-12 * (1.0 + abs(float(phi[i])))
+
+
+GRAD_CASES = [  # system, ions, order, theta, N_0, frontier entries on chip, leaf capacity
+    ("cube", 1, 4, 0.5, 0, 4096, 8), ("cube", 2, 5, 0.5, 0, 4096, 8), ("cube", 15, 6, 0.9, 0, 4096, 2),
+    ("cube", 33, 1, 0.7, 2, 4096, 1), ("colloid", 63, 0, 0.5, 0, 64, 8), ("colloid", 80, 7, 0.6, 0, 4096, 4),
+    ("colloid", 401, 9, 0.5, 0, 4096, 1), ("colloid", 257, 10, 0.5, 4, 64, 8), ("colloid", 1025, 3, 0.3, 0, 64, 8),
+]
+
+
+@pytest.mark.parametrize("kind,n,p,theta,n0,front,leaf", GRAD_CASES)
+def test_gradient_matches_oracle(kind, n, p, theta, n0, front, leaf):
+    P, x, y, z, q = system(kind, n, p, theta, n0)
+    P = dict(P, leaf_cap=leaf)
+    g = bhmc.Tree(P, x, y, z, q)
+    g.set_frontier_capacity(front)
+    print(kind, n, p, theta, n0, front, flush=True)
+    E, dr, dq = g.energy_grad()
+    o = O.Tree(P, x, y, z, q)
+    Eo = o.energy()
+    go, gqo = o.grad()[-2:]
+    dr, dq = dr.cpu().numpy(), dq.cpu().numpy()
+    go = np.asarray(go).reshape(n, 3)
+    rms = np.sqrt(np.mean(go ** 2)) + 1e-300
+    assert np.all(np.abs(dr - go) <= 1e-10 * (np.abs(go) + rms)), np.max(np.abs(dr - go) / (np.abs(go) + rms))
+    assert np.all(np.abs(dq - gqo) <= 1e-10 * (np.abs(gqo) + 1.0))
+    assert abs(E - Eo) <= 1e-11 * max(1.0, np.sum(np.abs(q) * np.abs(gqo)))
+
+
+def test_gradient_after_moves_with_a_single_precision_far_field():
+    """Its moves repair the moments the single-precision copy is made of; the gradient, always
+    in FP64, forms its expansion rows from them."""
+    P, x, y, z, q = system("colloid", 400, 5, 0.5, 0)
+    t = bhmc.Tree(dict(P, far_fp32=1), x, y, z, q)
+    t.mc_run(seed=3, n_moves=200, step=1.0)
+    E, dr, dq = t.energy_grad()
+    t.refresh_moments()
+    E2, dr2, dq2 = t.energy_grad()
+    s = float(dr2.abs().max())
+    assert float((dr - dr2).abs().max()) <= 1e-11 * s and float((dq - dq2).abs().max()) <= 1e-11 * float(dq2.abs().max())
+    xs, ys, zs, qs = (v.cpu().numpy() for v in t.state())
+    f = bhmc.Tree(P, xs, ys, zs, qs)
+    assert abs(E - E2) <= 1e-11 * max(1.0, abs(E2))
+    # a fresh FP64 tree of the same ions has the cells of the current positions, not of the built
+    # ones: its gradient differs by truncation only (order 5 at theta = 0.5)
+    _, dr3, _ = f.energy_grad()
+    assert float((dr2 - dr3).abs().max()) <= 1e-2 * s
