@@ -151,6 +151,9 @@ struct bhmc_tree {
     long long* sweep_add = nullptr;  // n_r per replica
     int* build_list = nullptr;       // replicas of a build (at most R)
     long long* build_off = nullptr;  // their first ion in the caller's arrays
+    // at the end of the descriptors' pinned mirror: results that kernels write to the host themselves
+    // (a single move's and an energy call's one value), so such a call is one launch and one wait --
+    // no copies, each of which the host would wait for
     bhmc::MoveIO* io = nullptr;
     double* eterm = nullptr; int eterm_n = 0;
     char* gwork = nullptr; size_t gwork_bytes = 0;  // gradient workspace
@@ -583,7 +586,7 @@ static void destroy(bhmc_tree* t) {
     for (void* p : t->arena1) if (p) hipFree(p);
     for (void* p : t->arena2) if (p) hipFree(p);
     hipFree(t->reps); hipFree(t->queue); hipFree(t->list_all); hipFree(t->list_one); hipFree(t->list_rest);
-    hipFree(t->sweep_add); hipFree(t->build_list); hipFree(t->build_off); hipFree(t->io); hipFree(t->eterm); hipFree(t->scalar); hipFree(t->gwork);
+    hipFree(t->sweep_add); hipFree(t->build_list); hipFree(t->build_off); hipFree(t->eterm); hipFree(t->gwork);
     hipFree(t->spill); hipFree(t->wide_buf);
     if (t->host) hipHostFree(t->host);
     if (t->pin) hipHostFree(t->pin);
@@ -612,10 +615,14 @@ static bhmc_status create(const bhmc_params* params, int32_t R, const int64_t* n
     t->h_stale.assign(R, 0);
     t->stream = (hipStream_t)stream;
     t->params.assign(params, params + R);
-    if (hipHostMalloc((void**)&t->host, sizeof(Rep) * R, hipHostMallocDefault) != hipSuccess) {
+    const size_t tail = (sizeof(Rep) * R + 255) & ~(size_t)255;
+    if (hipHostMalloc((void**)&t->host, tail + 256, hipHostMallocDefault) != hipSuccess) {
         delete t;
         return fail(BHMC_ENOMEM, "pinned descriptor mirror");
     }
+    t->io = (bhmc::MoveIO*)((char*)t->host + tail);
+    t->scalar = (double*)((char*)t->host + tail + 128);
+    static_assert(sizeof(bhmc::MoveIO) <= 128, "a move's result fits its place");
     t->arena1.assign(R, nullptr);
     t->arena2.assign(R, nullptr);
     t->ops = bhmc::eval_ops(t->p);
@@ -636,8 +643,6 @@ static bhmc_status create(const bhmc_params* params, int32_t R, const int64_t* n
     if (hipMalloc(&t->sweep_add, sizeof(long long) * R) != hipSuccess) return bail(fail(BHMC_ENOMEM, "sweep"));
     if (hipMalloc(&t->build_list, sizeof(int) * R) != hipSuccess) return bail(fail(BHMC_ENOMEM, "build list"));
     if (hipMalloc(&t->build_off, sizeof(long long) * R) != hipSuccess) return bail(fail(BHMC_ENOMEM, "build list"));
-    if (hipMalloc(&t->io, sizeof(bhmc::MoveIO)) != hipSuccess) return bail(fail(BHMC_ENOMEM, "io"));
-    if (hipMalloc(&t->scalar, sizeof(double) * 4) != hipSuccess) return bail(fail(BHMC_ENOMEM, "scalar"));
     if (ensure_pin(t, 1 << 16) != BHMC_OK) return bail(BHMC_ENOMEM);
     if (bhmc::upload_build_tables(t->p, t->pin) != hipSuccess) return bail(fail(BHMC_EHIP, "constant tables"));
     std::vector<int> list(R);
@@ -741,9 +746,9 @@ static bhmc_status finish_energy(bhmc_tree* t, int r, int n, double* E_host, con
     *again = false;
     bhmc::launch_sum(t->stream, t->eterm, n, t->host[r].l_B, t->scalar);
     HIP_TRY(hipGetLastError());
-    double E = 0.0;
-    bhmc_status st = d2h(t, &E, t->scalar, sizeof(double));
-    if (st) return st;
+    bhmc_status st = BHMC_OK;
+    HIP_TRY(hipStreamSynchronize(t->stream));
+    const double E = *(volatile double*)t->scalar;
     if (std::isnan(E)) {
         if ((st = download(t))) return st;
         const int d = t->host[r].err_detail;
@@ -853,11 +858,12 @@ static bhmc_status run_move(bhmc_tree* t, int64_t i, const double* r_new, int mo
     const bhmc::MoveIO io_in = io;
     for (;;) {
         io = io_in;
-        if ((st = h2d(t, t->io, &io, sizeof(io)))) return st;
         if (mode == 1) moves_ran(t, 0);
-        t->ops->move(t->stream, t->reps, 0, t->io, t->has_lines ? 1 : 0, t->host[0].far32);
+        *t->io = io;
+        t->ops->move(t->stream, t->reps, 0, io, t->io, t->has_lines ? 1 : 0, t->host[0].far32);
         HIP_TRY(hipGetLastError());
-        if ((st = d2h(t, &io, t->io, sizeof(io)))) return st;
+        HIP_TRY(hipStreamSynchronize(t->stream));
+        io = *t->io;
         if (io.status != -7) break;
         if ((st = download(t))) return st;
         if (retry_with_spill(t, t->host[0].err_detail, &st)) {

@@ -1973,18 +1973,18 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2)))
 }
 
 template <bool LINES, bool F32>
-__global__ void __launch_bounds__(kMcBlock) k_move(Rep* reps, int r, MoveIO* io) {
+__global__ void __launch_bounds__(kMcBlock) k_move(Rep* reps, int r, MoveIO in, MoveIO* io) {
     __shared__ Trav<2, kMcBlock> S;
     __shared__ McShared MS;
     __shared__ Rep Rs;
     fill_mi(S);
     load_rep(Rs, reps + r);
     __syncthreads();
-    const int i = io->i;
+    const int i = in.i;
     const double4 si = Rs.src[i];
     const double4 mo = Rs.images ? Rs.src[Rs.n + i] : make_double4(0, 0, 0, 0);
-    const MoveOut o = one_move<kMcBlock, LINES, F32>(RepU(Rs), S, MS, i, si, mo, io->rn[0], io->rn[1], io->rn[2], 0.0,
-                                         io->mode == 0 ? 0 : 2, -1);
+    const MoveOut o = one_move<kMcBlock, LINES, F32>(RepU(Rs), S, MS, i, si, mo, in.rn[0], in.rn[1], in.rn[2], 0.0,
+                                         in.mode == 0 ? 0 : 2, -1);
     if (threadIdx.x == 0) {
         io->dE = o.dE;
         io->reason = o.reason;
@@ -2213,14 +2213,14 @@ void run_mcb(hipStream_t s, Rep* reps, const McArgs& a, int grid, int wide) {
     if (a.far32) start_mcb<true>(s, reps, a, grid, wide);
     else start_mcb<false>(s, reps, a, grid, wide);
 }
-void run_move(hipStream_t s, Rep* reps, int r, MoveIO* io, int lines, int far32) {
+void run_move(hipStream_t s, Rep* reps, int r, const MoveIO& in, MoveIO* io, int lines, int far32) {
     const dim3 grid(1), block(kMcBlock);
     if (lines) {
-        if (far32) hipLaunchKernelGGL((k_move<true, true>), grid, block, 0, s, reps, r, io);
-        else hipLaunchKernelGGL((k_move<true, false>), grid, block, 0, s, reps, r, io);
+        if (far32) hipLaunchKernelGGL((k_move<true, true>), grid, block, 0, s, reps, r, in, io);
+        else hipLaunchKernelGGL((k_move<true, false>), grid, block, 0, s, reps, r, in, io);
     } else {
-        if (far32) hipLaunchKernelGGL((k_move<false, true>), grid, block, 0, s, reps, r, io);
-        else hipLaunchKernelGGL((k_move<false, false>), grid, block, 0, s, reps, r, io);
+        if (far32) hipLaunchKernelGGL((k_move<false, true>), grid, block, 0, s, reps, r, in, io);
+        else hipLaunchKernelGGL((k_move<false, false>), grid, block, 0, s, reps, r, in, io);
     }
 }
 // Line images of the multiple-image model (one thread per ion, after k_energy): an

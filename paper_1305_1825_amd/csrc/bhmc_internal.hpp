@@ -83,7 +83,8 @@ struct EvalOps {
     int moves_per_round;  // the most the batched kernel takes per round at this order
     // expansion rows H of the replicas in list from their moments M (max_ncell: of the largest)
     void (*expand)(hipStream_t s, int nrep, Rep* reps, const int* list, int max_ncell);
-    void (*move)(hipStream_t s, Rep* reps, int r, MoveIO* io_dev, int lines, int far32);
+    // in: the move, by value; out: its result (pinned host memory)
+    void (*move)(hipStream_t s, Rep* reps, int r, const MoveIO& in, MoveIO* out, int lines, int far32);
     // max_grid > 0 bounds the number of workgroups (each then takes several target groups), so that
     // every workgroup has an HBM frontier region
     // nline > 0: the replica has line images (multiple-image model), corrected after the traversal
