@@ -157,7 +157,8 @@ struct bhmc_tree {
     bhmc::MoveIO* io = nullptr;
     double* eterm = nullptr; int eterm_n = 0;
     char* gwork = nullptr; size_t gwork_bytes = 0;  // gradient workspace
-    int* wide_buf = nullptr;         // grid-wide build of one large replica: sort histograms, level counts
+    int* wide_buf = nullptr;         // workspace of the grid-wide build of one large replica
+    size_t wide_bytes = 0;
     double* scalar = nullptr;
     double* scratch = nullptr;       // device address of the fixed scratch array on the handle's device
     // HBM frontier regions, allocated the first time a traversal level outgrows its LDS capacity
@@ -530,17 +531,31 @@ static bhmc_status build_list(bhmc_tree* t, const std::vector<int>& list, const 
     st = upload(t);
     if (st) return st;
     const int nsrc0 = t->host[list[0]].nsrc;
-    if (nr == 1 && nsrc0 >= bhmc::kWideBuildMin) {
+    const bool wide = nr == 1 && nsrc0 >= bhmc::kWideBuildMin;
+    bhmc::WideTree wt{};
+    if (wide) {
         // one large replica: sources, sort and count over a grid of workgroups (same results)
-        if (!t->wide_buf) {
-            const size_t bytes = sizeof(int) * (256 * bhmc::kSortGridMax + bhmc::kCountLevels + 64);
+        // its workspace: sort histograms, the split cells' bits and counts, the sources' flag
+        constexpr int kLevels = bhmc::kMaxDepth + 1;
+        wt.words = (nsrc0 + 63) / 64;
+        const size_t hist = sizeof(int) * 256 * (bhmc::kSortGridMax + 1), lev = sizeof(int) * 2 * kLevels;
+        const size_t head = align_up(hist + lev + sizeof(int));
+        const size_t bytes = head + (size_t)wt.words * bhmc::kMaxDepth * (sizeof(uint64_t) + sizeof(int));
+        if (t->wide_bytes < bytes) {
+            if (t->wide_buf) { hipFree(t->wide_buf); t->wide_buf = nullptr; t->wide_bytes = 0; }
             HIP_TRY(hipMalloc(&t->wide_buf, bytes));
-            HIP_TRY(hipMemsetAsync(t->wide_buf, 0, bytes, t->stream));
+            t->wide_bytes = bytes;
+            HIP_TRY(hipMemsetAsync(t->wide_buf, 0, head, t->stream));
         }
+        int* const flag = (int*)((char*)t->wide_buf + hist + lev);
+        wt.count = (int*)((char*)t->wide_buf + hist);
+        wt.first = wt.count + kLevels;
+        wt.bits = (uint64_t*)((char*)t->wide_buf + head);
+        wt.pre = (int*)(wt.bits + (size_t)wt.words * bhmc::kMaxDepth);
         bhmc::launch_sources_wide(t->stream, t->reps, list[0], t->host[list[0]].n, x, y, z, q, x ? doff : nullptr,
-                                  t->wide_buf + 256 * bhmc::kSortGridMax + bhmc::kCountLevels);
+                                  flag);
         bhmc::launch_sort_wide(t->stream, t->reps, list[0], nsrc0, t->wide_buf);
-        bhmc::launch_count_wide(t->stream, t->reps, list[0], nsrc0, t->wide_buf + 256 * bhmc::kSortGridMax);
+        bhmc::launch_count_wide(t->stream, t->reps, list[0], nsrc0, wt);
     } else {
         bhmc::launch_sources(t->stream, nr, t->reps, dlist, x, y, z, q, x ? doff : nullptr);
         bhmc::launch_sort(t->stream, nr, t->reps, dlist);
@@ -561,11 +576,17 @@ static bhmc_status build_list(bhmc_tree* t, const std::vector<int>& list, const 
     }
     for (int r : list) if ((st = alloc_phase2(t, r))) return st;
     if ((st = upload(t))) return st;
-    bhmc::launch_topology(t->stream, nr, t->reps, dlist);
-    if (nr == 1 && nsrc0 >= bhmc::kWideBuildMin)
-        bhmc::launch_leaves_wide(t->stream, t->reps, dlist, list[0], t->host[list[0]].nleaf);
-    else
+    if (wide) {
+        // the moments' space, written last, holds the split cells (8 B each; their children's rows have
+        // at least 256) and the capacities' block sums until then
+        const Rep& h = t->host[list[0]];
+        wt.list = (int2*)h.M;
+        bhmc::launch_topology_wide(t->stream, t->reps, list[0], nsrc0, h.nsplit, wt);
+        bhmc::launch_leaves_wide(t->stream, t->reps, list[0], h.nleaf, (int*)(wt.list + h.nsplit));
+    } else {
+        bhmc::launch_topology(t->stream, nr, t->reps, dlist);
         bhmc::launch_leaves(t->stream, nr, t->reps, dlist);
+    }
     HIP_TRY(hipGetLastError());
     if ((st = download(t))) return st;  // cells per level size the moment launches
     for (int r : list)

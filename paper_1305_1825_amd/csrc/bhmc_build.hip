@@ -182,7 +182,7 @@ k_sort(Rep* reps, const int* rep_list) {
 }
 
 // The same sort for one large replica over a grid of workgroups, three launches
-// per pass: block histograms, one scan, block scatters.  Block b takes the tiles
+// per pass: block histograms, their scans, block scatters.  Block b takes the tiles
 // [b T, (b + 1) T) (T tiles per block); the (digit, block) counts are scanned in
 // digit-major order, so each block's items of digit d land after every item of a
 // smaller digit and after those of digit d in earlier blocks: the order is the
@@ -203,55 +203,17 @@ k_sort_hist(const Rep* reps, int r, int pass, int tiles_per_block, int* hist) {
     if (threadIdx.x < 256) hist[threadIdx.x * gridDim.x + blockIdx.x] = h[threadIdx.x];
 }
 
-// Exclusive scan of m counts in place, one workgroup, in chunks of 16 counts per
-// thread staged through LDS: each chunk is loaded and stored back with coalesced
-// accesses, each thread scans its 16 consecutive counts (rows padded by one word
-// against bank conflicts), and the thread sums are scanned in LDS (Hillis-Steele)
-// on top of the carry of the chunks before.
-constexpr int kScanPer = 16;
-constexpr int kScanChunk = kScanPer * kBuildBlock;
-__device__ __forceinline__ int scan_pad(int i) { return i + i / kScanPer; }
-
-__global__ void __launch_bounds__(kBuildBlock) k_sort_scan(int* v, int m) {
-    __shared__ int buf[kScanChunk + kBuildBlock];
-    __shared__ int part[2][kBuildBlock];
-    __shared__ int carry;
-    const int tid = threadIdx.x;
-    if (tid == 0) carry = 0;
-    __syncthreads();
-    for (int base = 0; base < m; base += kScanChunk) {  // uniform
-        const int len = std::min(kScanChunk, m - base);
-        for (int k = tid; k < len; k += kBuildBlock) buf[scan_pad(k)] = v[base + k];
-        __syncthreads();
-        int c[kScanPer];
-        int s = 0;
-#pragma unroll
-        for (int j = 0; j < kScanPer; ++j) {
-            const int i = kScanPer * tid + j;
-            c[j] = i < len ? buf[scan_pad(i)] : 0;
-            s += c[j];
-        }
-        int cur = 0;
-        part[0][tid] = s;
-        const int carry0 = carry;
-        __syncthreads();
-        for (int d = 1; d < kBuildBlock; d <<= 1) {
-            part[cur ^ 1][tid] = part[cur][tid] + (tid >= d ? part[cur][tid - d] : 0);
-            cur ^= 1;
-            __syncthreads();
-        }
-        int run = carry0 + part[cur][tid] - s;  // exclusive prefix of this thread's counts
-#pragma unroll
-        for (int j = 0; j < kScanPer; ++j) {
-            const int i = kScanPer * tid + j;
-            if (i < len) buf[scan_pad(i)] = run;
-            run += c[j];
-        }
-        __syncthreads();
-        for (int k = tid; k < len; k += kBuildBlock) v[base + k] = buf[scan_pad(k)];
-        if (tid == kBuildBlock - 1) carry = run;  // carry0 plus the chunk's total
-        __syncthreads();
-    }
+// Exclusive scan of each digit's block counts, a workgroup per digit, with the digit's total
+// after the counts; the scatter adds the totals of the smaller digits itself.  (One workgroup
+// scanning all 256 x blocks counts took 24 us a pass at 2 10^5 sources, as long as the rest of it.)
+__global__ void __launch_bounds__(kSortGridMax) k_sort_rows(int* hist, int grid) {
+    __shared__ uint64_t wsum[kSortGridMax / 64 + 1];
+    int* row = hist + blockIdx.x * grid;
+    const int v = (int)threadIdx.x < grid ? row[threadIdx.x] : 0;
+    uint64_t tot;
+    const uint64_t ex = block_exscan<kSortGridMax>((uint64_t)v, wsum, tot);
+    if ((int)threadIdx.x < grid) row[threadIdx.x] = (int)ex;
+    if (threadIdx.x == 0) hist[256 * grid + blockIdx.x] = (int)tot;
 }
 
 __global__ void __launch_bounds__(kBuildBlock)
@@ -265,8 +227,12 @@ k_sort_scatter(Rep* reps, int r, int pass, int tiles_per_block, const int* hist)
     __shared__ int off[256];
     __shared__ int wcnt[kSortNW][256];
     __shared__ int tile_tot[256];
+    __shared__ uint64_t wsum[kSortNW + 1];
     for (int k = threadIdx.x; k < kSortNW * 256; k += kBuildBlock) (&wcnt[0][0])[k] = 0;
-    if (threadIdx.x < 256) off[threadIdx.x] = hist[threadIdx.x * gridDim.x + blockIdx.x];
+    uint64_t tot;
+    const uint64_t base0 = block_exscan<kBuildBlock>(threadIdx.x < 256 ? (uint64_t)hist[256 * gridDim.x + threadIdx.x] : 0ull,
+                                                     wsum, tot);
+    if (threadIdx.x < 256) off[threadIdx.x] = (int)base0 + hist[threadIdx.x * gridDim.x + blockIdx.x];
     __syncthreads();
     const long long lo = (long long)blockIdx.x * tiles_per_block * kBuildBlock;
     const int hi = (int)std::min<long long>(n, lo + (long long)tiles_per_block * kBuildBlock);
@@ -369,36 +335,64 @@ k_count(Rep* reps, const int* rep_list) {
     if (threadIdx.x == 0) set_cell_counts(R, total, depth);
 }
 
-// The same count for one large replica over a grid: thread k takes key k at
-// every level where it starts a run of equal prefix, and stops at the first
-// such run that is not split (its runs below are parts of it).  Per-level
-// counts go to cnt[] (zero on entry); k_count_finish sums them and zeroes cnt.
-__global__ void __launch_bounds__(kBuildBlock) k_count_wide(const Rep* reps, int r, int* cnt) {
+// The same count for one large replica over a grid, kept as bitmaps so that the topology can be
+// built over a grid too.  Thread k takes key k at every level where it starts a run of equal
+// prefix, and stops at the first such run that is not split (its runs below are parts of it); bit
+// k mod 64 of word k / 64 of level l tells whether a split cell of level l starts at key k.  The
+// split cells of a level in key order are its cells in index order, so a prefix count over the
+// words gives every split cell's rank, and with it every cell's and leaf's index.
+__global__ void __launch_bounds__(256) k_split_bits(const Rep* reps, int r, WideTree t) {
     const Rep& R = reps[r];
-    const int n = R.nsrc;
-    const int k = blockIdx.x * kBuildBlock + threadIdx.x;
-    if (k >= n) return;
+    const int n = R.nsrc, lane = lane_id();
+    const int k = blockIdx.x * 256 + threadIdx.x, word = k >> 6;
+    if (word >= t.words) return;  // uniform in a wave
     const uint64_t* keys = R.keys;
-    const uint64_t key = keys[k], prev = k > 0 ? keys[k - 1] : 0;
+    const bool valid = k < n;
+    const uint64_t key = valid ? keys[k] : 0, prev = valid && k > 0 ? keys[k - 1] : 0;
+    bool open = valid;
     for (int l = 0; l < R.max_depth; ++l) {
         const int shift = 63 - 3 * l;
         const uint64_t P = key >> shift;
-        if (k > 0 && (prev >> shift) == P) continue;
-        const uint64_t next = (P + 1) << shift;
-        const int e = (l == 0) ? n : lower_bound_key(keys, k, n, next);
-        if (e - k <= R.leaf_cap) break;
-        atomicAdd(&cnt[l], 1);
+        bool split = false;
+        if (open && (k == 0 || (prev >> shift) != P)) {
+            const int e = (l == 0) ? n : lower_bound_key(keys, k, n, (P + 1) << shift);
+            split = e - k > R.leaf_cap;
+            open = split;
+        }
+        const uint64_t bits = __ballot(split);
+        if (lane == 0) t.bits[(size_t)l * t.words + word] = bits;
     }
 }
 
-__global__ void k_count_finish(Rep* reps, int r, int* cnt) {
+// Exclusive prefix counts of level blockIdx.x's words, and the level's total.
+__global__ void __launch_bounds__(kBuildBlock) k_split_scan(const Rep* reps, int r, WideTree t) {
+    const int l = blockIdx.x;
+    if (l >= reps[r].max_depth) { if (threadIdx.x == 0) t.count[l] = 0; return; }  // uniform
+    __shared__ uint64_t wsum[kBuildBlock / 64 + 1];
+    const uint64_t* bits = t.bits + (size_t)l * t.words;
+    int* pre = t.pre + (size_t)l * t.words;
+    int carry = 0;
+    for (int base = 0; base < t.words; base += kBuildBlock) {
+        const int j = base + threadIdx.x;
+        const int v = j < t.words ? __popcll(bits[j]) : 0;
+        uint64_t tot;
+        const uint64_t ex = block_exscan<kBuildBlock>((uint64_t)v, wsum, tot);
+        if (j < t.words) pre[j] = carry + (int)ex;
+        carry += (int)tot;
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) t.count[l] = carry;
+}
+
+__global__ void k_split_finish(Rep* reps, int r, WideTree t) {
     Rep& R = reps[r];
     int total = 0, depth = 0;
-    for (int l = 0; l < kCountLevels; ++l) {
-        total += cnt[l];
-        if (cnt[l]) depth = l + 1;
-        cnt[l] = 0;
+    for (int l = 0; l < kMaxDepth; ++l) {
+        t.first[l] = total;
+        total += t.count[l];
+        if (t.count[l]) depth = l + 1;
     }
+    t.first[kMaxDepth] = total;
     set_cell_counts(R, total, depth);
 }
 
@@ -495,6 +489,116 @@ k_topology(Rep* reps, const int* rep_list) {
     }
 }
 
+// The same cells for one large replica over a grid, from the bitmaps: split cell number s (in level
+// and key order) has the children 1 + 8 s .. 8 + 8 s.  A level at a time on one workgroup took 0.83
+// of the 2.4 ms of a rebuild of 10^5 ions + images (p = 6); with this, the slot bases over a grid,
+// the sort's scans a workgroup per digit and M2M's binomials from a table it takes 1.16 ms.
+// Split cells of level l that start before key `pos`.
+__device__ __forceinline__ int split_rank(const WideTree& t, int l, int pos) {
+    const int w = pos >> 6, b = pos & 63;
+    if (w >= t.words) return t.count[l];
+    const size_t at = (size_t)l * t.words + w;
+    return t.pre[at] + __popcll(t.bits[at] & (b ? ~0ull >> (64 - b) : 0ull));
+}
+
+// First key and level of every split cell, in order.
+__global__ void __launch_bounds__(256) k_split_list(const Rep* reps, int r, WideTree t) {
+    const Rep& R = reps[r];
+    const int k = blockIdx.x * 256 + threadIdx.x;
+    if (k >= R.nsrc || R.status) return;
+    for (int l = 0; l < R.max_depth; ++l) {
+        if (!((t.bits[(size_t)l * t.words + (k >> 6)] >> (k & 63)) & 1ull)) continue;
+        const int s = t.first[l] + split_rank(t, l, k);
+        if (s < R.nsplit) t.list[s] = make_int2(k, l);
+    }
+}
+
+// Thread (s, d): child d of split cell s, every field of it; thread (0, 0) the root as well.
+__global__ void __launch_bounds__(256) k_topology_wide(Rep* reps, int r, WideTree t) {
+    Rep& R = reps[r];
+    const int it = blockIdx.x * 256 + threadIdx.x, s = it >> 3, d = it & 7;
+    const int n = R.nsrc;
+    if (it == 0) {
+        R.ckey[0] = 0; R.clevel[0] = 0; R.cparent[0] = -1; R.cbegin[0] = 0; R.cend[0] = n;
+        double4 g; cell_geometry(R, 0, 0, g); R.cgeo[0] = g;
+        const int cap = R.slack * (n > R.leaf_cap ? n : R.leaf_cap) + 2 + R.nline;
+        if (R.nsplit > 0) {
+            R.cm[0] = make_int4(n, 1, -1, 0);
+        } else {
+            R.cm[0] = make_int4(n, -1, -1, cap);
+            R.lcell[0] = 0; R.lcap[0] = cap;
+        }
+        // first cell of every level
+        R.level_start[0] = 0;
+        int c = 1, l = 1;
+        for (; l <= kMaxDepth && t.count[l - 1] > 0; ++l) { R.level_start[l] = c; c += 8 * t.count[l - 1]; }
+        for (; l <= kMaxLevels; ++l) R.level_start[l] = c;
+    }
+    if (s >= R.nsplit) return;
+    const int2 kl = t.list[s];
+    const int level = kl.y, shift = 60 - 3 * level;  // of the child's digit
+    const uint64_t* keys = R.keys;
+    const uint64_t mask = level > 0 ? ~0ull << (63 - 3 * level) : 0ull;
+    const uint64_t base = keys[kl.x] & mask & 0x7FFFFFFFFFFFFFFFull;
+    const uint64_t ck = base | ((uint64_t)d << shift);
+    const int cb = d == 0 ? kl.x : lower_bound_key(keys, kl.x, n, ck);
+    // the end is where the next child begins; of the last, where the next cell of the level does
+    int ce = __shfl_down(cb, 1, 8);
+    if (d == 7) ce = lower_bound_key(keys, cb, n, ck + (1ull << shift));
+    const int ch = 1 + 8 * s + d;
+    // the split cell itself: the root, or child digit of the split cell of the level above whose run
+    // its first key lies in, the last that starts at or before that key
+    int parent = 0;
+    if (level > 0) parent = 1 + 8 * (t.first[level - 1] + split_rank(t, level - 1, kl.x + 1) - 1) + key_digit(base, level);
+    const int cnt = ce - cb, l1 = level + 1;
+    // split cells before this child, of the levels above it and of its own
+    const int below = t.first[l1] + (l1 < R.max_depth ? split_rank(t, l1, cb) : 0);
+    const bool split = cnt > R.leaf_cap && l1 < R.max_depth;
+    if (ch >= R.ncell || (split && below >= R.nsplit) || (!split && ch - below >= R.nleaf)) {
+        R.status = -5;  // the counting pass and this pass disagree: write nothing
+        return;
+    }
+    R.ckey[ch] = ck; R.clevel[ch] = l1; R.cparent[ch] = parent;
+    R.cbegin[ch] = cb; R.cend[ch] = ce;
+    double4 g; cell_geometry(R, l1, ck, g); R.cgeo[ch] = g;
+    if (split) {
+        R.cm[ch] = make_int4(cnt, 1 + 8 * below, -1, 0);
+    } else {
+        const int leaf = ch - below;
+        const int cap = R.slack * (cnt > R.leaf_cap ? cnt : R.leaf_cap) + 2 + R.nline;
+        R.lcell[leaf] = ch;
+        R.lcap[leaf] = cap;
+        R.cm[ch] = make_int4(cnt, -1 - leaf, -1, cap);
+    }
+}
+
+// Slot bases of one large replica's leaves: the exclusive scan of their capacities over a grid,
+// block sums first, then every block on top of the sums before its own.
+__global__ void __launch_bounds__(kBuildBlock) k_cap_sums(const Rep* reps, int r, int* sums) {
+    const Rep& R = reps[r];
+    __shared__ uint64_t wsum[kBuildBlock / 64 + 1];
+    const int l = blockIdx.x * kBuildBlock + threadIdx.x;
+    uint64_t tot;
+    block_exscan<kBuildBlock>(l < R.nleaf && !R.status ? (uint64_t)R.lcap[l] : 0ull, wsum, tot);
+    if (threadIdx.x == 0) sums[blockIdx.x] = (int)tot;
+}
+__global__ void __launch_bounds__(kBuildBlock) k_cap_bases(Rep* reps, int r, const int* sums) {
+    Rep& R = reps[r];
+    if (R.status) return;  // uniform: not written during this launch
+    __shared__ uint64_t wsum[kBuildBlock / 64 + 1];
+    __shared__ int first;
+    if (threadIdx.x == 0) first = 0;
+    __syncthreads();
+    int sum = 0;
+    for (int b = threadIdx.x; b < (int)blockIdx.x; b += kBuildBlock) sum += sums[b];
+    if (sum) atomicAdd(&first, sum);
+    const int l = blockIdx.x * kBuildBlock + threadIdx.x;
+    const int cap = l < R.nleaf ? R.lcap[l] : 0;
+    uint64_t tot;
+    const uint64_t ex = block_exscan<kBuildBlock>((uint64_t)cap, wsum, tot);  // its barriers publish first
+    if (l < R.nleaf) R.lbase[l] = first + (int)ex;
+}
+
 // Members of leaf l in sorted order, with their tracking entries.
 __device__ __forceinline__ void fill_leaf(Rep& R, int l) {
     const int c = R.lcell[l];
@@ -512,10 +616,9 @@ __device__ __forceinline__ void fill_leaf(Rep& R, int l) {
 }
 
 // Leaf index arrays: bases by an exclusive scan of the capacities; members
-// in sorted order; tracking = (leaf, slot) of every source.  With fill = 0
-// only the bases (k_leaves_fill then fills the leaves over a grid).
+// in sorted order; tracking = (leaf, slot) of every source.
 __global__ void __launch_bounds__(kBuildBlock)
-k_leaves(Rep* reps, const int* rep_list, int fill) {
+k_leaves(Rep* reps, const int* rep_list) {
     Rep& R = reps[rep_list ? rep_list[blockIdx.x] : blockIdx.x];
     __shared__ uint64_t wsum[kBuildBlock / 64 + 1];
     __shared__ int carry;
@@ -535,16 +638,16 @@ k_leaves(Rep* reps, const int* rep_list, int fill) {
     }
     if (threadIdx.x == 0 && carry > R.pool) R.status = -5;
     __syncthreads();
-    if (carry > R.pool || R.status || !fill) return;  // uniform: nothing is written past the pool
+    if (carry > R.pool || R.status) return;  // uniform: nothing is written past the pool
     for (int l = threadIdx.x; l < nl; l += blockDim.x) fill_leaf(R, l);
 }
 
-// The leaves of one replica, one thread per leaf over a grid (after k_leaves with fill = 0;
-// a status set by the scan leaves every leaf unwritten).
+// The leaves of one replica, one thread per leaf over a grid.
 __global__ void __launch_bounds__(256) k_leaves_fill(Rep* reps, int r) {
     Rep& R = reps[r];
     const int l = blockIdx.x * blockDim.x + threadIdx.x;
     if (l >= R.nleaf || R.status) return;
+    if (R.lbase[l] < 0 || R.lbase[l] + R.lcap[l] > R.pool) { R.status = -5; return; }
     fill_leaf(R, l);
 }
 
@@ -609,6 +712,10 @@ k_m2m(Rep* reps, const int* rep_list, int nterms, int mstride, int level) {
     if (R.status || level >= R.depth || nterms > kM2MTerms) return;
     __shared__ double W[kM2MWaves][8][kM2MTerms];
     __shared__ double hpow[kM2MWaves][kPMax + 1];
+    __shared__ double bin[kPMax + 1][kPMax + 1];  // C(n, k); formed by its recurrence, a division each, they took most of the time
+    for (int k = threadIdx.x; k < (kPMax + 1) * (kPMax + 1); k += 64 * kM2MWaves)
+        bin[k / (kPMax + 1)][k % (kPMax + 1)] = (double)c_binom[k / (kPMax + 1)][k % (kPMax + 1)];
+    __syncthreads();
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int ls = R.level_start[level], le = R.level_start[level + 1];
     for (int base = ls + blockIdx.x * kM2MWaves; base < le; base += gridDim.x * kM2MWaves) {  // uniform
@@ -644,20 +751,15 @@ k_m2m(Rep* reps, const int* rep_list, int nterms, int mstride, int level) {
             for (int n = lane; n < nterms; n += 64) {
                 const int n1 = c_mi[3 * n], n2 = c_mi[3 * n + 1], n3 = c_mi[3 * n + 2];
                 double acc = 0.0;
-                double b1 = 1.0;  // C(n1, k1)
                 for (int k1 = 0; k1 <= n1; ++k1) {
-                    double b2 = 1.0;
                     for (int k2 = 0; k2 <= n2; ++k2) {
-                        double b3 = 1.0;
+                        const double b12 = bin[n1][k1] * bin[n2][k2];
                         for (int k3 = 0; k3 <= n3; ++k3) {
                             const int e = (((n1 - k1) & 1) << 2) | (((n2 - k2) & 1) << 1) | ((n3 - k3) & 1);
-                            acc += (b1 * b2 * b3) * hpow[w][(n1 - k1) + (n2 - k2) + (n3 - k3)] *
+                            acc += (b12 * bin[n3][k3]) * hpow[w][(n1 - k1) + (n2 - k2) + (n3 - k3)] *
                                    W[w][e][mindex_dev(k1, k2, k3)];
-                            b3 = b3 * (double)(n3 - k3) / (double)(k3 + 1);
                         }
-                        b2 = b2 * (double)(n2 - k2) / (double)(k2 + 1);
                     }
-                    b1 = b1 * (double)(n1 - k1) / (double)(k1 + 1);
                 }
                 R.M[(size_t)c * mstride + n] = acc;
             }
@@ -717,14 +819,18 @@ void launch_sort_wide(hipStream_t s, Rep* reps, int r, int nsrc, int* hist) {
     const int grid = std::max(1, (tiles + tpb - 1) / tpb);
     for (int pass = 0; pass < 8; ++pass) {
         hipLaunchKernelGGL(k_sort_hist, dim3(grid), dim3(kBuildBlock), 0, s, reps, r, pass, tpb, hist);
-        hipLaunchKernelGGL(k_sort_scan, dim3(1), dim3(kBuildBlock), 0, s, hist, 256 * grid);
+        hipLaunchKernelGGL(k_sort_rows, dim3(256), dim3(kSortGridMax), 0, s, hist, grid);
         hipLaunchKernelGGL(k_sort_scatter, dim3(grid), dim3(kBuildBlock), 0, s, reps, r, pass, tpb, hist);
     }
 }
-void launch_count_wide(hipStream_t s, Rep* reps, int r, int nsrc, int* cnt) {
-    hipLaunchKernelGGL(k_count_wide, dim3(std::max(1, (nsrc + kBuildBlock - 1) / kBuildBlock)), dim3(kBuildBlock), 0, s,
-                       reps, r, cnt);
-    hipLaunchKernelGGL(k_count_finish, dim3(1), dim3(1), 0, s, reps, r, cnt);
+void launch_count_wide(hipStream_t s, Rep* reps, int r, int nsrc, const WideTree& t) {
+    hipLaunchKernelGGL(k_split_bits, dim3((nsrc + 255) / 256), dim3(256), 0, s, reps, r, t);
+    hipLaunchKernelGGL(k_split_scan, dim3(kMaxDepth), dim3(kBuildBlock), 0, s, reps, r, t);
+    hipLaunchKernelGGL(k_split_finish, dim3(1), dim3(1), 0, s, reps, r, t);
+}
+void launch_topology_wide(hipStream_t s, Rep* reps, int r, int nsrc, int nsplit, const WideTree& t) {
+    hipLaunchKernelGGL(k_split_list, dim3((nsrc + 255) / 256), dim3(256), 0, s, reps, r, t);
+    hipLaunchKernelGGL(k_topology_wide, dim3(std::max(1, (8 * nsplit + 255) / 256)), dim3(256), 0, s, reps, r, t);
 }
 void launch_ion_order(hipStream_t s, int nrep, Rep* reps, const int* list, int max_nsrc) {
     const dim3 grid((max_nsrc + kOrderBlock - 1) / kOrderBlock, nrep);
@@ -735,10 +841,12 @@ void launch_topology(hipStream_t s, int nrep, Rep* reps, const int* list) {
     hipLaunchKernelGGL(k_topology, dim3(nrep), dim3(kBuildBlock), 0, s, reps, list);
 }
 void launch_leaves(hipStream_t s, int nrep, Rep* reps, const int* list) {
-    hipLaunchKernelGGL(k_leaves, dim3(nrep), dim3(kBuildBlock), 0, s, reps, list, 1);
+    hipLaunchKernelGGL(k_leaves, dim3(nrep), dim3(kBuildBlock), 0, s, reps, list);
 }
-void launch_leaves_wide(hipStream_t s, Rep* reps, const int* list, int r, int nleaf) {
-    hipLaunchKernelGGL(k_leaves, dim3(1), dim3(kBuildBlock), 0, s, reps, list, 0);
+void launch_leaves_wide(hipStream_t s, Rep* reps, int r, int nleaf, int* sums) {
+    const dim3 grid((nleaf + kBuildBlock - 1) / kBuildBlock);
+    hipLaunchKernelGGL(k_cap_sums, grid, dim3(kBuildBlock), 0, s, reps, r, sums);
+    hipLaunchKernelGGL(k_cap_bases, grid, dim3(kBuildBlock), 0, s, reps, r, sums);
     hipLaunchKernelGGL(k_leaves_fill, dim3(std::max(1, (nleaf + 255) / 256)), dim3(256), 0, s, reps, r);
 }
 static unsigned chunks(long long items) {

@@ -46,16 +46,28 @@ void launch_sources(hipStream_t s, int nrep, Rep* reps, const int* list, const d
 void launch_sort(hipStream_t s, int nrep, Rep* reps, const int* list);
 void launch_count(hipStream_t s, int nrep, Rep* reps, const int* list);
 // One large replica over a grid of workgroups, with the same results: the sort
-// uses hist (256 * kSortGridMax ints), the count cnt (kCountLevels ints) and the
-// sources flag (one int), both zero before the call and zero again after it.
+// uses hist (256 * (kSortGridMax + 1) ints), the sources flag (one int), zero before the
+// call and zero again after it.
 constexpr int kSortGridMax = 256;
-constexpr int kCountLevels = 64;
-constexpr int kWideBuildMin = 32768;  // sources from which a single-replica build goes wide
+// Sources from which a single-replica build goes wide (rebuild, one workgroup / grid: 4,000 sources
+// 0.45 / 0.40 ms, 9,000 0.75 / 0.47 ms, 20,000 1.22 / 0.49 ms).
+constexpr int kWideBuildMin = 2048;
+// Split cells of a tree under construction over a grid: per level and 64 sorted keys the bits of
+// the keys at which one starts and the counts before the word; per level how many there are and how
+// many the levels above it have; and their first keys and levels in order.
+struct WideTree {
+    uint64_t* bits;
+    int* pre;
+    int *count, *first;   // kMaxDepth + 1 each
+    int2* list;           // set once nsplit is known
+    int words;
+};
 void launch_sources_wide(hipStream_t s, Rep* reps, int r, int n, const double* x, const double* y,
                          const double* z, const double* q, const long long* ion_off, int* flag);
 void launch_sort_wide(hipStream_t s, Rep* reps, int r, int nsrc, int* hist);
-void launch_count_wide(hipStream_t s, Rep* reps, int r, int nsrc, int* cnt);
-void launch_leaves_wide(hipStream_t s, Rep* reps, const int* list, int r, int nleaf);
+void launch_count_wide(hipStream_t s, Rep* reps, int r, int nsrc, const WideTree& t);
+void launch_topology_wide(hipStream_t s, Rep* reps, int r, int nsrc, int nsplit, const WideTree& t);
+void launch_leaves_wide(hipStream_t s, Rep* reps, int r, int nleaf, int* sums);
 // ions in key order (Rep.iord) from the sorted keys; max_nsrc: of the largest replica in list
 void launch_ion_order(hipStream_t s, int nrep, Rep* reps, const int* list, int max_nsrc);
 void launch_topology(hipStream_t s, int nrep, Rep* reps, const int* list);

@@ -1,4 +1,4 @@
-"""Energies and gradients of whole systems at the edges of the group traversal: fewer ions than a group,
+"""Energies, gradients and builds of whole systems at the edges of their grid-wide forms: fewer ions than a group,
 one more or less than a multiple, the sizes at which the group grows, the N_0 rule, systems
 without images, the single-precision far field, and frontiers that leave the chip."""
 import numpy as np
@@ -113,3 +113,24 @@ def test_gradient_after_moves_with_a_single_precision_far_field():
     # ones: its gradient differs by truncation only (order 5 at theta = 0.5)
     _, dr3, _ = f.energy_grad()
     assert float((dr2 - dr3).abs().max()) <= 1e-2 * s
+
+
+@pytest.mark.parametrize("n,leaf,depth", [(1024, 16, 21), (1025, 1, 21), (1500, 0, 5), (4100, 200000, 21), (2500, 3, 0),
+                                          (2500, 3, 1), (20001, 16, 21)])
+def test_grid_build_equals_the_one_workgroup_build(n, leaf, depth):
+    """Sizes from which a single replica's tree is built over a grid (2,048 sources), one-source
+    leaves, uniform trees, and trees of one cell or one level, against the same replica in a handle
+    of two, built by one workgroup."""
+    c = W.config_colloid_10k(n=n, p=4)
+    P = dict(c["params"], leaf_cap=leaf, max_depth=depth)
+    print(n, leaf, depth, flush=True)
+    a = bhmc.Tree(P, c["x"], c["y"], c["z"], c["q"])
+    two = [np.concatenate([c[k], c[k][:100]]) for k in "xyzq"]
+    b = bhmc.Tree([P, P], *two, n_per_replica=[n, 100])
+    assert a.info() == b.info(0)
+    for u, v in zip(a.sorted(), b.sorted(0)):
+        assert np.array_equal(u, v)
+    ca, cb, la, lb = a.cells(), b.cells(0), a.leaves(), b.leaves(0)
+    assert all(np.array_equal(ca[k], cb[k]) for k in ca) and all(np.array_equal(la[k], lb[k]) for k in la)
+    assert all(np.array_equal(u, v) for u, v in zip(a.leaf_members(), b.leaf_members(0)))
+    assert a.energy() == b.energy()
