@@ -318,6 +318,9 @@ static void fill_rep(Rep& r, const bhmc_params& P, int64_t n) {
     {
         const double reach = P.hard_core + 1e-12 * P.box_side;
         r.reach2 = reach * reach;
+        // a far cell's sphere has radius sqrt(3) h <= theta d, so its cube is at least (1 - theta) d away
+        const double gap = 1.0 - P.theta;
+        r.ovl2 = gap > 1e-3 ? r.reach2 / (gap * gap) * (1.0 + 1e-9) : INFINITY;
     }
     r.geom = P.geom; r.images = P.images; r.leaf_cap = P.leaf_cap; r.n0 = P.n0;
     r.far32 = P.far_fp32 ? 1 : 0;

@@ -165,13 +165,13 @@ struct RepU {
     double4* cgeo; int4* cm; double* H; double* M; float* M32; double4* pool4; int* pidx; double4* src; int2* track;
     uint32_t* spill;
     long long spill_words;
-    double theta2, reach2, tau2, l_B, a, a2, gamma, Qc;
+    double theta2, reach2, ovl2, tau2, l_B, a, a2, gamma, Qc;
     int n, nsrc, ncell, pool, n0, images, geom, nline, fcap, spill_regions;
     const double *line_t, *line_c;
     __device__ __forceinline__ explicit RepU(const Rep& r)
         : d(r), cgeo(uni(r.cgeo)), cm(uni(r.cm)), H(uni(r.H)), M(uni(r.M)), M32(uni(r.M32)), pool4(uni(r.pool4)),
           pidx(uni(r.pidx)), src(uni(r.src)), track(uni(r.track)), spill(uni(r.spill)), spill_words(uni(r.spill_words)),
-          theta2(uni(r.theta2)), reach2(uni(r.reach2)), tau2(uni(r.tau2)), l_B(uni(r.l_B)), a(uni(r.a)), a2(uni(r.a2)),
+          theta2(uni(r.theta2)), reach2(uni(r.reach2)), ovl2(uni(r.ovl2)), tau2(uni(r.tau2)), l_B(uni(r.l_B)), a(uni(r.a)), a2(uni(r.a2)),
           gamma(uni(r.gamma)), Qc(uni(r.Qc)), n(uni(r.n)), nsrc(uni(r.nsrc)), ncell(uni(r.ncell)), pool(uni(r.pool)),
           n0(uni(r.n0)), images(uni(r.images)), geom(uni(r.geom)), nline(uni(r.nline)), fcap(uni(r.fcap)),
           spill_regions(uni(r.spill_regions)), line_t(r.line_t), line_c(r.line_c) {}
@@ -651,9 +651,26 @@ __device__ __forceinline__ uint32_t pack(int cell, int t, uint32_t flags) {
     return (uint32_t)cell | ((uint32_t)t << 24) | flags;
 }
 
-__device__ __forceinline__ uint64_t lanemask_lt() {
-    const int lane = lane_id();
-    return lane == 0 ? 0ull : (~0ull >> (64 - lane));
+// base + the lanes below this one in the ballot b: two instructions, the addition with them
+__device__ __forceinline__ int rank_below(uint64_t b, int base) {
+    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, (uint32_t)base));
+}
+
+// An opened cell's eight frontier entries (header ne for its first child; two 16-byte
+// stores where the frontier is in LDS, whose places are multiples of eight); the children
+// on the movers' root paths (digit dig_i, dig_k of 0..7, or -1) get their flag bits after.
+__device__ __forceinline__ void put_children(uint32_t* lds, uint32_t* hbm, uint32_t ne, int dig_i, uint32_t bit_i,
+                                             int dig_k, uint32_t bit_k) {
+    if (hbm) {
+#pragma unroll
+        for (int d = 0; d < 8; ++d) hbm[d] = (ne + (uint32_t)d) | (d == dig_i ? bit_i : 0u) | (d == dig_k ? bit_k : 0u);
+        return;
+    }
+    const uint32_t v[8] = {ne, ne + 1u, ne + 2u, ne + 3u, ne + 4u, ne + 5u, ne + 6u, ne + 7u};
+    __builtin_memcpy(__builtin_assume_aligned(lds, 16), v, 16);
+    __builtin_memcpy(__builtin_assume_aligned(lds + 4, 16), v + 4, 16);
+    if (dig_i >= 0) lds[dig_i] |= bit_i;
+    if (dig_k >= 0) lds[dig_k] |= bit_k;
 }
 
 // Frontier region of this workgroup in HBM (null if none): a level whose frontier
@@ -677,7 +694,7 @@ struct Trav {
     static constexpr int HROWS = (LISTWORDS / 2) / NH;
     union {
         struct {
-            uint32_t front[2][FCAP];
+            alignas(16) uint32_t front[2][FCAP];
             uint32_t farl[FARCAP];
             uint32_t nearl[NEARCAP];
             int near_base[NEARCAP];
@@ -732,6 +749,33 @@ __device__ __attribute__((noinline)) double flagged_value(const Rep& R, int c, d
     if (img) v -= sk.w * point_expansion(g.x - x, g.y - y, g.z - z, sk.x - g.x, sk.y - g.y, sk.z - g.z);
     return v;
 }
+
+// Prefix counts of a chunk's lists over its N <= 16 (part, wave) counts, four 16-bit fields
+// each (no field overflows: a chunk has at most 1024 entries).  Every 16-lane row scans a copy
+// of the counts by DPP, a 32-bit add a step for two fields, and a wave reads its own place and
+// the totals from there into scalar registers; summing the counts in every thread took about
+// 100 vector instructions a chunk.
+template <int N>
+struct ChunkScan {
+    uint32_t lo, hi;
+    __device__ __forceinline__ explicit ChunkScan(const uint64_t* cnt) {
+        static_assert(N <= 16, "a row of lanes holds the counts");
+        const int j = lane_id() & 15;
+        const uint64_t v = j < N ? cnt[j] : 0ull;
+        lo = (uint32_t)v; hi = (uint32_t)(v >> 32);
+#define BHMC_SCAN_STEP(CTRL)                                                              \
+        lo += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)lo, CTRL, 0xF, 0xF, false);   \
+        hi += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)hi, CTRL, 0xF, 0xF, false);
+        BHMC_SCAN_STEP(0x111) BHMC_SCAN_STEP(0x112) BHMC_SCAN_STEP(0x114) BHMC_SCAN_STEP(0x118)  // row_shr 1, 2, 4, 8
+#undef BHMC_SCAN_STEP
+    }
+    // counts of the first k places (k uniform), packed as the counts are
+    __device__ __forceinline__ uint64_t before(int k) const {
+        if (k == 0) return 0ull;
+        return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)hi, k - 1) << 32) |
+               (uint32_t)__builtin_amdgcn_readlane((int)lo, k - 1);
+    }
+};
 
 // The near list entry of flattened slot f: the last j with pre[j] <= f.
 __device__ __forceinline__ int near_search(const int* pre, int near_n, int f) {
@@ -980,7 +1024,7 @@ __device__ int traverse_mc(const RepU& R, Trav<2, BLOCK>& S, int* cnt2, Hook&& h
                     copen = rest & ((np > R.n0 && internal) ? 3u : 0u);
                     nearb = (rest & ~copen & (internal ? 0u : 3u)) | (dir & (internal ? 0u : 3u));
                     cdir = (rest & ~copen & (internal ? 3u : 0u)) | (dir & (internal ? 3u : 0u));
-                    if ((farb & 2u) && S.ovl_t == 1 && box_dist2(g, S.tx[1], S.ty[1], S.tz[1]) <= R.reach2) {
+                    if ((farb & 2u) && d21 <= R.ovl2 && S.ovl_t == 1 && box_dist2(g, S.tx[1], S.ty[1], S.tz[1]) <= R.reach2) {
                         const int slot = atomicAdd(&S.n_ovl, 1);
                         if (slot < TS::OVLCAP) S.ovl[slot] = (uint32_t)c; else S.err = kErrStack;
                     }
@@ -988,19 +1032,13 @@ __device__ int traverse_mc(const RepU& R, Trav<2, BLOCK>& S, int* cnt2, Hook&& h
             }
             const bool flagged = (fi | fk) != 0;
             const bool kf = farb && !flagged, kg = farb && flagged, kn = nearb != 0, ks = (copen | cdir) != 0;
-            const uint64_t lt = lanemask_lt();
             const uint64_t bf = __ballot(kf), bn = __ballot(kn), bs = __ballot(ks), bg = __ballot(kg);
             if (lane == 0)
                 S.wcnt[buf][w] = (uint64_t)__popcll(bf) | ((uint64_t)__popcll(bn) << 16) |
                                  ((uint64_t)__popcll(bs) << 32) | ((uint64_t)__popcll(bg) << 48);
             __syncthreads();
-            uint64_t before = 0, tot = 0;
-#pragma unroll
-            for (int ww = 0; ww < NW; ++ww) {
-                const uint64_t v = S.wcnt[buf][ww];
-                before += ww < w ? v : 0ull;
-                tot += v;
-            }
+            const ChunkScan<NW> scan(S.wcnt[buf]);
+            const uint64_t before = scan.before(uni(w)), tot = scan.before(NW);
             buf ^= 1;
             const int tf = (int)(tot & 0xffff), tn = (int)((tot >> 16) & 0xffff);
             const int ts = (int)((tot >> 32) & 0xffff), tg = (int)(tot >> 48);
@@ -1017,26 +1055,22 @@ __device__ int traverse_mc(const RepU& R, Trav<2, BLOCK>& S, int* cnt2, Hook&& h
                 wg = true;
             }
             const uint32_t flags = e & (kFlagIon | kFlagImg);
-            if (kf) S.farl[far_n + (int)(before & 0xffff) + __popcll(bf & lt)] = (uint32_t)c | (farb << kMaskSh);
-            if (kg) S.flagl[nflag + (int)(before >> 48) + __popcll(bg & lt)] = (uint32_t)c | (farb << kMaskSh) | flags;
+            if (kf) S.farl[rank_below(bf, far_n + (int)(before & 0xffff))] = (uint32_t)c | (farb << kMaskSh);
+            if (kg) S.flagl[rank_below(bg, nflag + (int)(before >> 48))] = (uint32_t)c | (farb << kMaskSh) | flags;
             if (kn) {
-                const int o = near_n + (int)((before >> 16) & 0xffff) + __popcll(bn & lt);
+                const int o = rank_below(bn, near_n + (int)((before >> 16) & 0xffff));
                 S.nearl[o] = (uint32_t)c | (nearb << kMaskSh) | flags;
                 S.near_base[o] = m.z;
                 S.near_pre[o] = m.x;
                 if (m.x < 0 || m.z < 0 || m.z + m.x > R.pool) { S.near_pre[o] = 0; S.err = kErrNearSlots; }
             }
             if (ks) {
-                const int o = next_n + 8 * ((int)((before >> 32) & 0xffff) + __popcll(bs & lt));
+                const int o = next_n + 8 * rank_below(bs, (int)((before >> 32) & 0xffff));
                 const int dig_i = fi ? key_digit(S.kx_i[0], level + 1) : -1;
                 const int dig_k = fk ? key_digit(S.kx_k[0], level + 1) : -1;
                 const uint32_t masks = (copen << kMaskSh) | (cdir << kDirSh);
-#pragma unroll
-                for (int d = 0; d < 8; ++d) {
-                    const uint32_t fl = (d == dig_i ? kFlagIon : 0u) | (d == dig_k ? kFlagImg : 0u);
-                    if (wg) gfr[(size_t)(cur ^ 1) * gcap + o + d] = (uint32_t)(m.y + d) | masks | fl;
-                    else S.front[cur ^ 1][o + d] = (uint32_t)(m.y + d) | masks | fl;
-                }
+                put_children(&S.front[cur ^ 1][wg ? 0 : o], wg ? gfr + (size_t)(cur ^ 1) * gcap + o : nullptr,
+                             (uint32_t)m.y | masks, dig_i, kFlagIon, dig_k, kFlagImg);
             }
             far_n += tf; near_n += tn; nflag += tg; next_n += 8 * ts;
         }

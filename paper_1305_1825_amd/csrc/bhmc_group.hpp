@@ -237,18 +237,12 @@ __device__ __forceinline__ void group_traverse(const RepU& R, GS& S, bool flag_a
                 }
             }
             const bool kf = farb != 0, kn = nearb != 0, ks = (copen | cdir) != 0;
-            const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
             const uint64_t bf = __ballot(kf), bn = __ballot(kn), bs = __ballot(ks);
             if (lane == 0)
                 S.wcnt[buf][w] = (uint64_t)__popcll(bf) | ((uint64_t)__popcll(bn) << 16) | ((uint64_t)__popcll(bs) << 32);
             __syncthreads();
-            uint64_t before = 0, tot = 0;
-#pragma unroll
-            for (int ww = 0; ww < NW; ++ww) {
-                const uint64_t v = S.wcnt[buf][ww];
-                before += ww < w ? v : 0ull;
-                tot += v;
-            }
+            const ChunkScan<NW> scan(S.wcnt[buf]);
+            const uint64_t before = scan.before(uni(w)), tot = scan.before(NW);
             buf ^= 1;
             const int tf = (int)(tot & 0xffff), tn = (int)((tot >> 16) & 0xffff), ts = (int)(tot >> 32);
             if (next + ts > (wg ? gcap : lcap)) {  // uniform
@@ -264,19 +258,19 @@ __device__ __forceinline__ void group_traverse(const RepU& R, GS& S, bool flag_a
                 wg = true;
             }
             if (kf) {
-                const int o = far_n + (int)(before & 0xffff) + __popcll(bf & lt);
+                const int o = rank_below(bf, far_n + (int)(before & 0xffff));
                 S.farc[o] = c;
                 S.farm[o] = (uint16_t)farb;
             }
             if (kn) {
-                const int o = near_n + (int)((before >> 16) & 0xffff) + __popcll(bn & lt);
+                const int o = rank_below(bn, near_n + (int)((before >> 16) & 0xffff));
                 S.nearm[o] = (uint16_t)nearb;
                 S.near_base[o] = m.z;
                 S.near_pre[o] = m.x;
                 if (m.z < 0 || m.z + m.x > R.pool) { S.near_pre[o] = 0; S.err = kErrNearSlots; }
             }
             if (ks) {
-                const int o = next + (int)(before >> 32) + __popcll(bs & lt);
+                const int o = rank_below(bs, next + (int)(before >> 32));
                 const uint32_t live = copen | cdir;
                 const uint64_t mk = (uint64_t)copen | ((uint64_t)cdir << 16) | ((uint64_t)(im & live) << 32) |
                                     ((uint64_t)(io & live) << 48);

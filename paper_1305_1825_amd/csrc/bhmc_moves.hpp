@@ -80,7 +80,7 @@ struct BTrav {
     static constexpr int HROWS = (LISTWORDS / 2) / NH;
     union {
         struct {
-            uint32_t front[2][FCAP];
+            alignas(16) uint32_t front[2][FCAP];
             uint32_t farl[FARCAP];
             uint32_t nearl[NEARCAP];
             int near_base[NEARCAP];
@@ -375,7 +375,6 @@ __device__ void traverse_mb(const RepU& R, BTrav<BLOCK>& S, BMoves& MV, Hook&& h
             if (base == 0) hook(level);
             uint32_t farb[kChunk], nearb[kChunk], copen[kChunk];
             uint64_t bf[kChunk], bn[kChunk], bs[kChunk], bg[kChunk];
-            const uint64_t lt = lanemask_lt();
 #pragma unroll
             for (int h = 0; h < kChunk; ++h) {
                 const int c = (int)(e[h] & kCellMask), b = mv_of(e[h]);
@@ -402,7 +401,8 @@ __device__ void traverse_mb(const RepU& R, BTrav<BLOCK>& S, BMoves& MV, Hook&& h
                         const uint32_t rest = open & ~farb[h];
                         copen[h] = internal ? rest : 0u;
                         nearb[h] = internal ? 0u : rest;
-                        if ((farb[h] & 2u) && box_dist2(gg, MV.tx[t0 + 1], MV.ty[t0 + 1], MV.tz[t0 + 1]) <= R.reach2) {
+                        if ((farb[h] & 2u) && d21 <= R.ovl2 &&
+                            box_dist2(gg, MV.tx[t0 + 1], MV.ty[t0 + 1], MV.tz[t0 + 1]) <= R.reach2) {
                             const int slot = atomicAdd(&S.n_ovl, 1);
                             if (slot < TS::OVLCAP) S.ovl[slot] = (uint32_t)c | ((uint32_t)b << kMvSh); else S.err = kErrStack;
                         }
@@ -431,21 +431,10 @@ __device__ void traverse_mb(const RepU& R, BTrav<BLOCK>& S, BMoves& MV, Hook&& h
             PHASE_COUNT(kPhChunks, 1);
             __syncthreads();
             // offsets: the entries of part h of every wave come after all of part h - 1
-            uint64_t before[kChunk], tot[kChunk];
-#pragma unroll
-            for (int h = 0; h < kChunk; ++h) {
-                before[h] = 0; tot[h] = 0;
-#pragma unroll
-                for (int ww = 0; ww < NW; ++ww) {
-                    const uint64_t v = S.wcnt[buf][h][ww];
-                    before[h] += ww < w ? v : 0ull;
-                    tot[h] += v;
-                }
-            }
+            const ChunkScan<kChunk * NW> scan(&S.wcnt[buf][0][0]);
             buf ^= 1;
-            uint64_t all = 0;
-#pragma unroll
-            for (int h = 0; h < kChunk; ++h) all += tot[h];
+            const int wu = uni(w);
+            const uint64_t all = scan.before(kChunk * NW);
             const int tf = (int)(all & 0xffff), tn = (int)((all >> 16) & 0xffff);
             const int ts = (int)((all >> 32) & 0xffff), tg = (int)(all >> 48);
             if (nflag + tg > 4 * kBM) {  // uniform
@@ -460,39 +449,32 @@ __device__ void traverse_mb(const RepU& R, BTrav<BLOCK>& S, BMoves& MV, Hook&& h
                 for (int k = tid; k < next_n; k += BLOCK) gfr[(size_t)(cur ^ 1) * gcap + k] = S.front[cur ^ 1][k];
                 wg = true;
             }
-            uint64_t prior = 0;  // the parts before h, summed over the whole workgroup
 #pragma unroll
             for (int h = 0; h < kChunk; ++h) {
-                const uint64_t at = prior + before[h];
-                prior += tot[h];
+                const uint64_t at = scan.before(h * NW + wu);
                 const int c = (int)(e[h] & kCellMask), b = mv_of(e[h]);
                 const int fi = (e[h] & kMbIon) ? 1 : 0, fk = (e[h] & kMbImg) ? 1 : 0;
                 const bool flagged = (fi | fk) != 0;
                 const uint32_t flags = e[h] & (kMbIon | kMbImg);
                 const uint32_t mvb = (uint32_t)b << kMvSh;
                 if (farb[h] && !flagged)
-                    S.farl[far_n + (int)(at & 0xffff) + __popcll(bf[h] & lt)] = (uint32_t)c | mvb | (farb[h] << kOpSh);
+                    S.farl[rank_below(bf[h], far_n + (int)(at & 0xffff))] = (uint32_t)c | mvb | (farb[h] << kOpSh);
                 if (farb[h] && flagged)
-                    S.flagl[nflag + (int)(at >> 48) + __popcll(bg[h] & lt)] = (uint32_t)c | mvb | (farb[h] << kOpSh) | flags;
+                    S.flagl[rank_below(bg[h], nflag + (int)(at >> 48))] = (uint32_t)c | mvb | (farb[h] << kOpSh) | flags;
                 if (nearb[h]) {
-                    const int o = near_n + (int)((at >> 16) & 0xffff) + __popcll(bn[h] & lt);
+                    const int o = rank_below(bn[h], near_n + (int)((at >> 16) & 0xffff));
                     S.nearl[o] = (uint32_t)c | mvb | (nearb[h] << kOpSh) | flags;
                     S.near_base[o] = m[h].z;
                     S.near_pre[o] = m[h].x;
                     if (m[h].x < 0 || m[h].z < 0 || m[h].z + m[h].x > R.pool) { S.near_pre[o] = 0; S.err = kErrNearSlots; }
                 }
                 if (copen[h]) {
-                    const int o = next_n + 8 * ((int)((at >> 32) & 0xffff) + __popcll(bs[h] & lt));
+                    const int o = next_n + 8 * rank_below(bs[h], (int)((at >> 32) & 0xffff));
                     const int dig_i = fi ? key_digit(MV.key[b][0], level + 1) : -1;
                     const int dig_k = fk ? key_digit(MV.key[b][2], level + 1) : -1;
                     const uint32_t hdr = mvb | (copen[h] << kOpSh);
-#pragma unroll
-                    for (int d = 0; d < 8; ++d) {
-                        const uint32_t fl = (d == dig_i ? kMbIon : 0u) | (d == dig_k ? kMbImg : 0u);
-                        const uint32_t ne = (uint32_t)(m[h].y + d) | hdr | fl;
-                        if (wg) gfr[(size_t)(cur ^ 1) * gcap + o + d] = ne;
-                        else S.front[cur ^ 1][o + d] = ne;
-                    }
+                    put_children(&S.front[cur ^ 1][wg ? 0 : o], wg ? gfr + (size_t)(cur ^ 1) * gcap + o : nullptr,
+                                 (uint32_t)m[h].y | hdr, dig_i, kMbIon, dig_k, kMbImg);
                 }
             }
             far_n += tf; near_n += tn; nflag += tg; next_n += 8 * ts;
@@ -1011,7 +993,7 @@ __device__ RoundOut round_mb(const RepU& R, BTrav<BLOCK>& S, BMoves& MV, int b0,
             if (lane == 0) at = atomicAdd(&MV.nlist, __popcll(owners));
             at = __shfl(at, 0, 64);
             if (owner) {
-                const int slot = at + __popcll(owners & lanemask_lt());
+                const int slot = rank_below(owners, at);
                 MV.list_cell[slot] = c;
                 MV.list_mask[slot] = mask;
                 MV.list_at[slot] = (lane * kMaxLevels + l) | (l < len - 1 ? (1 << 30) : 0);
