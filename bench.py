@@ -86,14 +86,14 @@ def log(*a):
 def algorithmic_bytes_per_move(c, n_sample=400, replica=0, accept=0.9):
     """Bytes a move must touch at least, from the oracle's interaction counts:
     48 B per visited cell (centre and half side, 32 B; count, link, leaf slot
-    base and capacity, 16 B), 8 B per moment of every far cell, 32 B per near
-    source (x, y, z, q), and for an accepted move a read and a write of every
-    moment on the root paths."""
+    base and capacity, 16 B), 8 B per coefficient of every far cell's row (its
+    (p + 1)^2 harmonics and its centre), 32 B per near source (x, y, z, q), and
+    for an accepted move a read and a write of every row on the root paths."""
     import oracle as O
     P = c["params"]
     o = O.Tree(P, c["x"], c["y"], c["z"], c["q"])
     inf = o.info()
-    nterms = inf["nterms"]
+    row = (P["p"] + 1) ** 2 + 3
     n = len(c["x"])
     tot_v = tot_f = tot_s = 0
     evald = 0
@@ -104,11 +104,11 @@ def algorithmic_bytes_per_move(c, n_sample=400, replica=0, accept=0.9):
         if reason == 0:
             tot_v += cnt[0]; tot_f += cnt[1]; tot_s += cnt[2]
             evald += 1
-    per_eval = (48.0 * tot_v + 8.0 * nterms * tot_f + 32.0 * tot_s) / max(evald, 1)
+    per_eval = (48.0 * tot_v + 8.0 * row * tot_f + 32.0 * tot_s) / max(evald, 1)
     frac_eval = evald / n_sample
     depth = inf["depth"] + 1
     paths = 4 if P["images"] else 2
-    commit = paths * depth * nterms * 16.0
+    commit = paths * depth * row * 16.0
     return dict(per_move=per_eval * frac_eval + commit * accept,
                 per_eval=per_eval, visited=tot_v / max(evald, 1), far=tot_f / max(evald, 1),
                 near=tot_s / max(evald, 1), eval_fraction=frac_eval, commit_bytes=commit)
