@@ -2282,9 +2282,11 @@ __global__ void __launch_bounds__(256) k_eline(Rep* reps, int r, double* phi, do
 }
 
 // Ions per group of the energy traversal: 16 once that fills the chip, fewer (more workgroups)
-// for small systems.  Measured with 4 / 8 / 16: 500 ions 39 / 44 / 53 us, 2,000 43 / 47 / 61,
+// for small systems; 4 only as long as all its workgroups run at once (two on each of 256 CUs).
+// (2,500 ions, p = 4: 52 us in groups of 4, where the last 113 of 625 run alone; single precision 55
+// against 49 in groups of 8.)  Measured with 4 / 8 / 16: 500 ions 39 / 44 / 53 us, 2,000 43 / 47 / 61,
 // 4,500 92 / 79 / 85, 10,000 176 / 139 / 147, 30,000 474 / 326 / 280, 100,000 1558 / 1068 / 898.
-int energy_group_log2(int n) { return n >= 16384 ? 4 : (n >= 4096 ? 3 : 2); }
+int energy_group_log2(int n) { return n >= 16384 ? 4 : (n > 2048 ? 3 : 2); }
 
 void run_energy(hipStream_t s, Rep* reps, int r, int n, double* phi, double* eterm, int max_grid, int nline, int far32) {
     const int lg = energy_group_log2(n);

@@ -96,9 +96,23 @@ __device__ __forceinline__ int group_near_scan(GS& S, int near_n) {
 }
 
 // The lists' far part for energies: a lane reads a row once for kFT of the group's targets,
-// so a cell takes gt / kFT lanes.  far: this lane's sums of its targets.
+// so a cell takes gt / kFT lanes.  far: this lane's sums of its targets.  In single precision
+// (apart) the targets of a row are evaluated one after the other, so there a cell takes gt
+// lanes, one a target, and far[0] is the lane's sum: small systems' few far cells otherwise
+// left lanes idle (300 ions, p = 8: 38.9 us with four targets a lane, 31.1 with one a workgroup).
 template <bool F32>
 __device__ __forceinline__ void energy_far(const RepU& R, GroupShared<false>& S, int far_n, int lq, double (&far)[kFT]) {
+    if constexpr (F32) {  // a far_fp32 replica: M32 is there
+        const int lg = lq + kFTLog, k = (int)threadIdx.x & ((1 << lg) - 1);
+        const double x = S.tx[k], y = S.ty[k], z = S.tz[k];
+        for (int j = (int)threadIdx.x >> lg; j < far_n; j += kGroupBlock >> lg) {
+            if (!((S.farm[j] >> k) & 1u)) continue;
+            const int c = S.farc[j];
+            const double4 g = gload(R.cgeo + c);
+            far[0] += far_eval_f(g.x - x, g.y - y, g.z - z, R.M32 + (size_t)c * MSTR);
+        }
+        return;
+    }
     const int q = (int)threadIdx.x & ((1 << lq) - 1);
     double tx[kFT], ty[kFT], tz[kFT];
 #pragma unroll
@@ -107,19 +121,10 @@ __device__ __forceinline__ void energy_far(const RepU& R, GroupShared<false>& S,
         const uint32_t m = ((uint32_t)S.farm[j] >> (kFT * q)) & ((1u << kFT) - 1u);
         if (!m) continue;
         const int c = S.farc[j];
-        if (F32 && R.M32) {
-            const double4 g = gload(R.cgeo + c);
+        double v[kFT];
+        far_rows<kFT>(grow(R.H + (size_t)c * HSTR), tx, ty, tz, v);
 #pragma unroll
-            for (int u = 0; u < kFT; ++u) {
-                if ((m >> u) & 1u) far[u] += far_eval_f(g.x - tx[u], g.y - ty[u], g.z - tz[u], R.M32 + (size_t)c * MSTR);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        } else {
-            double v[kFT];
-            far_rows<kFT>(grow(R.H + (size_t)c * HSTR), tx, ty, tz, v);
-#pragma unroll
-            for (int u = 0; u < kFT; ++u) far[u] += ((m >> u) & 1u) ? v[u] : 0.0;
-        }
+        for (int u = 0; u < kFT; ++u) far[u] += ((m >> u) & 1u) ? v[u] : 0.0;
     }
 }
 
@@ -353,7 +358,7 @@ __global__ void __launch_bounds__(kGroupBlock) __attribute__((amdgpu_waves_per_e
     const RepU R(Rs);
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int gt = 1 << lg, lq = lg - kFTLog;
-    const bool apart = F32 && R.M32;
+    constexpr bool apart = F32;
     const int ngroups = (R.n + gt - 1) / gt;
     // one group per workgroup, or several when the grid is bounded (HBM frontier regions)
     for (int grp = blockIdx.x; grp < ngroups; grp += gridDim.x) {
@@ -364,11 +369,13 @@ __global__ void __launch_bounds__(kGroupBlock) __attribute__((amdgpu_waves_per_e
             energy_near(R, S, near_n, lg, near);
         });
         // the lanes of a wave that share targets, then the waves
-        for (int off = 1 << lq; off < 64; off <<= 1)
+        for (int off = apart ? gt : 1 << lq; off < 64; off <<= 1)
 #pragma unroll
             for (int u = 0; u < kFT; ++u) far[u] += __shfl_xor(far[u], off, 64);
         for (int off = gt; off < 64; off <<= 1) near += __shfl_xor(near, off, 64);
-        if (lane < (1 << lq))
+        if (apart) {
+            if (lane < gt) S.red[w][lane][0] = far[0];
+        } else if (lane < (1 << lq))
 #pragma unroll
             for (int u = 0; u < kFT; ++u) S.red[w][kFT * lane + u][0] = far[u];
         if (lane < gt) S.red[w][lane][1] = near;

@@ -20,7 +20,7 @@ CASES = [  # system, ions, order, theta, N_0, frontier entries on chip
     ("cube", 1, 4, 0.5, 0, 4096), ("cube", 2, 4, 0.5, 0, 4096), ("cube", 5, 3, 0.9, 1, 4096),
     ("cube", 17, 10, 0.7, 0, 4096), ("cube", 4095, 3, 0.5, 0, 4096), ("cube", 4097, 3, 0.5, 8, 64),
     ("colloid", 4099, 6, 0.3, 0, 64), ("cube", 16383, 2, 0.6, 0, 4096), ("cube", 16387, 2, 0.6, 0, 4096),
-    ("colloid", 777, 8, 0.0, 0, 4096),
+    ("colloid", 777, 8, 0.0, 0, 4096), ("cube", 2048, 3, 0.5, 0, 4096), ("cube", 2049, 3, 0.5, 0, 4096),
 ]
 
 
@@ -55,7 +55,7 @@ def test_energy_and_potentials_match_oracle(kind, n, p, theta, n0, front):
     assert abs(E - Eo) <= 1e-12 * np.sum(np.abs(q) * mag)
 
 
-@pytest.mark.parametrize("n", [61, 4100])
+@pytest.mark.parametrize("n", [61, 2048, 2049, 4100])
 def test_single_precision_far_field_excludes_the_own_image_exactly(n):
     """Where every far cell but the one with the own image is replaced by its single-precision
     value, the potential stays within that rounding of the FP64 one."""
