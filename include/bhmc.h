@@ -318,8 +318,10 @@ bhmc_status bhmc_phase_ticks(bhmc_tree* tree, uint64_t* ticks, int32_t n, int32_
  * keeps up to lds_entries frontier entries on chip (64..4096; 4096 after
  * build).  With allow_spill = 1 (the default) a level that outgrows them
  * continues in HBM regions the library allocates the first time this happens
- * (per handle, 8 B per cell of the largest replica per workgroup region, one
- * region per workgroup of a launch), and the call that stopped runs again; a
+ * (per handle; with width the cells of the widest level of its trees and m the
+ * moves per round its replicas allow, the larger of 8 m width B for each
+ * workgroup of a Metropolis launch and 3 width B for each of 512 workgroups of
+ * an energy or gradient), and the call that stopped runs again; a
  * traversal then never fails for lack of frontier space, so theta = 0 (the
  * direct sum) works at any size.  With allow_spill = 0 such a call returns
  * BHMC_ESTACK instead.  The results do not depend on where the frontier lives. */

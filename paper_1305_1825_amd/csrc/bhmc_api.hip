@@ -163,8 +163,8 @@ struct bhmc_tree {
     double* scratch = nullptr;       // device address of the fixed scratch array on the handle's device
     // HBM frontier regions, allocated the first time a traversal level outgrows its LDS capacity
     uint32_t* spill = nullptr;
-    int spill_regions = 0;
-    long long spill_words = 0;       // 32-bit words per region
+    int spill_regions = 0, gspill_regions = 0;            // of the move kernels, of energies and gradients
+    long long spill_words = 0, gspill_words = 0;         // 32-bit words per region
     int fcap = 4096;                 // frontier entries a level keeps in LDS
     int allow_spill = 1;
     bool energy_bounded = false;     // energy / gradient launches keep their grid within the regions
@@ -434,29 +434,45 @@ static bhmc_status download(bhmc_tree* t) {
     return BHMC_OK;
 }
 
-// Frontier regions in HBM for every workgroup that may need one: one per workgroup of the
-// Metropolis launch and of a bounded energy / gradient launch.  A region holds the two levels a
-// traversal keeps at once of its widest possible frontier: 4 targets x every cell (energy,
-// 32-bit entries), or every cell with a 32-bit cell and a 64-bit mask word (gradient).  Sized
-// for the replicas' current cell counts; returns whether it had to grow.
+// Frontier regions in HBM: the launches of a handle follow one another on its stream, so the move
+// kernels and the energy and gradient kernels cut the same buffer into regions of their own.
+// A region holds the two levels a traversal keeps at once of its widest possible frontier, the
+// widest level of the current trees opened in full:
+//   move kernels: a 32-bit entry per (cell, move of a round), one region per workgroup;
+//   energy and gradient (a bounded grid): per opened cell, one for each eight cells of the next
+//   level, its first child and a 64-bit mask word.
+// Returns whether it had to grow.
 static bhmc_status ensure_spill(bhmc_tree* t, bool* grown) {
     *grown = false;
-    long long maxc = 1;
-    for (int r = 0; r < t->R; ++r) maxc = std::max<long long>(maxc, t->host[r].ncell);
-    const long long words = (8 * maxc + 16 + 63) & ~63ll;
+    long long width = 1;
+    for (int r = 0; r < t->R; ++r) {
+        const Rep& h = t->host[r];
+        for (int l = 0; l <= h.depth && l <= bhmc::kMaxDepth; ++l)
+            width = std::max<long long>(width, h.level_start[l + 1] - h.level_start[l]);
+    }
+    auto up = [](long long v) { return (v + 63) & ~63ll; };
+    const long long moves = t->rounds_ok ? t->ops->moves_per_round : 1;
+    const long long words = up(2 * moves * width + 16), gwords = up(6 * ((width + 7) / 8) + 16);
     int dev = 0, ncu = 0;
     hipGetDevice(&dev);
     hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
-    const int regions = std::max(std::max(512, 2 * ncu), t->mc_grid);
-    if (t->spill && words <= t->spill_words && regions <= t->spill_regions) return BHMC_OK;
-    if (t->spill) { hipFree(t->spill); t->spill = nullptr; t->spill_words = 0; t->spill_regions = 0; }
-    HIP_TRY(hipMalloc(&t->spill, sizeof(uint32_t) * (size_t)words * regions));
+    const int gregions = std::max(512, 2 * ncu), regions = std::max(std::min(t->R, gregions), t->mc_grid);
+    if (t->spill && words <= t->spill_words && regions <= t->spill_regions && gwords <= t->gspill_words) return BHMC_OK;
+    // the old buffer goes only once there is a new one: the descriptors point into it
+    uint32_t* fresh = nullptr;
+    HIP_TRY(hipMalloc(&fresh, sizeof(uint32_t) * (size_t)std::max(words * regions, gwords * gregions)));
+    if (t->spill) hipFree(t->spill);
+    t->spill = fresh;
     t->spill_words = words;
+    t->gspill_words = gwords;
     t->spill_regions = regions;
+    t->gspill_regions = gregions;
     for (int r = 0; r < t->R; ++r) {
         t->host[r].spill = t->spill;
         t->host[r].spill_words = words;
         t->host[r].spill_regions = regions;
+        t->host[r].gspill_words = gwords;
+        t->host[r].gspill_regions = gregions;
     }
     *grown = true;
     return BHMC_OK;
@@ -792,7 +808,7 @@ static bhmc_status finish_energy(bhmc_tree* t, int r, int n, double* E_host, con
     return BHMC_OK;
 }
 
-static int energy_grid_bound(const bhmc_tree* t) { return t->energy_bounded && t->spill ? t->spill_regions : 0; }
+static int energy_grid_bound(const bhmc_tree* t) { return t->energy_bounded && t->spill ? t->gspill_regions : 0; }
 
 extern "C" bhmc_status bhmc_energy(bhmc_tree* t, int32_t replica, double* E_host, double* phi_dev) {
     bhmc_status st = check_rep(t, replica);

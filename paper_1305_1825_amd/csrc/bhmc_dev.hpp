@@ -47,10 +47,11 @@ struct Rep {
     int level_start[kMaxLevels + 1];
     int status;                    // build status (0 or a negative bhmc_status)
     // ---- frontier spill (host): a level whose frontier outgrows fcap entries in LDS continues in
-    // the HBM region of its workgroup (blockIdx.x < spill_regions), spill_words 32-bit words each
+    // the HBM region of its workgroup (blockIdx.x < spill_regions), spill_words 32-bit words each;
+    // energies and gradients cut the same buffer into gspill_regions of gspill_words
     int fcap;
-    int spill_regions;
-    long long spill_words;
+    int spill_regions, gspill_regions;
+    long long spill_words, gspill_words;
     uint32_t* spill;
     // ---- buffers
     double4* src;                  // (x, y, z, q) per source, home copy

@@ -675,10 +675,8 @@ __device__ __forceinline__ void put_children(uint32_t* lds, uint32_t* hbm, uint3
 
 // Frontier region of this workgroup in HBM (null if none): a level whose frontier
 // outgrows its LDS capacity continues there, and so do the levels after it.
-template <class RT>
-__device__ __forceinline__ uint32_t* spill_region(const RT& R) {
-    return (R.spill && (int)blockIdx.x < R.spill_regions) ? R.spill + (size_t)blockIdx.x * (size_t)R.spill_words
-                                                          : nullptr;
+__device__ __forceinline__ uint32_t* spill_region(uint32_t* spill, int regions, long long words) {
+    return (spill && (int)blockIdx.x < regions) ? spill + (size_t)blockIdx.x * (size_t)words : nullptr;
 }
 
 template <int NTG, int BLOCK>
@@ -968,7 +966,7 @@ __device__ int traverse_mc(const RepU& R, Trav<2, BLOCK>& S, int* cnt2, Hook&& h
     int cur = 0, fs = fs0, far_n = 0, near_n = 0, nflag = 0, buf = 0;
     bool failed = false, frontier_full = false;
     // the frontier: LDS up to lcap entries, then HBM (see traverse)
-    uint32_t* const gfr = spill_region(R);
+    uint32_t* const gfr = spill_region(R.spill, R.spill_regions, R.spill_words);
     const int gcap = gfr ? (int)(R.spill_words / 2 < 0x7FFFFFFF ? R.spill_words / 2 : 0x7FFFFFFF) : 0;
     const int lcap = R.fcap < TS::FCAP ? R.fcap : TS::FCAP;
     bool rg = false, wg = false;

@@ -159,8 +159,9 @@ __device__ __forceinline__ void group_traverse(const RepU& R, GS& S, bool flag_a
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const bool imgs = R.images != 0;
     // levels past the LDS capacity go to this workgroup's HBM region: first children, then masks
-    uint32_t* const gfr = spill_region(R);
-    const int gcap = gfr ? (int)((R.spill_words - 2) / 6 < 0x7FFFFFFF ? (R.spill_words - 2) / 6 : 0x7FFFFFFF) : 0;
+    const long long gw = uni(R.d.gspill_words);
+    uint32_t* const gfr = spill_region(R.spill, uni(R.d.gspill_regions), gw);
+    const int gcap = gfr ? (int)((gw - 2) / 6 < 0x7FFFFFFF ? (gw - 2) / 6 : 0x7FFFFFFF) : 0;
     int* const gpl = (int*)gfr;
     uint64_t* const gpm = gfr ? (uint64_t*)(gfr + 2 * (size_t)gcap) : nullptr;
     const int lcap = R.fcap / 8 < GS::FCAP ? R.fcap / 8 : GS::FCAP;

@@ -332,7 +332,7 @@ __device__ void traverse_mb(const RepU& R, BTrav<BLOCK>& S, BMoves& MV, Hook&& h
     for (int k = 0; k < kBT; ++k) acc[k] = 0.0;
     int cur = 0, fs = MV.fs0, far_n = 0, near_n = 0, nflag = 0, buf = 0;
     bool failed = false, frontier_full = false;
-    uint32_t* const gfr = spill_region(R);
+    uint32_t* const gfr = spill_region(R.spill, R.spill_regions, R.spill_words);
     const int gcap = gfr ? (int)(R.spill_words / 2 < 0x7FFFFFFF ? R.spill_words / 2 : 0x7FFFFFFF) : 0;
     const int lcap = R.fcap < TS::FCAP ? R.fcap : TS::FCAP;
     bool rg = false, wg = false;
