@@ -7,8 +7,9 @@
 // every source below it directly (the N_0 rule), targets whose own image, and whose own ion,
 // lies inside.  Thread j of a chunk classifies child j mod 8 of entry j / 8.  Each target
 // takes exactly the decisions its own traversal would take (Sec. 3.2): a cell that passes or
-// fails the MAC for the group's bounding sphere, with a margin far above rounding, does so
-// for every target, and only the cells between are tested target by target.
+// fails the MAC for the group's bounding sphere, widened by more than the rounding of the
+// sphere and of the test, does so for every target, and only the cells between are tested
+// target by target.
 // Far cells go to a list with their target masks, near leaves likewise; the lists are
 // evaluated when they fill up and at the end.
 //
@@ -327,7 +328,10 @@ __device__ __forceinline__ void group_targets(const RepU& R, GS& S, const int* o
         if (tid == 0) {
             const double ex = 0.5 * (hx - lx), ey = 0.5 * (hy - ly), ez = 0.5 * (hz - lz);
             S.ctr[0] = 0.5 * (lx + hx); S.ctr[1] = 0.5 * (ly + hy); S.ctr[2] = 0.5 * (lz + hz);
-            S.ctr[3] = sqrt(ex * ex + ey * ey + ez * ez) * (1.0 + 1e-9);
+            // the midpoints round in the coordinates' own last place, which far from the origin is
+            // large against a deep cell: at most 2^-53 of the coordinate an axis
+            const double m = fmax(fabs(lx), fabs(hx)) + fmax(fabs(ly), fabs(hy)) + fmax(fabs(lz), fabs(hz));
+            S.ctr[3] = sqrt(ex * ex + ey * ey + ez * ez) * (1.0 + 1e-9) + 0x1p-52 * m;
         }
         if (!ok) S.err = kErrBuildPerm;
     }
