@@ -786,10 +786,13 @@ __device__ __forceinline__ int near_search(const int* pre, int near_n, int f) {
 }
 
 // The same for every slot at once, where they fit: each entry writes its number to its
-// slots (a handful), so a slot finds it in one read instead of a search of dependent reads.
+// slots, so a slot finds it in one read instead of a search of dependent reads.  Entries of more
+// than 64 slots on average (leaf capacities in use are 8 to 32) are left to the search: a lane
+// would write an entry's slots one after another, all of them where a system is one leaf.
+__device__ __forceinline__ bool near_listed(int near_n, int total, int cap) { return total <= cap && total <= 64 * near_n; }
 template <int BLOCK>
 __device__ __forceinline__ void near_list(uint16_t* own, const int* pre, int near_n, int total, int cap) {
-    if (total > cap) return;  // uniform
+    if (!near_listed(near_n, total, cap)) return;  // uniform
     for (int j = threadIdx.x; j < near_n; j += BLOCK) {
         const int end = j + 1 < near_n ? pre[j + 1] : total;
         for (int f = pre[j]; f < end; ++f) own[f] = (uint16_t)j;
@@ -927,7 +930,7 @@ template <int BLOCK>
 __device__ __forceinline__ void near_pass_mc(const RepU& R, Trav<2, BLOCK>& S, int near_n, int total,
                                              double (&acc)[2]) {
     const int n_ion = R.n;
-    const bool listed = total <= Trav<2, BLOCK>::OWNCAP;  // uniform
+    const bool listed = near_listed(near_n, total, Trav<2, BLOCK>::OWNCAP);  // uniform
     for (int f = threadIdx.x; f < total; f += BLOCK) {
         const int lo = listed ? (int)S.near_own[f] : near_search(S.near_pre, near_n, f);
         const uint32_t e = S.nearl[lo];

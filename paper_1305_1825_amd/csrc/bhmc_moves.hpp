@@ -245,7 +245,7 @@ template <int BLOCK>
 __device__ __forceinline__ void near_pass_mb(const RepU& R, BTrav<BLOCK>& S, BMoves& MV, int near_n, int total,
                                              double (&acc)[kBT]) {
     const int n_ion = R.n;
-    const bool listed = total <= BTrav<BLOCK>::OWNCAP;  // uniform
+    const bool listed = near_listed(near_n, total, BTrav<BLOCK>::OWNCAP);  // uniform
     const int tid = fresh_tid();
     for (int f = tid; f < total; f += BLOCK) {
         const int lo = listed ? (int)S.near_own[f] : near_search(S.near_pre, near_n, f);

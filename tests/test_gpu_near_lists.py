@@ -1,8 +1,8 @@
-"""Near leaves around the sizes at which their slots are listed another way: by one lane, by the
-entry's wave, or (more slots than the list holds) found by search.  A system in one leaf has every
-source in one near entry a move: 32 slots and 33; 512 ions and 513 in rounds of eight moves, 2,048
-and 2,049 one move at a time for the list's capacity.  Leaves of a split system with many, few and
-no members between."""
+"""Near leaves around the sizes at which their slots are found another way, from a list of every
+slot's leaf or by search: more than 64 slots an entry on average, or more than the list holds.  A
+system in one leaf has every source in one near entry a move (64 ions and 65); leaves of a split
+system with many, few and no members, on both sides of the average and of the list's capacity
+(2,048 slots one move at a time, 4,096 in rounds)."""
 import numpy as np
 import pytest
 
@@ -17,8 +17,8 @@ if not torch.cuda.is_available():  # pragma: no cover
 
 from paper_1305_1825_amd import bhmc  # noqa: E402
 
-CASES = [(31, 5000), (32, 5000), (33, 5000), (65, 5000), (512, 5000), (513, 5000), (2048, 5000), (2049, 5000),
-         (1500, 400), (1500, 33), (3000, 700)]
+CASES = [(2, 5000), (64, 5000), (65, 5000), (513, 5000), (2049, 5000), (1500, 400), (1500, 33), (3000, 60), (3000, 64),
+         (3000, 70), (6000, 60)]
 
 
 def system(n, leaf):
