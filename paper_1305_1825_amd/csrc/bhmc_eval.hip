@@ -543,22 +543,17 @@ __device__ __forceinline__ double far_eval_f(double Rx, double Ry, double Rz, co
     return (double)acc;
 }
 
-// Far value of cell c at (tx, ty, tz): FP32 from M32 when the replica keeps it.  The kernels
-// are instantiated twice: F32 = false for handles without such a replica, whose registers the
-// FP32 recurrence (every T_n of eq. 3.4 at once) would otherwise set.
-template <bool F32>
-__device__ __forceinline__ double far_value(const RepU& R, int c, double tx, double ty, double tz) {
-    if (F32 && R.M32) {
-        const double4 g = gload(R.cgeo + c);
-        return far_eval_f(g.x - tx, g.y - ty, g.z - tz, R.M32 + (size_t)c * MSTR);
-    }
-    return far_row(grow(R.H + (size_t)c * HSTR), tx, ty, tz);
-}
-// The same at the two targets of a move.
+// Kernels with far cells are instantiated twice: F32 = false for handles without a replica that
+// keeps M32, whose registers the FP32 recurrence (every T_n of eq. 3.4 at once) would otherwise set.
+// That recurrence is run once for each target of a move either way: from order 5 on a lane takes one
+// target (one after the other in a lane against a lane each: 400 moves of 6,000 ions, p = 10, 18.1 and
+// 13.8 ms, p = 6 4.00 and 3.73 ms), below it both (p = 2: 2.39 and 2.50 ms).
+constexpr bool kF32Apart = P > 4;
+// Values at the two targets of a move.
 template <bool F32>
 __device__ __forceinline__ void far_value2(const RepU& R, int c, const double (&tx)[2], const double (&ty)[2],
                                            const double (&tz)[2], double (&v)[2]) {
-    if (F32 && R.M32) {
+    if (F32 && !kF32Apart && R.M32) {
         const double4 g = gload(R.cgeo + c);
         v[0] = far_eval_f(g.x - tx[0], g.y - ty[0], g.z - tz[0], R.M32 + (size_t)c * MSTR);
         __builtin_amdgcn_sched_barrier(0);  // one recurrence's T_n in registers at a time
@@ -902,18 +897,29 @@ constexpr int kMaskSh = 24, kDirSh = 26;
 template <bool F32, int BLOCK>
 __device__ __forceinline__ void far_pass_mc(const RepU& R, Trav<2, BLOCK>& S, int far_n, int nflag,
                                             double (&acc)[2]) {
-    for (int j = threadIdx.x; j < far_n; j += BLOCK) {
-        const uint32_t e = S.farl[j];
-        const int c = (int)(e & kCellMask);
-        if (c >= R.ncell) { S.err = kErrFarCell; continue; }
-        const double tx[2] = {S.tx[0], S.tx[1]}, ty[2] = {S.ty[0], S.ty[1]}, tz[2] = {S.tz[0], S.tz[1]};
-        double v[2];
-        far_value2<F32>(R, c, tx, ty, tz, v);
-        acc[0] += ((e >> kMaskSh) & 1u) ? v[0] : 0.0;
-        acc[1] += ((e >> kMaskSh) & 2u) ? v[1] : 0.0;
+    const int t = (int)(threadIdx.x & 1);
+    if (F32 && kF32Apart && R.M32) {
+        for (int j2 = threadIdx.x; j2 < 2 * far_n; j2 += BLOCK) {
+            const uint32_t e = S.farl[j2 >> 1];
+            if (!((e >> (kMaskSh + t)) & 1u)) continue;
+            const int c = (int)(e & kCellMask);
+            if (c >= R.ncell) { S.err = kErrFarCell; continue; }
+            const double4 g = gload(R.cgeo + c);
+            add_to<2>(acc, t, far_eval_f(g.x - S.tx[t], g.y - S.ty[t], g.z - S.tz[t], R.M32 + (size_t)c * MSTR));
+        }
+    } else {
+        for (int j = threadIdx.x; j < far_n; j += BLOCK) {
+            const uint32_t e = S.farl[j];
+            const int c = (int)(e & kCellMask);
+            if (c >= R.ncell) { S.err = kErrFarCell; continue; }
+            const double tx[2] = {S.tx[0], S.tx[1]}, ty[2] = {S.ty[0], S.ty[1]}, tz[2] = {S.tz[0], S.tz[1]};
+            double v[2];
+            far_value2<F32>(R, c, tx, ty, tz, v);
+            acc[0] += ((e >> kMaskSh) & 1u) ? v[0] : 0.0;
+            acc[1] += ((e >> kMaskSh) & 2u) ? v[1] : 0.0;
+        }
     }
     // the cells holding an excluded source, less what it adds: a lane per target
-    const int t = (int)(threadIdx.x & 1);
     for (int j2 = threadIdx.x; j2 < 2 * nflag; j2 += BLOCK) {
         const uint32_t e = S.flagl[j2 >> 1];
         if (!((e >> (kMaskSh + t)) & 1u)) continue;

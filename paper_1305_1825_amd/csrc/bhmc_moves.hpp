@@ -216,17 +216,29 @@ template <bool F32, int BLOCK>
 __device__ __forceinline__ void far_pass_mb(const RepU& R, BTrav<BLOCK>& S, const BMoves& MV, int far_n, int nflag,
                                             double (&acc)[kBT]) {
     const int tid = fresh_tid();
-    for (int j = tid; j < far_n; j += BLOCK) {
-        const uint32_t e = S.farl[j];
-        const int c = (int)(e & kCellMask), b = mv_of(e);
-        if (c >= R.ncell) { S.err = kErrFarCell; continue; }
-        const double tx[2] = {MV.tx[2 * b], MV.tx[2 * b + 1]}, ty[2] = {MV.ty[2 * b], MV.ty[2 * b + 1]};
-        const double tz[2] = {MV.tz[2 * b], MV.tz[2 * b + 1]};
-        double v[2];
-        far_value2<F32>(R, c, tx, ty, tz, v);
-        add_pair(acc, b, ((e >> kOpSh) & 1u) ? v[0] : 0.0, ((e >> kOpSh) & 2u) ? v[1] : 0.0);
-    }
     const int tb = tid & 1;
+    if (F32 && kF32Apart && R.M32) {
+        for (int j2 = tid; j2 < 2 * far_n; j2 += BLOCK) {
+            const uint32_t e = S.farl[j2 >> 1];
+            if (!((e >> (kOpSh + tb)) & 1u)) continue;
+            const int c = (int)(e & kCellMask), b = mv_of(e), t = 2 * b + tb;
+            if (c >= R.ncell) { S.err = kErrFarCell; continue; }
+            const double4 g = gload(R.cgeo + c);
+            const double v = far_eval_f(g.x - MV.tx[t], g.y - MV.ty[t], g.z - MV.tz[t], R.M32 + (size_t)c * MSTR);
+            add_pair(acc, b, tb ? 0.0 : v, tb ? v : 0.0);
+        }
+    } else {
+        for (int j = tid; j < far_n; j += BLOCK) {
+            const uint32_t e = S.farl[j];
+            const int c = (int)(e & kCellMask), b = mv_of(e);
+            if (c >= R.ncell) { S.err = kErrFarCell; continue; }
+            const double tx[2] = {MV.tx[2 * b], MV.tx[2 * b + 1]}, ty[2] = {MV.ty[2 * b], MV.ty[2 * b + 1]};
+            const double tz[2] = {MV.tz[2 * b], MV.tz[2 * b + 1]};
+            double v[2];
+            far_value2<F32>(R, c, tx, ty, tz, v);
+            add_pair(acc, b, ((e >> kOpSh) & 1u) ? v[0] : 0.0, ((e >> kOpSh) & 2u) ? v[1] : 0.0);
+        }
+    }
     for (int j2 = tid; j2 < 2 * nflag; j2 += BLOCK) {
         const uint32_t e = S.flagl[j2 >> 1];
         if (!((e >> (kOpSh + tb)) & 1u)) continue;
