@@ -490,6 +490,7 @@ __device__ __forceinline__ void cart_rec(double (&T)[NTERM], double Rx, double R
     if constexpr (K < NTERM) {
         if constexpr (K > 0) t_step<K>(T, Rx, Ry, Rz, ir2);
         acc = fma(T[K], Mc[K], acc);
+        if constexpr (K % 2 == 1) __builtin_amdgcn_sched_barrier(0);  // or the moments are all loaded ahead
         cart_rec<K + 1>(T, Rx, Ry, Rz, ir2, Mc, acc);
     }
 }
@@ -2289,14 +2290,19 @@ __global__ void __launch_bounds__(256) k_eline(Rep* reps, int r, double* phi, do
 }
 
 // Ions per group of the energy traversal: 16 once that fills the chip, fewer (more workgroups)
-// for small systems; 4 only as long as all its workgroups run at once (two on each of 256 CUs).
-// (2,500 ions, p = 4: 52 us in groups of 4, where the last 113 of 625 run alone; single precision 55
-// against 49 in groups of 8.)  Measured with 4 / 8 / 16: 500 ions 39 / 44 / 53 us, 2,000 43 / 47 / 61,
+// for small systems; 4 only as long as all its workgroups run at once (energy_groups_per_cu on
+// each of 256 CUs: up to 2,048 ions in FP64, 4,096 in single precision up to order 4).
+// (2,500 ions, p = 4: 52 us in groups of 4, where the last 113 of 625 run alone.)
+// Measured with 4 / 8 / 16: 500 ions 39 / 44 / 53 us, 2,000 43 / 47 / 61,
 // 4,500 92 / 79 / 85, 10,000 176 / 139 / 147, 30,000 474 / 326 / 280, 100,000 1558 / 1068 / 898.
-int energy_group_log2(int n) { return n >= 16384 ? 4 : (n > 2048 ? 3 : 2); }
+// Single precision, 2,500 ions (p = 4, theta = 0.5, leaf 8): 51.5 us in groups of 8 with two
+// workgroups a CU, 42.4 in groups of 4 with four.
+int energy_group_log2(int n, int far32) {
+    return n >= 16384 ? 4 : (n > 4 * 256 * energy_groups_per_cu(far32 != 0) ? 3 : 2);
+}
 
 void run_energy(hipStream_t s, Rep* reps, int r, int n, double* phi, double* eterm, int max_grid, int nline, int far32) {
-    const int lg = energy_group_log2(n);
+    const int lg = energy_group_log2(n, far32);
     int grid = (n + (1 << lg) - 1) >> lg;
     if (max_grid > 0 && grid > max_grid) grid = max_grid;
     if (far32) hipLaunchKernelGGL(k_energy<true>, dim3(grid), dim3(kGroupBlock), 0, s, reps, r, lg, phi, eterm);

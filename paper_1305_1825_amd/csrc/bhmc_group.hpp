@@ -352,8 +352,14 @@ __device__ __forceinline__ double ion_term(const RepU& R, double x, double y, do
 // Potential at every ion, with the ion and its image excluded, and each ion's term of
 //   E / l_B = 1/2 q phi + 1/2 gamma a q^2 / (r^2 - a^2) + Q q / r.
 // The ion itself is never in a far cell of its own traversal (theta < 1); its image may be,
-// and is then taken back out through that cell's expansion (flagged_value where the far
-// cells are taken in single precision).
+// and is then taken back out through that cell's expansion (with that cell's value in FP64 from
+// the moments where the far cells are taken in single precision).
+//
+// Workgroups a CU that the registers leave room for, a wave of each to a SIMD: in single precision 4
+// up to order 4 (127 registers) and 3 at order 5 (146).  Small systems are bound by latencies, which
+// they share.  (Holding the compiler to it by attribute cost up to 8 % at orders 2 and 3, which have
+// registers to spare.)
+constexpr int energy_groups_per_cu(bool f32) { return !f32 || P > 5 ? 2 : (P > 4 ? 3 : 4); }
 template <bool F32>
 __global__ void __launch_bounds__(kGroupBlock) __attribute__((amdgpu_waves_per_eu(2))) k_energy(Rep* reps, int r, int lg, double* phi, double* eterm) {
     __shared__ GroupShared<false> S;
@@ -394,12 +400,10 @@ __global__ void __launch_bounds__(kGroupBlock) __attribute__((amdgpu_waves_per_e
             const int c = S.flag_cell[tid];
             if (c >= 0) {
                 const double4 k = gload(R.src + R.n + ion);
-                if (apart) {
-                    ph += flagged_value<F32>(R, c, x, y, z, false, k, true, k);
-                } else {
-                    const double4 g = gload(R.cgeo + c);
-                    ph -= k.w * point_expansion(g.x - x, g.y - y, g.z - z, k.x - g.x, k.y - g.y, k.z - g.z);
-                }
+                const double4 g = gload(R.cgeo + c);
+                // (inline: as a call it set the kernel's registers, 214 for 127 at order 4)
+                if (apart) ph += cart_eval(g.x - x, g.y - y, g.z - z, grow(R.M + (size_t)c * MSTR));
+                ph -= k.w * point_expansion(g.x - x, g.y - y, g.z - z, k.x - g.x, k.y - g.y, k.z - g.z);
             }
             if (S.err) {
                 ph = __builtin_nan("");
