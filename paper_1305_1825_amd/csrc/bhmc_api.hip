@@ -575,14 +575,14 @@ static bhmc_status build_list(bhmc_tree* t, const std::vector<int>& list, const 
                                   flag);
         bhmc::launch_sort_wide(t->stream, t->reps, list[0], nsrc0, t->wide_buf);
         bhmc::launch_count_wide(t->stream, t->reps, list[0], nsrc0, wt);
+        bhmc::launch_ion_order(t->stream, 1, t->reps, dlist, nsrc0);
     } else {
         bhmc::launch_sources(t->stream, nr, t->reps, dlist, x, y, z, q, x ? doff : nullptr);
         bhmc::launch_sort(t->stream, nr, t->reps, dlist);
-        bhmc::launch_count(t->stream, nr, t->reps, dlist);
+        int max_nsrc = 1;
+        for (int r : list) max_nsrc = std::max(max_nsrc, t->host[r].nsrc);
+        bhmc::launch_count(t->stream, nr, t->reps, dlist, max_nsrc);
     }
-    int max_nsrc = 1;
-    for (int r : list) max_nsrc = std::max(max_nsrc, t->host[r].nsrc);
-    bhmc::launch_ion_order(t->stream, nr, t->reps, dlist, max_nsrc);
     HIP_TRY(hipGetLastError());
     if ((st = download(t))) return st;
     for (int r : list) {
@@ -604,7 +604,6 @@ static bhmc_status build_list(bhmc_tree* t, const std::vector<int>& list, const 
         bhmc::launch_leaves_wide(t->stream, t->reps, list[0], h.nleaf, (int*)(wt.list + h.nsplit));
     } else {
         bhmc::launch_topology(t->stream, nr, t->reps, dlist);
-        bhmc::launch_leaves(t->stream, nr, t->reps, dlist);
     }
     HIP_TRY(hipGetLastError());
     if ((st = download(t))) return st;  // cells per level size the moment launches

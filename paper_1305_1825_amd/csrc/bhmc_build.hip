@@ -4,9 +4,9 @@
 //
 //   k_sources   ions copied in, Kelvin (and line) images made, confinement checked, keys
 //   k_sort      stable LSD radix sort of (key, source) in LDS-ranked tiles
-//   k_count     number of split cells per level, straight from sorted keys
-//   k_topology  cells level by level (Sec. 3.2 bisection, adaptive by count)
-//   k_leaves    leaf index arrays (pool) and tracking information (Sec. 3.3)
+//   k_count     number of split cells per level, straight from sorted keys, and the ions in key order
+//   k_topology  cells level by level (Sec. 3.2 bisection, adaptive by count), then the leaf index
+//               arrays (pool) and tracking information (Sec. 3.3)
 //   k_p2m       leaf moments M^n = sum q (r - c)^n            (eq. 3.3)
 //   k_m2m       parent moments from children by the binomial shift, one wave per cell
 #include "bhmc_dev.hpp"
@@ -304,10 +304,26 @@ __device__ __forceinline__ void set_cell_counts(Rep& R, int total, int depth) {
 // and l < max_depth; such a cell's parent holds at least as many, so it was
 // split too.  The split cells of level l are therefore the runs of equal
 // l-prefix longer than leaf_cap.
+//
+// order: the list of the ions in key order as well (k_ion_count and k_ion_fill do it over a grid):
+// a thread takes a run of consecutive positions, one scan places them.
 __global__ void __launch_bounds__(kBuildBlock)
-k_count(Rep* reps, const int* rep_list) {
+k_count(Rep* reps, const int* rep_list, int order) {
     Rep& R = reps[rep_list ? rep_list[blockIdx.x] : blockIdx.x];
     const int n = R.nsrc;
+    if (order) {
+        __shared__ uint64_t wsum[kBuildBlock / 64 + 1];
+        const int per = (n + kBuildBlock - 1) / kBuildBlock;
+        const int k0 = std::min(n, (int)threadIdx.x * per), k1 = std::min(n, k0 + per);
+        int mine = 0;
+        for (int k = k0; k < k1; ++k) mine += (unsigned)R.perm[k] < (unsigned)R.n ? 1 : 0;
+        uint64_t tot;
+        int at = (int)block_exscan<kBuildBlock>((uint64_t)mine, wsum, tot);
+        for (int k = k0; k < k1; ++k) {
+            const int i = R.perm[k];
+            if ((unsigned)i < (unsigned)R.n && at < R.n) R.iord[at++] = i;
+        }
+    }
     __shared__ int cnt;
     __shared__ int total;
     __shared__ int depth;
@@ -408,8 +424,48 @@ __device__ __forceinline__ void cell_geometry(const Rep& R, int level, uint64_t 
     g.w = h;
 }
 
+// Members of leaf l in sorted order, with their tracking entries.
+__device__ __forceinline__ void fill_leaf(Rep& R, int l) {
+    const int c = R.lcell[l];
+    if (c < 0 || c >= R.ncell) { R.status = -8; return; }
+    const int b = R.cbegin[c], e = R.cend[c], base = R.lbase[l];
+    if (b < 0 || e > R.nsrc || b > e || base + (e - b) > R.pool) { R.status = -8; return; }
+    R.cm[c].z = base;
+    for (int k = b; k < e; ++k) {
+        const int s = R.perm[k];
+        if (s < 0 || s >= R.nsrc) { R.status = -8; continue; }
+        R.pool4[base + k - b] = R.src[s];
+        R.pidx[base + k - b] = s;
+        R.track[s] = make_int2(c, k - b);
+    }
+}
+
+// Leaf index arrays: bases by an exclusive scan of the capacities; members
+// in sorted order; tracking = (leaf, slot) of every source.
+__device__ __forceinline__ void leaf_arrays(Rep& R, uint64_t* wsum) {
+    __shared__ int carry;
+    if (threadIdx.x == 0) carry = 0;
+    __syncthreads();
+    const int nl = R.nleaf;
+    for (int base = 0; base < nl; base += kBuildBlock) {
+        const int l = base + threadIdx.x;
+        const int cap = l < nl ? R.lcap[l] : 0;
+        uint64_t tot;
+        const uint64_t ex = block_exscan<kBuildBlock>((uint64_t)cap, wsum, tot);
+        const int c0 = carry;
+        if (l < nl) R.lbase[l] = c0 + (int)ex;
+        __syncthreads();
+        if (threadIdx.x == 0) carry = c0 + (int)tot;
+        __syncthreads();
+    }
+    if (threadIdx.x == 0 && carry > R.pool) R.status = -5;
+    __syncthreads();
+    if (carry > R.pool || R.status) return;  // uniform: nothing is written past the pool
+    for (int l = threadIdx.x; l < nl; l += blockDim.x) fill_leaf(R, l);
+}
+
 // Cells in level order; the children of a split cell are consecutive in digit
-// order; leaves are numbered in cell order.
+// order; leaves are numbered in cell order.  Then the leaf index arrays.
 __global__ void __launch_bounds__(kBuildBlock)
 k_topology(Rep* reps, const int* rep_list) {
     Rep& R = reps[rep_list ? rep_list[blockIdx.x] : blockIdx.x];
@@ -487,6 +543,8 @@ k_topology(Rep* reps, const int* rep_list) {
         if (s_next != R.ncell || s_leaf != R.nleaf) R.status = -5;
         R.depth = level - 1;
     }
+    __syncthreads();
+    leaf_arrays(R, wsum);
 }
 
 // The same cells for one large replica over a grid, from the bitmaps: split cell number s (in level
@@ -597,49 +655,6 @@ __global__ void __launch_bounds__(kBuildBlock) k_cap_bases(Rep* reps, int r, con
     uint64_t tot;
     const uint64_t ex = block_exscan<kBuildBlock>((uint64_t)cap, wsum, tot);  // its barriers publish first
     if (l < R.nleaf) R.lbase[l] = first + (int)ex;
-}
-
-// Members of leaf l in sorted order, with their tracking entries.
-__device__ __forceinline__ void fill_leaf(Rep& R, int l) {
-    const int c = R.lcell[l];
-    if (c < 0 || c >= R.ncell) { R.status = -8; return; }
-    const int b = R.cbegin[c], e = R.cend[c], base = R.lbase[l];
-    if (b < 0 || e > R.nsrc || b > e || base + (e - b) > R.pool) { R.status = -8; return; }
-    R.cm[c].z = base;
-    for (int k = b; k < e; ++k) {
-        const int s = R.perm[k];
-        if (s < 0 || s >= R.nsrc) { R.status = -8; continue; }
-        R.pool4[base + k - b] = R.src[s];
-        R.pidx[base + k - b] = s;
-        R.track[s] = make_int2(c, k - b);
-    }
-}
-
-// Leaf index arrays: bases by an exclusive scan of the capacities; members
-// in sorted order; tracking = (leaf, slot) of every source.
-__global__ void __launch_bounds__(kBuildBlock)
-k_leaves(Rep* reps, const int* rep_list) {
-    Rep& R = reps[rep_list ? rep_list[blockIdx.x] : blockIdx.x];
-    __shared__ uint64_t wsum[kBuildBlock / 64 + 1];
-    __shared__ int carry;
-    if (threadIdx.x == 0) carry = 0;
-    __syncthreads();
-    const int nl = R.nleaf;
-    for (int base = 0; base < nl; base += kBuildBlock) {
-        const int l = base + threadIdx.x;
-        const int cap = l < nl ? R.lcap[l] : 0;
-        uint64_t tot;
-        const uint64_t ex = block_exscan<kBuildBlock>((uint64_t)cap, wsum, tot);
-        const int c0 = carry;
-        if (l < nl) R.lbase[l] = c0 + (int)ex;
-        __syncthreads();
-        if (threadIdx.x == 0) carry = c0 + (int)tot;
-        __syncthreads();
-    }
-    if (threadIdx.x == 0 && carry > R.pool) R.status = -5;
-    __syncthreads();
-    if (carry > R.pool || R.status) return;  // uniform: nothing is written past the pool
-    for (int l = threadIdx.x; l < nl; l += blockDim.x) fill_leaf(R, l);
 }
 
 // The leaves of one replica, one thread per leaf over a grid.
@@ -804,8 +819,16 @@ void launch_sources(hipStream_t s, int nrep, Rep* reps, const int* list, const d
 void launch_sort(hipStream_t s, int nrep, Rep* reps, const int* list) {
     hipLaunchKernelGGL(k_sort, dim3(nrep), dim3(kBuildBlock), 0, s, reps, list);
 }
-void launch_count(hipStream_t s, int nrep, Rep* reps, const int* list) {
-    hipLaunchKernelGGL(k_count, dim3(nrep), dim3(kBuildBlock), 0, s, reps, list);
+void launch_ion_order(hipStream_t s, int nrep, Rep* reps, const int* list, int max_nsrc) {
+    const dim3 grid((max_nsrc + kOrderBlock - 1) / kOrderBlock, nrep);
+    hipLaunchKernelGGL(k_ion_count, grid, dim3(kOrderBlock), 0, s, reps, list);
+    hipLaunchKernelGGL(k_ion_fill, grid, dim3(kOrderBlock), 0, s, reps, list);
+}
+void launch_count(hipStream_t s, int nrep, Rep* reps, const int* list, int max_nsrc) {
+    // (the list of the ions: two small launches more over a grid, or up to 16 positions a thread here)
+    const int order = max_nsrc <= 16 * kBuildBlock ? 1 : 0;
+    hipLaunchKernelGGL(k_count, dim3(nrep), dim3(kBuildBlock), 0, s, reps, list, order);
+    if (!order) launch_ion_order(s, nrep, reps, list, max_nsrc);
 }
 void launch_sources_wide(hipStream_t s, Rep* reps, int r, int n, const double* x, const double* y,
                          const double* z, const double* q, const long long* ion_off, int* flag) {
@@ -832,16 +855,8 @@ void launch_topology_wide(hipStream_t s, Rep* reps, int r, int nsrc, int nsplit,
     hipLaunchKernelGGL(k_split_list, dim3((nsrc + 255) / 256), dim3(256), 0, s, reps, r, t);
     hipLaunchKernelGGL(k_topology_wide, dim3(std::max(1, (8 * nsplit + 255) / 256)), dim3(256), 0, s, reps, r, t);
 }
-void launch_ion_order(hipStream_t s, int nrep, Rep* reps, const int* list, int max_nsrc) {
-    const dim3 grid((max_nsrc + kOrderBlock - 1) / kOrderBlock, nrep);
-    hipLaunchKernelGGL(k_ion_count, grid, dim3(kOrderBlock), 0, s, reps, list);
-    hipLaunchKernelGGL(k_ion_fill, grid, dim3(kOrderBlock), 0, s, reps, list);
-}
 void launch_topology(hipStream_t s, int nrep, Rep* reps, const int* list) {
     hipLaunchKernelGGL(k_topology, dim3(nrep), dim3(kBuildBlock), 0, s, reps, list);
-}
-void launch_leaves(hipStream_t s, int nrep, Rep* reps, const int* list) {
-    hipLaunchKernelGGL(k_leaves, dim3(nrep), dim3(kBuildBlock), 0, s, reps, list);
 }
 void launch_leaves_wide(hipStream_t s, Rep* reps, int r, int nleaf, int* sums) {
     const dim3 grid((nleaf + kBuildBlock - 1) / kBuildBlock);

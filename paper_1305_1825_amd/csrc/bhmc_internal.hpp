@@ -44,7 +44,8 @@ hipError_t upload_build_tables(int p, void* pinned);  // pinned: >= 16 KiB of hi
 void launch_sources(hipStream_t s, int nrep, Rep* reps, const int* list, const double* x,
                     const double* y, const double* z, const double* q, const long long* ion_off);
 void launch_sort(hipStream_t s, int nrep, Rep* reps, const int* list);
-void launch_count(hipStream_t s, int nrep, Rep* reps, const int* list);
+// split cells, and the ions in key order (Rep.iord); max_nsrc: of the largest replica in list
+void launch_count(hipStream_t s, int nrep, Rep* reps, const int* list, int max_nsrc);
 // One large replica over a grid of workgroups, with the same results: the sort
 // uses hist (256 * (kSortGridMax + 1) ints), the sources flag (one int), zero before the
 // call and zero again after it.
@@ -68,10 +69,9 @@ void launch_sort_wide(hipStream_t s, Rep* reps, int r, int nsrc, int* hist);
 void launch_count_wide(hipStream_t s, Rep* reps, int r, int nsrc, const WideTree& t);
 void launch_topology_wide(hipStream_t s, Rep* reps, int r, int nsrc, int nsplit, const WideTree& t);
 void launch_leaves_wide(hipStream_t s, Rep* reps, int r, int nleaf, int* sums);
-// ions in key order (Rep.iord) from the sorted keys; max_nsrc: of the largest replica in list
+// ions in key order (Rep.iord) from the sorted keys over a grid
 void launch_ion_order(hipStream_t s, int nrep, Rep* reps, const int* list, int max_nsrc);
 void launch_topology(hipStream_t s, int nrep, Rep* reps, const int* list);
-void launch_leaves(hipStream_t s, int nrep, Rep* reps, const int* list);
 // host / host_list: the host mirror of the descriptors (sizes and levels as counted) and the replicas
 void launch_moments(hipStream_t s, int nrep, Rep* reps, const int* list, int nterms, int mstride,
                     const Rep* host, const int* host_list);
