@@ -129,6 +129,10 @@ static double* scratch_address(int dev) {
 }
 
 // ------------------------------------------------------------ handle
+// Device memory of a replica's arrays: an allocation of its own, or a slice of one made for all
+// replicas of a batch.
+struct Arena { char* p = nullptr; size_t cap = 0; bool own = false; };
+
 struct bhmc_tree {
     int R = 0, p = 0, nterms = 0, mstride = 0, hstride = 0;
     hipStream_t stream = nullptr;
@@ -141,7 +145,8 @@ struct bhmc_tree {
     char* pin = nullptr;             // pinned staging for every other host<->device copy
     size_t pin_bytes = 0;
     Rep* reps = nullptr;             // device descriptor table
-    std::vector<void*> arena1, arena2;
+    std::vector<Arena> arena1, arena2;  // sources; tree
+    void *block1 = nullptr, *block2 = nullptr;  // what a batch's arenas are slices of
     const bhmc::EvalOps* ops = nullptr;
     int* queue = nullptr;
     int* list_all = nullptr;         // replicas, largest first
@@ -387,11 +392,46 @@ static size_t phase1_bytes(int nsrc) {
     return b;
 }
 
+// An arena of at least `bytes`; a rebuilt tree mostly fits the one it has.
+static bhmc_status reserve(Arena& a, size_t bytes) {
+    if (a.cap >= bytes) return BHMC_OK;
+    if (a.own) hipFree(a.p);
+    a = Arena{};
+    HIP_TRY(hipMalloc(&a.p, bytes));
+    a.cap = bytes;
+    a.own = true;
+    return BHMC_OK;
+}
+
+// Arenas of a new batch's replicas cut from one allocation: beyond 1 MiB an allocation costs about
+// 10 us to make and 60 to free, and host memory freed after it waits 240.  Created and freed with an
+// allocation a replica / with one: 20 replicas of 300 to 1,700 ions, some of whose trees pass that
+// size, 1.36 / 0.69 ms, 200 of them 42.8 / 1.8 ms.  If it fails each replica gets its own.
+static void reserve_slices(std::vector<Arena>& arenas, void** block, const std::vector<int>& list,
+                           const std::vector<size_t>& bytes) {
+    size_t total = 0;
+    for (size_t k = 0; k < list.size(); ++k) {
+        if (arenas[list[k]].p) return;
+        total += align_up(bytes[k]);
+    }
+    if (list.size() < 2 || *block) return;
+    if (hipMalloc(block, total) != hipSuccess) {
+        (void)hipGetLastError();
+        *block = nullptr;
+        return;
+    }
+    char* p = (char*)*block;
+    for (size_t k = 0; k < list.size(); ++k) {
+        arenas[list[k]] = Arena{p, align_up(bytes[k]), false};
+        p += align_up(bytes[k]);
+    }
+}
+
 static bhmc_status alloc_phase1(bhmc_tree* t, int r) {
     Rep& h = t->host[r];
-    if (t->arena1[r]) { hipFree(t->arena1[r]); t->arena1[r] = nullptr; }
-    HIP_TRY(hipMalloc(&t->arena1[r], phase1_bytes(h.nsrc)));
-    Carver c{(char*)t->arena1[r]};
+    bhmc_status st = reserve(t->arena1[r], phase1_bytes(h.nsrc));
+    if (st) return st;
+    Carver c{t->arena1[r].p};
     h.src = c.take<double4>(h.nsrc);
     h.keys = c.take<uint64_t>(h.nsrc); h.ktmp = c.take<uint64_t>(h.nsrc);
     h.perm = c.take<int>(h.nsrc); h.ptmp = c.take<int>(h.nsrc); h.iord = c.take<int>(h.n);
@@ -400,16 +440,20 @@ static bhmc_status alloc_phase1(bhmc_tree* t, int r) {
     return BHMC_OK;
 }
 
+static size_t phase2_bytes(const bhmc_tree* t, int r) {
+    const Rep& h = t->host[r];
+    const size_t nc = h.ncell, nl = h.nleaf, np = h.pool;
+    return align_up(32 * nc) + align_up(16 * nc) + 4 * align_up(4 * nc) + align_up(8 * nc) +
+           align_up(8 * nc * (size_t)t->mstride) + align_up(8 * nc * (size_t)t->hstride) + 3 * align_up(4 * nl) +
+           align_up(32 * np) + align_up(4 * np) + (h.far32 ? align_up(4 * nc * (size_t)t->mstride) : 0);
+}
+
 static bhmc_status alloc_phase2(bhmc_tree* t, int r) {
     Rep& h = t->host[r];
-    if (t->arena2[r]) { hipFree(t->arena2[r]); t->arena2[r] = nullptr; }
-    const size_t nc = h.ncell, nl = h.nleaf, np = h.pool;
-    size_t b = align_up(32 * nc) + align_up(16 * nc) + 4 * align_up(4 * nc) + align_up(8 * nc) +
-               align_up(8 * nc * (size_t)t->mstride) + align_up(8 * nc * (size_t)t->hstride) + 3 * align_up(4 * nl) + align_up(32 * np) +
-               align_up(4 * np) + (h.far32 ? align_up(4 * nc * (size_t)t->mstride) : 0);
-    HIP_TRY(hipMalloc(&t->arena2[r], b));
-    Carver c{(char*)t->arena2[r]};
-    const size_t cap_bytes = b;
+    const size_t nc = h.ncell, nl = h.nleaf, np = h.pool, cap_bytes = phase2_bytes(t, r);
+    bhmc_status st = reserve(t->arena2[r], cap_bytes);
+    if (st) return st;
+    Carver c{t->arena2[r].p};
     h.cgeo = c.take<double4>(nc);
     h.cm = c.take<int4>(nc); h.cparent = c.take<int>(nc);
     h.clevel = c.take<int>(nc); h.cbegin = c.take<int>(nc); h.cend = c.take<int>(nc);
@@ -533,6 +577,8 @@ static bhmc_status current_moments(bhmc_tree* t, int r) {
     return BHMC_OK;
 }
 
+constexpr size_t kSliceMean = (size_t)4 << 20;  // bytes of a tree
+
 // Build (or rebuild) the replicas in `list`.  x == nullptr rebuilds from the
 // replicas' own current ions.
 static bhmc_status build_list(bhmc_tree* t, const std::vector<int>& list, const double* x,
@@ -545,6 +591,9 @@ static bhmc_status build_list(bhmc_tree* t, const std::vector<int>& list, const 
     bhmc_status st = h2d(t, dlist, list.data(), sizeof(int) * nr);
     if (st) return st;
     if (x && (st = h2d(t, doff, ion_off.data(), sizeof(long long) * nr))) return st;
+    std::vector<size_t> bytes;
+    for (int r : list) bytes.push_back(phase1_bytes(t->host[r].nsrc));
+    reserve_slices(t->arena1, &t->block1, list, bytes);
     for (int r : list)
         if (!t->host[r].src && (st = alloc_phase1(t, r))) return st;
     st = upload(t);
@@ -593,6 +642,10 @@ static bhmc_status build_list(bhmc_tree* t, const std::vector<int>& list, const 
         if (h.status) return fail(h.status == -1 ? BHMC_EINVAL : BHMC_EOUTSIDE, "replica %d: %s", r, status_name(h.status));
         if (h.ncell >= (1 << 24)) return fail(BHMC_EINVAL, "replica %d: %d cells exceed 2^24", r, h.ncell);
     }
+    // a slice is lost once its replica's tree outgrows it: only where trees are small
+    size_t total = 0;
+    for (size_t k = 0; k < list.size(); ++k) total += bytes[k] = phase2_bytes(t, list[k]);
+    if (total <= list.size() * kSliceMean) reserve_slices(t->arena2, &t->block2, list, bytes);
     for (int r : list) if ((st = alloc_phase2(t, r))) return st;
     if ((st = upload(t))) return st;
     if (wide) {
@@ -622,8 +675,9 @@ static void destroy(bhmc_tree* t) {
     if (t->gexec) hipGraphExecDestroy(t->gexec);
     if (t->graph) hipGraphDestroy(t->graph);
     if (t->graph_stream) hipStreamDestroy(t->graph_stream);
-    for (void* p : t->arena1) if (p) hipFree(p);
-    for (void* p : t->arena2) if (p) hipFree(p);
+    for (const Arena& a : t->arena1) if (a.own) hipFree(a.p);
+    for (const Arena& a : t->arena2) if (a.own) hipFree(a.p);
+    hipFree(t->block1); hipFree(t->block2);
     hipFree(t->reps); hipFree(t->queue); hipFree(t->list_all); hipFree(t->list_one); hipFree(t->list_rest);
     hipFree(t->sweep_add); hipFree(t->build_list); hipFree(t->build_off); hipFree(t->eterm); hipFree(t->gwork);
     hipFree(t->spill); hipFree(t->wide_buf);
@@ -662,8 +716,8 @@ static bhmc_status create(const bhmc_params* params, int32_t R, const int64_t* n
     t->io = (bhmc::MoveIO*)((char*)t->host + tail);
     t->scalar = (double*)((char*)t->host + tail + 128);
     static_assert(sizeof(bhmc::MoveIO) <= 128, "a move's result fits its place");
-    t->arena1.assign(R, nullptr);
-    t->arena2.assign(R, nullptr);
+    t->arena1.assign(R, Arena{});
+    t->arena2.assign(R, Arena{});
     t->ops = bhmc::eval_ops(t->p);
     for (int r = 0; r < R; ++r) {
         if (params[r].line_images > 0) t->has_lines = true;
