@@ -2291,7 +2291,7 @@ __global__ void __launch_bounds__(256) k_eline(Rep* reps, int r, double* phi, do
 
 // Ions per group of the energy traversal: 16 once that fills the chip, fewer (more workgroups)
 // for small systems; 4 only as long as all its workgroups run at once (energy_groups_per_cu on
-// each of 256 CUs: up to 2,048 ions in FP64, 4,096 in single precision up to order 4).
+// each of 256 CUs: up to 2,048 ions in FP64 from order 4 on, 4,096 in single precision up to order 4).
 // (2,500 ions, p = 4: 52 us in groups of 4, where the last 113 of 625 run alone.)
 // Measured with 4 / 8 / 16: 500 ions 39 / 44 / 53 us, 2,000 43 / 47 / 61,
 // 4,500 92 / 79 / 85, 10,000 176 / 139 / 147, 30,000 474 / 326 / 280, 100,000 1558 / 1068 / 898.
@@ -2306,6 +2306,8 @@ void run_energy(hipStream_t s, Rep* reps, int r, int n, double* phi, double* ete
     int grid = (n + (1 << lg) - 1) >> lg;
     if (max_grid > 0 && grid > max_grid) grid = max_grid;
     if (far32) hipLaunchKernelGGL(k_energy<true>, dim3(grid), dim3(kGroupBlock), 0, s, reps, r, lg, phi, eterm);
+    else if (kEnergyTwice && n >= kEnergyW3Min)
+        hipLaunchKernelGGL((k_energy<false, kEnergyTwice ? 3 : 2>), dim3(grid), dim3(kGroupBlock), 0, s, reps, r, lg, phi, eterm);
     else hipLaunchKernelGGL(k_energy<false>, dim3(grid), dim3(kGroupBlock), 0, s, reps, r, lg, phi, eterm);
     if (nline > 0) hipLaunchKernelGGL(k_eline, dim3((n + 255) / 256), dim3(256), 0, s, reps, r, phi, eterm);
 }

@@ -356,12 +356,19 @@ __device__ __forceinline__ double ion_term(const RepU& R, double x, double y, do
 // the moments where the far cells are taken in single precision).
 //
 // Workgroups a CU that the registers leave room for, a wave of each to a SIMD: in single precision 4
-// up to order 4 (127 registers) and 3 at order 5 (146).  Small systems are bound by latencies, which
-// they share.  (Holding the compiler to it by attribute cost up to 8 % at orders 2 and 3, which have
-// registers to spare.)
-constexpr int energy_groups_per_cu(bool f32) { return !f32 || P > 5 ? 2 : (P > 4 ? 3 : 4); }
-template <bool F32>
-__global__ void __launch_bounds__(kGroupBlock) __attribute__((amdgpu_waves_per_eu(2))) k_energy(Rep* reps, int r, int lg, double* phi, double* eterm) {
+// up to order 4 (127 registers) and 3 at order 5 (146), in FP64 4 at order 0, 3 at 1 and 2 (158), 2
+// from order 4 on (190).  Small systems are bound by latencies, which they share.  At orders 3 and 4
+// the FP64 form is there twice, W = 2 and held to W = 3 waves a SIMD (172 registers cut to 168, 190 to
+// 168 with 17 spilled): at order 3 from 2,049 ions on, at order 4 from 4,097, where groups of 8 no
+// longer all run two to a CU (p = 4, theta = 0.8, leaf 16: 6,000 ions 61 -> 48 us; 2,000 ions 35 ->
+// 38).  (Holding orders 2 and 3 of the single-precision form to 4 waves cost up to 8 %.)
+constexpr int energy_groups_per_cu(bool f32) {
+    return f32 ? (P > 5 ? 2 : (P > 4 ? 3 : 4)) : (P > 3 ? 2 : (P > 0 ? 3 : 4));
+}
+constexpr bool kEnergyTwice = P == 3 || P == 4;
+constexpr int kEnergyW3Min = P == 3 ? 2049 : 4097;
+template <bool F32, int W = 2>
+__global__ void __launch_bounds__(kGroupBlock) __attribute__((amdgpu_waves_per_eu(W))) k_energy(Rep* reps, int r, int lg, double* phi, double* eterm) {
     __shared__ GroupShared<false> S;
     __shared__ Rep Rs;
     load_rep(Rs, reps + r);
