@@ -929,7 +929,7 @@ extern "C" bhmc_status bhmc_energy_grad(bhmc_tree* t, int32_t replica, double* d
     w.G = (double4*)(t->gwork + lb);
     w.Gt = (double4*)(t->gwork + lb + gb);
     w.fcell = (int*)(t->gwork + lb + gb + tb);
-    w.ncell = h.ncell; w.nleaf = h.nleaf; w.nsrc = h.nsrc; w.n = n; w.nline = h.nline;
+    w.nsrc = h.nsrc; w.n = n; w.nline = h.nline;
     for (;;) {
         t->ops->grad(t->stream, t->reps, replica, w, dEdr_dev, dEdq_dev, t->eterm, energy_grid_bound(t));
         HIP_TRY(hipGetLastError());

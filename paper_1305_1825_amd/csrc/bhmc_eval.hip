@@ -641,11 +641,7 @@ __device__ __forceinline__ double row_sum4_scatter(double a, double b, double c,
 
 // ------------------------------------------------------------ traversal state
 constexpr uint32_t kCellMask = 0xFFFFFFu;
-constexpr uint32_t kFlagIon = 1u << 28, kFlagImg = 1u << 29, kFlagDirect = 1u << 30;
-
-__device__ __forceinline__ uint32_t pack(int cell, int t, uint32_t flags) {
-    return (uint32_t)cell | ((uint32_t)t << 24) | flags;
-}
+constexpr uint32_t kFlagIon = 1u << 28, kFlagImg = 1u << 29;
 
 // base + the lanes below this one in the ballot b: two instructions, the addition with them
 __device__ __forceinline__ int rank_below(uint64_t b, int base) {
@@ -962,9 +958,17 @@ __device__ __forceinline__ void near_pass_mc(const RepU& R, Trav<2, BLOCK>& S, i
 }
 
 // Breadth-first MAC traversal (Sec. 3.2) of the two targets of a move from
-// the fs0 entries of level level0 in front[0]; otherwise as traverse():
-// deterministic lists, hook once per level, res[0..1] the potentials (the
-// same in every thread), S.err / S.overlap / S.coincide as there.
+// the fs0 entries of level level0 in front[0].  A level is taken BLOCK entries at a
+// time: every lane classifies one, and ballots and one barrier hand out places in the
+// far, near and flagged lists and the next frontier in the order of the entries, so
+// every list, and with it every sum, is the same from run to run.  Full lists are
+// evaluated on the way, what is left at the end.  A frontier lives in LDS up to lcap
+// entries; a level that outgrows them moves to the workgroup's HBM region, what it has
+// written so far first, and the levels after it stay there.  hook(level) is called once
+// a level.  On return res[0..1] are the potentials (the same in every thread); S.err is
+// 0 or the check that failed (kErrFrontier: no room for a frontier, kErrStack: another
+// list; then res is not set); S.overlap: an ion other than the mover within tau of the
+// new position; S.coincide: a source at a target.
 template <bool F32, int BLOCK, class Hook>
 __device__ int traverse_mc(const RepU& R, Trav<2, BLOCK>& S, int* cnt2, Hook&& hook, int fs0, int level0,
                            double (&res)[2]) {
@@ -975,7 +979,6 @@ __device__ int traverse_mc(const RepU& R, Trav<2, BLOCK>& S, int* cnt2, Hook&& h
     double acc[2] = {0.0, 0.0};
     int cur = 0, fs = fs0, far_n = 0, near_n = 0, nflag = 0, buf = 0;
     bool failed = false, frontier_full = false;
-    // the frontier: LDS up to lcap entries, then HBM (see traverse)
     uint32_t* const gfr = spill_region(R.spill, R.spill_regions, R.spill_words);
     const int gcap = gfr ? (int)(R.spill_words / 2 < 0x7FFFFFFF ? R.spill_words / 2 : 0x7FFFFFFF) : 0;
     const int lcap = R.fcap < TS::FCAP ? R.fcap : TS::FCAP;

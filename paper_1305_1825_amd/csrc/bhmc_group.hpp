@@ -56,7 +56,7 @@ struct GroupShared {
     int flag_cell[kGT];
     double ctr[4];                 // the group's bounding sphere
     double red[NW][kGT][2];
-    int nt, near_tot, err;
+    int nt, err;
     uint64_t wcnt[2][NW];
     uint64_t wsum[NW + 1];
 };

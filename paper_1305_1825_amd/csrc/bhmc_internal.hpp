@@ -82,7 +82,7 @@ struct GradWork {
     double4* G;           // per source: dE/dx, dE/dy, dE/dz, dE/dq through its source role; follows L
     double4* Gt;          // per ion: the same through its target role
     int* fcell;           // per ion: the far cell holding its own image in its traversal, or -1 (n)
-    int ncell, nleaf, nsrc, n;
+    int nsrc, n;
     int nline;            // line images per ion (multiple-image model), 0 without
 };
 

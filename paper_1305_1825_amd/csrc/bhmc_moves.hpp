@@ -96,7 +96,6 @@ struct BTrav {
     uint64_t wcnt[2][kChunk][NW];
     double red[4 * NW][kBT];
     uint32_t mi[NTERM];
-    HTab ht;
     int cnt2[2];
 };
 
@@ -1152,7 +1151,6 @@ __global__ void __launch_bounds__(BLOCK) k_mcb(Rep* reps, McArgs A) {
     __shared__ int s_r;
     const int tid = threadIdx.x;
     for (int k = tid; k < NTERM; k += BLOCK) S.mi[k] = mi_code(k);
-    fill_htab(S.ht);
 #ifdef BHMC_PHASE_TIMERS
     for (int k = tid; k < kNumPhases; k += BLOCK) s_phase[k] = 0;
 #endif
