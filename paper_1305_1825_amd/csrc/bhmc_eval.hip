@@ -483,23 +483,24 @@ constexpr HRows make_hrows() {
 }
 __device__ const HRows c_hrows = make_hrows();
 
-// sum_n T_n M^n in the Cartesian form, each T_n folded into the sum as soon as it exists
-template <int K, class MP>
+// sum_n T_n M^n in the Cartesian form, each T_n folded into the sum as soon as it exists.  LEAN:
+// the moments are read two at a time where they are used, for registers, instead of all ahead.
+template <bool LEAN, int K, class MP>
 __device__ __forceinline__ void cart_rec(double (&T)[NTERM], double Rx, double Ry, double Rz, double ir2,
                                          MP __restrict__ Mc, double& acc) {
     if constexpr (K < NTERM) {
         if constexpr (K > 0) t_step<K>(T, Rx, Ry, Rz, ir2);
         acc = fma(T[K], Mc[K], acc);
-        if constexpr (K % 2 == 1) __builtin_amdgcn_sched_barrier(0);  // or the moments are all loaded ahead
-        cart_rec<K + 1>(T, Rx, Ry, Rz, ir2, Mc, acc);
+        if constexpr (LEAN && K % 2 == 1) __builtin_amdgcn_sched_barrier(0);
+        cart_rec<LEAN, K + 1>(T, Rx, Ry, Rz, ir2, Mc, acc);
     }
 }
-template <class MP>
+template <bool LEAN, class MP>
 __device__ __forceinline__ double cart_eval(double Rx, double Ry, double Rz, MP Mc) {
     double T[NTERM];
     T[0] = rsqrt_nr(Rx * Rx + Ry * Ry + Rz * Rz);
     double acc = 0.0;
-    cart_rec<0>(T, Rx, Ry, Rz, T[0] * T[0], Mc, acc);
+    cart_rec<LEAN, 0>(T, Rx, Ry, Rz, T[0] * T[0], Mc, acc);
     return acc;
 }
 
@@ -733,7 +734,7 @@ __device__ __attribute__((noinline)) double flagged_value(const Rep& R, int c, d
                                                           double4 si, bool img, double4 sk) {
     const double4 g = gload(R.cgeo + c);
     double v;
-    if (F32 && R.M32) v = cart_eval(g.x - x, g.y - y, g.z - z, grow(R.M + (size_t)c * MSTR));
+    if (F32 && R.M32) v = cart_eval<false>(g.x - x, g.y - y, g.z - z, grow(R.M + (size_t)c * MSTR));
     else v = far_row(grow(R.H + (size_t)c * HSTR), x, y, z);
     if (ion) v -= si.w * point_expansion(g.x - x, g.y - y, g.z - z, si.x - g.x, si.y - g.y, si.z - g.z);
     if (img) v -= sk.w * point_expansion(g.x - x, g.y - y, g.z - z, sk.x - g.x, sk.y - g.y, sk.z - g.z);
