@@ -406,7 +406,9 @@ static bhmc_status reserve(Arena& a, size_t bytes) {
 // Arenas of a new batch's replicas cut from one allocation: beyond 1 MiB an allocation costs about
 // 10 us to make and 60 to free, and host memory freed after it waits 240.  Created and freed with an
 // allocation a replica / with one: 20 replicas of 300 to 1,700 ions, some of whose trees pass that
-// size, 1.36 / 0.69 ms, 200 of them 42.8 / 1.8 ms.  If it fails each replica gets its own.
+// size, 1.36 / 0.69 ms, 200 of them 42.8 / 1.8 ms.  Only where arenas take 1 MiB at most on average:
+// a slice is lost once its replica's tree outgrows it.  If it fails each replica gets its own.
+constexpr size_t kSliceMean = (size_t)1 << 20;
 static void reserve_slices(std::vector<Arena>& arenas, void** block, const std::vector<int>& list,
                            const std::vector<size_t>& bytes) {
     size_t total = 0;
@@ -414,7 +416,7 @@ static void reserve_slices(std::vector<Arena>& arenas, void** block, const std::
         if (arenas[list[k]].p) return;
         total += align_up(bytes[k]);
     }
-    if (list.size() < 2 || *block) return;
+    if (list.size() < 2 || *block || total > list.size() * kSliceMean) return;
     if (hipMalloc(block, total) != hipSuccess) {
         (void)hipGetLastError();
         *block = nullptr;
@@ -577,8 +579,6 @@ static bhmc_status current_moments(bhmc_tree* t, int r) {
     return BHMC_OK;
 }
 
-constexpr size_t kSliceMean = (size_t)4 << 20;  // bytes of a tree
-
 // Build (or rebuild) the replicas in `list`.  x == nullptr rebuilds from the
 // replicas' own current ions.
 static bhmc_status build_list(bhmc_tree* t, const std::vector<int>& list, const double* x,
@@ -642,10 +642,8 @@ static bhmc_status build_list(bhmc_tree* t, const std::vector<int>& list, const 
         if (h.status) return fail(h.status == -1 ? BHMC_EINVAL : BHMC_EOUTSIDE, "replica %d: %s", r, status_name(h.status));
         if (h.ncell >= (1 << 24)) return fail(BHMC_EINVAL, "replica %d: %d cells exceed 2^24", r, h.ncell);
     }
-    // a slice is lost once its replica's tree outgrows it: only where trees are small
-    size_t total = 0;
-    for (size_t k = 0; k < list.size(); ++k) total += bytes[k] = phase2_bytes(t, list[k]);
-    if (total <= list.size() * kSliceMean) reserve_slices(t->arena2, &t->block2, list, bytes);
+    for (size_t k = 0; k < list.size(); ++k) bytes[k] = phase2_bytes(t, list[k]);
+    reserve_slices(t->arena2, &t->block2, list, bytes);
     for (int r : list) if ((st = alloc_phase2(t, r))) return st;
     if ((st = upload(t))) return st;
     if (wide) {
