@@ -566,7 +566,11 @@ def main():
         "stats": res["stats"],
         "autotune": res["autotune"],
         "mc_kernel_ms_per_step": mc_ms,
-        "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+        "roofline": {"bound": "latency",
+                     "bound_by": "dependent levels and their barriers on one CU, whose vector instructions issue in "
+                                 "30 % of its cycles (profiles/counters_valu_lds_l1_harmonic_rows.md); the figures "
+                                 "here are its algorithmic bytes against HBM and one CU's L2 path",
+                     "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": traffic("chain", c["moves"]),
                      "achievable": achievable, "frac_achievable": achieved / achievable,
                      "per_cu": {"peak": CU_L2_GBS, "frac": achieved / CU_L2_GBS,
@@ -615,7 +619,11 @@ def main():
         b = run_batched(256, args.batched_sweeps, GATED_REPLICAS)
         bpm = batched_bytes_per_move(GATED_REPLICAS)
         ach = bpm * b["moves_per_s"] / 1e9
-        b["roofline"] = {"bound": "hbm", "achieved": ach, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+        b["roofline"] = {"bound": "latency",
+                         "bound_by": "sequential chains, a CU each, the largest replicas' last: CUs busy half of the "
+                                     "sweep, vector instructions in 25 % of their busy cycles "
+                                     "(profiles/counters_valu_lds_l1_harmonic_rows.md)",
+                         "achieved": ach, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                          "frac": ach / HBM_PEAK_GBS, "achievable": achievable, "frac_achievable": ach / achievable,
                          "traffic": traffic("sweep", b["moves"] // b["sweeps"]),
                          "kernel": kernel_label(b["autotune"], GATED_REPLICAS["p"]) + ", one sweep per launch",

@@ -87,7 +87,11 @@ enum { BHMC_REASON_NONE = 0, BHMC_REASON_WALL = 1, BHMC_REASON_OVERLAP = 2 };
  *              moments themselves and their repair stay FP64).  The rounding
  *              this adds is at most about (C(p+3,3) + 3p + 4) 2^-24 times the
  *              far field's magnitude sum_A sum_n |T_n M_A^n|.  The gradient is
- *              always FP64.  0: everything in FP64.
+ *              always FP64.  0: everything in FP64.  This is a choice of
+ *              precision, not of speed: in FP64 the traversals read (p+1)^2
+ *              harmonic coefficients a cell where the single-precision form sums
+ *              C(p+3,3) Cartesian terms, and moves are faster with far_fp32 = 0
+ *              (10^4 ions, theta = 0.4, p = 5: 144,000 against 117,000 moves/s).
  *   line_images 0, or M in 1..8 (needs images = 1, n0 = 0, eps_in <= eps_out):
  *              the multiple-image model of the dielectric sphere that the paper
  *              names in Sec. 1 and Sec. 5.  The exact reaction potential of a
@@ -282,7 +286,7 @@ bhmc_status bhmc_set_launch_shape(bhmc_tree* tree, int32_t shape);
  * rounding of its sums (about 1e-15 relative).  The
  * far-field source side is summed with device atomics, so the gradient can
  * differ between calls by rounding.  The library keeps a workspace of
- * about 8 (ncell * round4(C(p+3,3)) + 4.5 nsrc + 5 n) bytes per handle. */
+ * about 8 (ncell * ((p+1)^2 + 4) + 4 nsrc + 4.5 n) bytes per handle. */
 bhmc_status bhmc_energy_grad(bhmc_tree* tree, int32_t replica, double* dEdr_dev, double* dEdq_dev,
                              double* E_host);
 
@@ -304,9 +308,9 @@ bhmc_status bhmc_set_moves_per_round(bhmc_tree* tree, int32_t moves, int32_t* ef
 /* Phase timers of the batched Metropolis kernel, present only in a library
  * built with phase timers (python -m paper_1305_1825_amd.build --phase-timers):
  * ticks of the device's constant clock summed over every round run on this
- * handle's expansion order -- set-up, traversal levels, corrected moments and
- * scan, far cells, near leaves, hard cores below far cells, path descents,
- * corrections, decisions, leaf index arrays, moments -- then the number of
+ * handle's expansion order -- set-up, traversal levels, the scan and list of
+ * near slots, far cells, near leaves, hard cores below far cells, path descents,
+ * corrections, decisions, leaf index arrays, expansion rows -- then the number of
  * rounds and of moves, the level loop's chunks, frontier entries, empty
  * entries, far and near list entries, and the ticks the root-path descents
  * and the commit prefetch spend inside the level loop.  ticks: host, n values; count (nullable, host) receives

@@ -4,9 +4,10 @@
 //
 // Traversal (Sec. 3.2).  A workgroup evaluates the potential at a few targets
 // at once.  The MAC traversal runs breadth first: the frontier of one level
-// sits in LDS, every lane classifies one (cell, target) entry, and a block
-// scan hands out slots in the far list, the near list and the next frontier,
-// so the order of every list, and therefore every sum, is deterministic.
+// sits in LDS, every lane classifies one cell for the targets that reached it,
+// and a scan of the lanes' counts hands out slots in the far list, the near list
+// and the next frontier, so the order of every list, and therefore every sum, is
+// deterministic.
 // Far cells are evaluated lane-per-cell in the harmonic form of the expansion
 // of eq. 3.3 (below); near leaves are flattened
 // into (leaf, slot) pairs read from the leaf-ordered pool, so the lanes of a
@@ -888,8 +889,7 @@ __device__ void overlap_below_far(const RepU& R, Trav<NTG, BLOCK>& S, int* cnt2)
 // the targets summing every source below it directly by the N_0 rule (bits
 // 26-27) and the two exclusion flags.  Each target takes exactly the decisions
 // of its own traversal.  A lane reads a far cell's row once and evaluates both
-// targets from it (the rows' way through the CU's L1, 64 B a clock, is what
-// bounds the far cells), and likewise near sources.
+// targets from it, and likewise near sources.
 constexpr int kMaskSh = 24, kDirSh = 26;
 
 template <bool F32, int BLOCK>

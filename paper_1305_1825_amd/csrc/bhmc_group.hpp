@@ -13,11 +13,13 @@
 // Far cells go to a list with their target masks, near leaves likewise; the lists are
 // evaluated when they fill up and at the end.
 //
-// What bounds it: the far rows' way through the CU's L1 and the FP64 issue of their
-// evaluation, so a row is read once for four targets.  Energy of 10^5 ions + images
-// (theta = 0.5, p = 6): 2.88 -> 0.90 ms against groups of four key positions whose targets
-// each had frontier entries and lane-per-(cell, target) rows of their own; 199,999 ions at
-// p = 8: 13.8 -> 2.0 ms; 10^4 ions (theta = 0.4, p = 5): 0.25 -> 0.14 ms.
+// What bounds it: latencies at two waves a SIMD, by the counters of 10^5 ions + images (theta =
+// 0.5, p = 6): waves wait 56 % of their cycles, vector instructions (69 % of them FP64 arithmetic)
+// issue in 47 % of the time, LDS bank conflicts cost 2 % of its accesses.  A row read once for four
+// targets has more arithmetic between its loads: that system 2.88 -> 0.90 ms against groups of four key
+// positions whose targets each had frontier entries and lane-per-(cell, target) rows of their own
+// (0.81 with the level loop's later changes); 199,999 ions at p = 8: 13.8 -> 2.0 ms; 10^4 ions
+// (theta = 0.4, p = 5): 0.25 -> 0.13 ms.
 constexpr int kGT = 16;
 constexpr int kGroupBlock = 256;
 constexpr int kStage = 256;     // near sources staged in LDS at a time
@@ -437,9 +439,11 @@ __global__ void __launch_bounds__(kGroupBlock) __attribute__((amdgpu_waves_per_e
 // and the (p + 1)^2 terms of 16 cells and 16 targets end in (p + 1)^2 / 4 of them; they go
 // through LDS to one atomic per cell and term, consecutive lanes on consecutive words.
 // (Summing 16 terms at a time across 16-lane rows by DPP exchanges took 105 instructions per
-// 16 terms, as much as the evaluation.)  Bound by FP64 issue: gradient of 10^5 ions + images
-// (theta = 0.5, p = 6) 9.46 -> 2.49 ms against the Cartesian form with 84 adjoint terms a
-// cell, 199,999 ions at p = 8 56.4 -> 7.1 ms, 10^4 ions (theta = 0.4, p = 5) 1.05 -> 0.40 ms.
+// 16 terms, as much as the evaluation.)  Gradient of 10^5 ions + images (theta = 0.5, p = 6)
+// 9.46 -> 2.39 ms against the Cartesian form with 84 adjoint terms a cell, 199,999 ions at p = 8
+// 56.4 -> 6.95 ms, 10^4 ions (theta = 0.4, p = 5) 1.05 -> 0.40 ms.  By the counters (p = 6 / 8)
+// vector instructions issue in 52 / 50 % of the time and the matrix cores are busy in 14 / 15 %, waves
+// wait 42 / 43 % of their cycles at two a SIMD, and bank conflicts add 43 / 46 % to the LDS's cycles.
 struct GradTerms { double phi, gx, gy, gz; };
 // phi and grad phi at X of a row: with the sums S = sum (.) zeta^m, E = sum (l + 1) (.) zeta^m over
 // the terms H_lm a_lm and U = dS/du (da_lm/du = (l - m) a_{l,m+1}, from the Gegenbauer form of a_lm),
@@ -447,10 +451,10 @@ struct GradTerms { double phi, gx, gy, gz; };
 // (each term is homogeneous of degree l in the scale of 1 / X).  wt J_lm joins D.
 // The columns go upwards, m = 0 .. p, each a_lm used as it comes: by the sums of its own column
 // and, as da_{l,m-1}/du, by U through the coefficients of the column below.  Neither the a_lm of
-// a column nor the powers of zeta are kept, so the order 8 evaluation fits 256 registers
-// (downwards with Horner's rule it spilled: 14.9 ms for 199,999 ions).
-// The column below in registers; at higher orders its words are read again, for registers
-// (10^5 ions, p = 6: 2.49 ms kept, 2.64 read again; at p = 8 keeping it would spill).
+// a column nor the powers of zeta are kept, so at order 8 only 29 of 256 registers spill (112 B a
+// lane; downwards with Horner's rule so many that 199,999 ions took 14.9 ms for 7.1).
+// The column below in registers; above order 6 its words are read again, for registers
+// (10^5 ions, p = 6: 2.49 ms kept, 2.64 read again).
 constexpr bool kKeepColumn = P <= 6;
 struct GradSums { double S, E, U, d0, d1, zr, zi, pr, pi; };
 

@@ -24,7 +24,10 @@
 // their root paths with the contributions applied in move order.  Every result is
 // the one the move-by-move chain gives, up to the rounding of the sums.
 
-constexpr int kBM = P <= 8 ? 8 : 2;  // trial moves per round (LDS: p = 8 with 8 moves just fits 160 KB)
+// Trial moves per round.  2 at orders 9 and 10: the Cartesian tables of the commit once left the LDS
+// room for no more.  The tables of harmonics would leave it for 8 (130 KB; 400 moves of 6,000 ions at
+// p = 10 then took 5.7 ms for 7.5), but callers are told the number (bhmc_set_moves_per_round).
+constexpr int kBM = P <= 8 ? 8 : 2;
 constexpr int kBT = 2 * kBM;                         // targets per round: 2b old, 2b + 1 new position
 // frontier / list entry: cell (bits 0-23), move (24-26), mask of the move's two targets (27-28),
 // the cell holds the move's own ion (29) or image (30)
@@ -210,7 +213,7 @@ __device__ int near_scan_mb(BTrav<BLOCK>& S, int near_n) {
 
 // Far cells, a lane per entry: the row is read once and evaluated at both targets of the
 // entry's move; acc[2b + t] of a lane holds its sum for target t of move b.  (Lane pairs
-// reading the same row, one target each, are bound by the rows' way through the CU's L1.)
+// reading the same row, one target each: 256 replicas at theta = 0.3, p = 5 368 ms a sweep, 347 so.)
 template <bool F32, int BLOCK>
 __device__ __forceinline__ void far_pass_mb(const RepU& R, BTrav<BLOCK>& S, const BMoves& MV, int far_n, int nflag,
                                             double (&acc)[kBT]) {
