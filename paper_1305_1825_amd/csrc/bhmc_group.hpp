@@ -410,8 +410,9 @@ __global__ void __launch_bounds__(kGroupBlock) __attribute__((amdgpu_waves_per_e
             if (c >= 0) {
                 const double4 k = gload(R.src + R.n + ion);
                 const double4 g = gload(R.cgeo + c);
-                // (inline: as a call it set the kernel's registers, 214 for 127 at order 4)
-                if (apart) ph += cart_eval<true>(g.x - x, g.y - y, g.z - z, grow(R.M + (size_t)c * MSTR));
+                // (inline: as a call it set the kernel's registers, 214 for 127 at order 4; from order 6 on
+                // two workgroups a CU fit either way)
+                if (apart) ph += cart_eval<(P <= 5)>(g.x - x, g.y - y, g.z - z, grow(R.M + (size_t)c * MSTR));
                 ph -= k.w * point_expansion(g.x - x, g.y - y, g.z - z, k.x - g.x, k.y - g.y, k.z - g.z);
             }
             if (S.err) {
