@@ -550,13 +550,19 @@ __device__ __forceinline__ double far_eval_f(double Rx, double Ry, double Rz, co
 // keeps M32, whose registers the FP32 recurrence (every T_n of eq. 3.4 at once) would otherwise set.
 // That recurrence is run once for each target of a move either way: from order 5 on a lane takes one
 // target (one after the other in a lane against a lane each: 400 moves of 6,000 ions, p = 10, 18.1 and
-// 13.8 ms, p = 6 4.00 and 3.73 ms), below it both (p = 2: 2.39 and 2.50 ms).
+// 13.8 ms, p = 6 4.00 and 3.73 ms), below it both (p = 2: 2.39 and 2.50 ms). One move at a time at p = 5:
+// 400 moves of 2,000 ions 7.1 and 6.7 ms, 256 replicas, 1,000 moves each, 25.4 and 25.9 ms.
+// The rounds of a 256-thread workgroup, with twice the far cells a lane, gain only from order 9 on
+// (both and apart: 256 replicas, 1,000 moves at p = 5 14.3 and 15.8 ms, p = 8 30.2 and 32.8, p = 9 49.6
+// and 49.8, p = 10 64.1 and 60.6; 400 moves of 2,000 ions at p = 8 5.0 and 5.0, p = 10 12.8 and 11.7).
 constexpr bool kF32Apart = P > 4;
-// Values at the two targets of a move.
+template <int BLOCK>
+constexpr bool kF32RoundsApart = P > (BLOCK > 256 ? 4 : 8);
+// Values at the two targets of a move (F32: single precision where a lane takes both).
 template <bool F32>
 __device__ __forceinline__ void far_value2(const RepU& R, int c, const double (&tx)[2], const double (&ty)[2],
                                            const double (&tz)[2], double (&v)[2]) {
-    if (F32 && !kF32Apart && R.M32) {
+    if (F32 && R.M32) {
         const double4 g = gload(R.cgeo + c);
         v[0] = far_eval_f(g.x - tx[0], g.y - ty[0], g.z - tz[0], R.M32 + (size_t)c * MSTR);
         __builtin_amdgcn_sched_barrier(0);  // one recurrence's T_n in registers at a time
@@ -912,7 +918,7 @@ __device__ __forceinline__ void far_pass_mc(const RepU& R, Trav<2, BLOCK>& S, in
             if (c >= R.ncell) { S.err = kErrFarCell; continue; }
             const double tx[2] = {S.tx[0], S.tx[1]}, ty[2] = {S.ty[0], S.ty[1]}, tz[2] = {S.tz[0], S.tz[1]};
             double v[2];
-            far_value2<F32>(R, c, tx, ty, tz, v);
+            far_value2<F32 && !kF32Apart>(R, c, tx, ty, tz, v);
             acc[0] += ((e >> kMaskSh) & 1u) ? v[0] : 0.0;
             acc[1] += ((e >> kMaskSh) & 2u) ? v[1] : 0.0;
         }

@@ -219,7 +219,7 @@ __device__ __forceinline__ void far_pass_mb(const RepU& R, BTrav<BLOCK>& S, cons
                                             double (&acc)[kBT]) {
     const int tid = fresh_tid();
     const int tb = tid & 1;
-    if (F32 && kF32Apart && R.M32) {
+    if (F32 && kF32RoundsApart<BLOCK> && R.M32) {
         for (int j2 = tid; j2 < 2 * far_n; j2 += BLOCK) {
             const uint32_t e = S.farl[j2 >> 1];
             if (!((e >> (kOpSh + tb)) & 1u)) continue;
@@ -237,7 +237,7 @@ __device__ __forceinline__ void far_pass_mb(const RepU& R, BTrav<BLOCK>& S, cons
             const double tx[2] = {MV.tx[2 * b], MV.tx[2 * b + 1]}, ty[2] = {MV.ty[2 * b], MV.ty[2 * b + 1]};
             const double tz[2] = {MV.tz[2 * b], MV.tz[2 * b + 1]};
             double v[2];
-            far_value2<F32>(R, c, tx, ty, tz, v);
+            far_value2<F32 && !kF32RoundsApart<BLOCK>>(R, c, tx, ty, tz, v);
             add_pair(acc, b, ((e >> kOpSh) & 1u) ? v[0] : 0.0, ((e >> kOpSh) & 2u) ? v[1] : 0.0);
         }
     }

@@ -1,6 +1,6 @@
-"""The single-precision far field of moves on both sides of the order (5) from which a lane takes
-one target of a move instead of both, within the rounding bound K 2^-24 sum |T_n M^n| of a far cell's single-precision value,
-K = C(p+3,3) + 3p + 4."""
+"""The single-precision far field of moves on both sides of the order from which a lane takes one
+target of a move instead of both (5; 9 in the rounds of 256-thread workgroups), within the rounding
+bound K 2^-24 sum |T_n M^n| of a far cell's single-precision value, K = C(p+3,3) + 3p + 4."""
 import math
 
 import numpy as np
@@ -55,11 +55,22 @@ def test_energy_changes(p, n0, lines):
 @pytest.mark.parametrize("p", [4, 5, 10])
 @pytest.mark.parametrize("rounds", [0, 1])
 def test_chains(p, rounds):
+    check_chain(p, rounds, 0)
+
+
+@pytest.mark.parametrize("p", [5, 8, 9])
+def test_rounds_of_256_threads(p):
+    """There a lane takes one target from order 9 on."""
+    check_chain(p, 0, 1)
+
+
+def check_chain(p, rounds, shape):
     P, x, y, z, q = system(500, p)
     n, moves = len(x), 300
     g = bhmc.Tree(dict(P, far_fp32=1), x, y, z, q)
+    g.set_shape(shape)
     g.set_moves_per_round(rounds)
-    print("p=%d rounds=%d" % (p, rounds), flush=True)
+    print("p=%d rounds=%d shape=%d" % (p, rounds, shape), flush=True)
     bits = g.mc_run(seed=1, n_moves=moves, step=1.0, accept_bits=True)["accept"].cpu().numpy()
     o = O.Tree(P, x, y, z, q)
     ro = o.mc_run(seed=1, replica=0, move0=0, n_moves=moves, step=1.0)
