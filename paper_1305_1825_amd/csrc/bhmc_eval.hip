@@ -552,10 +552,13 @@ __device__ __forceinline__ double far_eval_f(double Rx, double Ry, double Rz, co
 // target (one after the other in a lane against a lane each: 400 moves of 6,000 ions, p = 10, 18.1 and
 // 13.8 ms, p = 6 4.00 and 3.73 ms), below it both (p = 2: 2.39 and 2.50 ms). One move at a time at p = 5:
 // 400 moves of 2,000 ions 7.1 and 6.7 ms, 256 replicas, 1,000 moves each, 25.4 and 25.9 ms.
-// The rounds of a 256-thread workgroup, with twice the far cells a lane, gain only from order 9 on
-// (both and apart: 256 replicas, 1,000 moves at p = 5 14.3 and 15.8 ms, p = 8 30.2 and 32.8, p = 9 49.6
-// and 49.8, p = 10 64.1 and 60.6; 400 moves of 2,000 ions at p = 8 5.0 and 5.0, p = 10 12.8 and 11.7).
-constexpr bool kF32Apart = P > 4;
+// A 256-thread workgroup has twice the far cells a lane and gains from a higher order on: its rounds from
+// 9 (both and apart: 256 replicas, 1,000 moves at p = 5 14.3 and 15.8 ms, p = 8 30.2 and 32.8, p = 9 49.6
+// and 49.8, p = 10 64.1 and 60.6; 400 moves of 2,000 ions at p = 8 5.0 and 5.0, p = 10 12.8 and 11.7), one
+// move at a time from 8 (500 moves at p = 5 14.0 and 14.4 ms, p = 7 19.8 and 20.2, p = 8 24.8 and 24.9,
+// p = 9 30.9 and 30.3; 400 moves of 2,000 ions at p = 8 10.9 and 9.9).
+template <int BLOCK>
+constexpr bool kF32Apart = P > (BLOCK > 256 ? 4 : 7);
 template <int BLOCK>
 constexpr bool kF32RoundsApart = P > (BLOCK > 256 ? 4 : 8);
 // Values at the two targets of a move (F32: single precision where a lane takes both).
@@ -902,7 +905,7 @@ template <bool F32, int BLOCK>
 __device__ __forceinline__ void far_pass_mc(const RepU& R, Trav<2, BLOCK>& S, int far_n, int nflag,
                                             double (&acc)[2]) {
     const int t = (int)(threadIdx.x & 1);
-    if (F32 && kF32Apart && R.M32) {
+    if (F32 && kF32Apart<BLOCK> && R.M32) {
         for (int j2 = threadIdx.x; j2 < 2 * far_n; j2 += BLOCK) {
             const uint32_t e = S.farl[j2 >> 1];
             if (!((e >> (kMaskSh + t)) & 1u)) continue;
@@ -918,7 +921,7 @@ __device__ __forceinline__ void far_pass_mc(const RepU& R, Trav<2, BLOCK>& S, in
             if (c >= R.ncell) { S.err = kErrFarCell; continue; }
             const double tx[2] = {S.tx[0], S.tx[1]}, ty[2] = {S.ty[0], S.ty[1]}, tz[2] = {S.tz[0], S.tz[1]};
             double v[2];
-            far_value2<F32 && !kF32Apart>(R, c, tx, ty, tz, v);
+            far_value2<F32 && !kF32Apart<BLOCK>>(R, c, tx, ty, tz, v);
             acc[0] += ((e >> kMaskSh) & 1u) ? v[0] : 0.0;
             acc[1] += ((e >> kMaskSh) & 2u) ? v[1] : 0.0;
         }

@@ -1,5 +1,5 @@
 """The single-precision far field of moves on both sides of the order from which a lane takes one
-target of a move instead of both (5; 9 in the rounds of 256-thread workgroups), within the rounding
+target of a move instead of both (5; in 256-thread workgroups 8, in their rounds 9), within the rounding
 bound K 2^-24 sum |T_n M^n| of a far cell's single-precision value, K = C(p+3,3) + 3p + 4."""
 import math
 
@@ -58,10 +58,10 @@ def test_chains(p, rounds):
     check_chain(p, rounds, 0)
 
 
-@pytest.mark.parametrize("p", [5, 8, 9])
-def test_rounds_of_256_threads(p):
-    """There a lane takes one target from order 9 on."""
-    check_chain(p, 0, 1)
+@pytest.mark.parametrize("p,rounds", [(5, 0), (8, 0), (9, 0), (7, 1), (8, 1)])
+def test_256_threads(p, rounds):
+    """There a lane takes one target from order 9 on in rounds, from 8 on one move at a time."""
+    check_chain(p, rounds, 1)
 
 
 def check_chain(p, rounds, shape):
